@@ -101,16 +101,16 @@ typedef struct lb_options {
                                  kept alive until lb_destroy returns           */
   int device;                 /* HIP device ordinal; -1: current device         */
   int check_nonfinite;        /* nonzero: lb_step scans for NaN/Inf afterwards  */
-  int fuse_steps;             /* 0: lb_step advances K time steps per launch
-                                 (register-resident multi-step sweep; same
-                                 result bit for bit; K = 7 for LB_F64, 6 for
-                                 the shifted formats) on lattices of at least
-                                 48^2 nodes, where it is faster, a remainder of
-                                 2 .. K-1 steps in one shorter fused launch
-                                 (periodic OReg lattices) and one step per
-                                 launch below that size and otherwise;
+  int fuse_steps;             /* 0: lb_step advances several time steps per
+                                 launch, same result bit for bit.  The kernel
+                                 and the steps per launch follow from the
+                                 lattice's size and storage: tiles exchanged
+                                 through LDS on small lattices, blocks held in
+                                 registers on middle ones, column strips on
+                                 large ones (up to 7 steps per launch for
+                                 LB_F64, 6 for the shifted formats);
                                  1: one sweep launch per time step;
-                                 2: fused launches whatever the size           */
+                                 2: as 0                                       */
 } lb_options;
 
 /* Defaults: 0 x 0, tau 1, theta 1/3, guided, LB_F64, OReg, periodic, rho0 1,

@@ -549,14 +549,6 @@ hipError_t launch_tile_map(const LatticeDesc* d, int n, int* tile_map, int64_t t
 
 int fused_strip_width(int st) { return 64 - 2 * fused_levels(st); }
 
-bool fused_worthwhile(int st, int nx, int ny) {
-  // With the row count chosen per lattice (fused_rows), fused launches beat
-  // single-step ones on MI355X from 64^2 nodes up in every storage format
-  // (1.1-1.3x at 64^2..192^2, 2-3x at 384^2..1024^2, 3.6x for F64 at
-  // 4096^2) and tie at 32^2.
-  return fused_levels(st) > 1 && (int64_t)nx * ny >= 48 * 48;
-}
-
 hipError_t launch_batched_fused(int eq, int st, const LatticeDesc* d, const int* item_map,
                                 int64_t items, int64_t T, hipStream_t s) {
   if (items <= 0) return hipSuccess;

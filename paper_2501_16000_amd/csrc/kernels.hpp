@@ -11,6 +11,7 @@
 #include <stdint.h>
 
 #include "d2q9.hpp"
+#include "plan.hpp"
 
 namespace oreg {
 
@@ -38,9 +39,6 @@ int fused_levels(int st);
 // Wavefronts that sweep one strip of a fused launch together (1 or 4).
 int fused_wavefronts(int st);
 
-// Whether fused launches beat single-step launches for this lattice size.
-bool fused_worthwhile(int st, int nx, int ny);
-
 // Whether a fused launch of `levels` steps (2 .. fused_levels(st)) is
 // compiled for this collision and boundary: the full count always, fewer
 // steps for periodic OReg lattices.
@@ -67,6 +65,15 @@ double fused_cost(int st, int nx, int ny, int H, const FusedShape& sh, int K);
 
 // Output rows per strip (a multiple of 3) that minimise fused_cost.
 int fused_rows(int st, int nx, int ny, const FusedShape& sh, int levels);
+
+// `levels` time steps in one launch of the tile sweep (tile.hip) or the block
+// sweep (block.hip): src -> dst.
+hipError_t launch_tile_sweep(int eq, int coll, int bc, int st, const void* src, void* dst,
+                             const Geometry& g, const Coef64& c, const TileShape& sh, int levels,
+                             hipStream_t s);
+hipError_t launch_block_sweep(int eq, int coll, int bc, int st, const void* src, void* dst,
+                              const Geometry& g, const Coef64& c, const BlockShape& b, int levels,
+                              hipStream_t s);
 
 // g from fields (device FP64 [ny][nx] each); counts invalid input nodes
 // (non-finite value or rho <= 0) into *bad.

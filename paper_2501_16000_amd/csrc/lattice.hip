@@ -27,6 +27,10 @@ struct lb_lattice {
   size_t elem = 8;                    // bytes per stored population
   Geometry geo{};
   int fused_rows[8] = {};             // output rows per strip of fused launches, by step count
+  bool strips = false;                // multi-step launches use the strip pipeline
+  int cus = 256;                      // compute units of the device
+  StepPlan best;                      // the multi-step launch with the least time per step
+  StepPlan exact[kPlanLevels + 1];    // plans for launches of exactly L steps (us = 0: not made yet)
   Coef64 coef{};
   double theta_energy = 0.0;          // theta of p = rho theta in the energy sum
   bool initialized = false;
@@ -176,6 +180,18 @@ lb_status scratch_ptr(lb_lattice* h, int dev, double** out) {
   return LB_OK;
 }
 
+// The plan for a launch of exactly L steps (made on first use and kept: it
+// depends on the lattice's size and storage only).
+const StepPlan& step_plan(lb_lattice* h, int L) {
+  if (L == h->best.levels) return h->best;
+  StepPlan& p = h->exact[L];
+  if (p.us == 0) {
+    p = plan_levels(h->opt.storage, h->geo.nx, h->geo.ny, L, h->cus);
+    if (p.us < 0) p.kind = StepKind::sweep;
+  }
+  return p;
+}
+
 lb_status finish_init(lb_lattice* h) {
   unsigned int bad = 0;
   HIP_TRY(h, hipMemcpyAsync(&bad, h->counter, sizeof bad, hipMemcpyDeviceToHost, h->stream));
@@ -276,10 +292,17 @@ lb_status lb_create_ex(const lb_options* opt, lb_lattice** out) {
   if (e != hipSuccess) return cleanup(hip_fail(nullptr, e, "hipMalloc(aux)"));
   e = hipMalloc((void**)&h->counter, sizeof(unsigned int));
   if (e != hipSuccess) return cleanup(hip_fail(nullptr, e, "hipMalloc(counter)"));
-  for (int L = 2; L <= fused_levels(h->opt.storage); ++L)
-    if (fused_levels_available(h->opt.collision, h->opt.boundary_x, h->opt.storage, L))
-      h->fused_rows[L] = fused_rows(h->opt.storage, h->geo.nx, h->geo.ny,
-                                    fused_shape(h->opt.storage, L), L);
+  if (hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    h->cus = 256;
+  h->strips = plan_strips(h->opt.storage, h->geo.nx, h->geo.ny);
+  if (h->strips) {
+    for (int L = 2; L <= fused_levels(h->opt.storage); ++L)
+      if (fused_levels_available(h->opt.collision, h->opt.boundary_x, h->opt.storage, L))
+        h->fused_rows[L] = fused_rows(h->opt.storage, h->geo.nx, h->geo.ny,
+                                      fused_shape(h->opt.storage, L), L);
+  } else {
+    h->best = plan_best(h->opt.storage, h->geo.nx, h->geo.ny, h->cus);
+  }
   *out = h;
   return LB_OK;
 }
@@ -324,31 +347,53 @@ lb_status lb_step(lb_lattice* h, int64_t n) {
   if (n == 0) return LB_OK;
   DeviceScope ds(h->device);
   if (!ds.ok) return fail(h, LB_EDEVICE, "cannot select device %d", h->device);
-  // Fused launches advance K steps each.  A remainder of two or more steps
-  // runs as one shorter fused launch where that is compiled (periodic OReg:
-  // it reads and writes the state once, where single steps would do so per
-  // step), otherwise, and for a single step, one step per launch.
-  const bool fuse =
-      h->opt.fuse_steps == 2 ||
-      (h->opt.fuse_steps == 0 && fused_worthwhile(h->opt.storage, h->geo.nx, h->geo.ny));
-  const int64_t K = fuse ? fused_levels(h->opt.storage) : 1;
   int64_t left = n;
-  while (K > 1 && left >= 2) {
-    const int L = (int)std::min<int64_t>(K, left);
-    if (!fused_levels_available(h->opt.collision, h->opt.boundary_x, h->opt.storage, L)) break;
-    HIP_TRY(h, launch_fused_sweep(h->opt.equilibrium, h->opt.collision, h->opt.boundary_x,
-                                  h->opt.storage, h->buf[h->cur], h->buf[1 - h->cur], h->geo,
-                                  h->coef, h->fused_rows[L], L, h->stream));
+  auto done = [&](int L) {
     h->cur = 1 - h->cur;
     h->t += L;
     left -= L;
+  };
+  if (h->opt.fuse_steps != 1 && h->strips) {
+    // Strip launches advance K steps each.  A remainder of two or more steps
+    // runs as one shorter launch where that is compiled (periodic OReg: it
+    // reads and writes the state once, where single steps would do so per
+    // step), otherwise, and for a single step, one step per launch.
+    const int64_t K = fused_levels(h->opt.storage);
+    while (left >= 2) {
+      const int L = (int)std::min<int64_t>(K, left);
+      if (!fused_levels_available(h->opt.collision, h->opt.boundary_x, h->opt.storage, L)) break;
+      HIP_TRY(h, launch_fused_sweep(h->opt.equilibrium, h->opt.collision, h->opt.boundary_x,
+                                    h->opt.storage, h->buf[h->cur], h->buf[1 - h->cur], h->geo,
+                                    h->coef, h->fused_rows[L], L, h->stream));
+      done(L);
+    }
+  } else if (h->opt.fuse_steps != 1 && h->best.us >= 0) {
+    // Tile and block launches: the steps in as few launches as the best plan
+    // needs, spread evenly over them.
+    int64_t launches = (n + h->best.levels - 1) / h->best.levels;
+    for (; launches > 0 && left >= 2; --launches) {
+      const int L = (int)((left + launches - 1) / launches);
+      if (L < 2) break;
+      const StepPlan& p = step_plan(h, L);
+      if (p.kind == StepKind::tile) {
+        HIP_TRY(h, launch_tile_sweep(h->opt.equilibrium, h->opt.collision, h->opt.boundary_x,
+                                     h->opt.storage, h->buf[h->cur], h->buf[1 - h->cur], h->geo,
+                                     h->coef, p.tile, L, h->stream));
+      } else if (p.kind == StepKind::block) {
+        HIP_TRY(h, launch_block_sweep(h->opt.equilibrium, h->opt.collision, h->opt.boundary_x,
+                                      h->opt.storage, h->buf[h->cur], h->buf[1 - h->cur], h->geo,
+                                      h->coef, p.block, L, h->stream));
+      } else {
+        break;
+      }
+      done(L);
+    }
   }
-  for (; left > 0; --left) {
+  while (left > 0) {
     HIP_TRY(h, launch_sweep(h->opt.equilibrium, h->opt.collision, h->opt.boundary_x,
                             h->opt.storage, h->buf[h->cur], h->buf[1 - h->cur], h->geo, h->coef,
                             h->stream));
-    h->cur = 1 - h->cur;
-    h->t += 1;
+    done(1);
   }
   if (h->opt.check_nonfinite) {
     double d[6];

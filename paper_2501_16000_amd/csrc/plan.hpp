@@ -1,0 +1,285 @@
+// plan.hpp -- which multi-step kernel advances a lattice, and with which
+// shape: the launch model of the tile sweep (tile.hip) and the block sweep
+// (block.hip), in plain host code.
+//
+// Both kernels advance a lattice L time steps per launch and recompute a halo
+// around each tile, so a longer launch spends less on launches and memory and
+// more on halos.  The choice minimises the modelled time per step; every
+// choice gives the same populations bit for bit.
+//
+// The models were fitted to 33,000 timed launches (24 lattices from 32^2 and
+// 800 x 1 to 3000^2, F64, F32S and F16S, every shape below): the chosen shape
+// ran within 5 % of the fastest one on three lattices out of four, and within
+// 26 % on the worst.  Times are microseconds.
+#pragma once
+
+#include <algorithm>
+#include <cmath>
+#include <cstdint>
+
+#include "oreg.h"
+
+namespace oreg {
+
+// Tile sweep: the lattice in tx x ty tiles of ox x oy output nodes; a tile's
+// region is rx x ry nodes (one per thread), with hx and hy halo nodes per
+// side (levels - 1, or 0 on an axis that one tile covers and that wraps).
+constexpr int kTileNodes = 1024;
+struct TileShape {
+  int tx, ty;
+  int ox, oy;
+  int rx, ry;
+  int hx, hy;
+};
+
+// Block sweep: the lattice in tx x ty tiles of ox x oy output nodes, each
+// advanced by a workgroup of `waves` wavefronts that holds 64 columns x waves
+// * rows rows in registers (halo: levels - 1 on every side).
+constexpr int kBlockWaves = 8;
+struct BlockShape {
+  int tx, ty;
+  int ox, oy;
+  int waves, rows;
+};
+
+// Rows per wavefront of the block sweep, two sizes per storage: eight rows of
+// nine populations take 250 VGPRs in F64 (two wavefronts per SIMD) and 106 -
+// 119 in F32S and F16S (four); in BF16S eight rows do not fit four wavefronts
+// per SIMD, six do.
+constexpr int block_rows_small(int) { return 4; }
+constexpr int block_rows_big(int st) { return st == LB_BF16S ? 6 : 8; }
+// Wavefronts of the block sweep that one SIMD holds (from its VGPRs).
+constexpr int block_waves_per_simd(int st, int rows) {
+  return st == LB_F64 ? (rows == 4 ? 3 : 2) : (rows == 4 ? 7 : 4);
+}
+
+enum class StepKind { sweep, tile, block };
+constexpr int kPlanLevels = 128;  // most steps of one launch
+
+struct StepPlan {
+  StepKind kind = StepKind::sweep;
+  int levels = 1;       // steps per launch
+  double us = 0;        // modelled time of the launch
+  TileShape tile{};
+  BlockShape block{};
+};
+
+namespace plan_detail {
+
+constexpr int kBytes[4] = {8, 4, 2, 2};
+
+// Tile sweep.  Launch t0 + t1, a step `lat` plus `c` for every wavefront of
+// the fullest SIMD that still has nodes to update, and 1/seg for every row
+// segment the first step loads.
+struct TileFit {
+  double t0, lat, c, t1, seg;
+};
+constexpr TileFit kTileFit[4] = {{1.64, 0.040, 0.230, 1.71, 28.1},
+                                 {3.30, 0.096, 0.175, 0.0, 41.1},
+                                 {3.28, 0.146, 0.182, 0.0, 55.4},
+                                 {3.28, 0.146, 0.190, 0.0, 55.4}};
+// Block sweep.  A step takes the longer of one wavefront's own rows (c1 each,
+// plus lat) and the row updates of the fullest SIMD (c each).
+struct BlockFit {
+  double t0, lat, c, c1, t1;
+};
+constexpr BlockFit kBlockFit[4] = {{0.95, 0.0, 0.233, 0.225, 1.84},
+                                   {3.47, 0.056, 0.185, 0.248, 0.0},
+                                   {4.18, 0.013, 0.225, 0.298, 0.0},
+                                   {4.18, 0.013, 0.235, 0.305, 0.0}};
+
+inline double tile_us(int st, const TileShape& t, int L, int cus) {
+  const TileFit& f = kTileFit[st];
+  const int nodes = t.rx * t.ry, W = (nodes + 63) / 64;
+  const int lds = L > 1 ? 16 * W * 64 * kBytes[st] : 0;
+  int fit = 28 / W;  // 70 VGPRs: seven wavefronts per SIMD
+  if (lds) fit = std::min(fit, 160 * 1024 / lds);
+  fit = std::max(1, std::min(fit, 16));
+  const int need = (t.tx * t.ty + cus - 1) / cus, conc = std::min(fit, need);
+  const int rounds = (t.tx * t.ty + cus * conc - 1) / (cus * conc);
+  double us = f.t1 + conc * W * (64.0 / t.rx + 1) / f.seg;
+  if (t.hx == 0 && t.hy == 0 && L > 1) {  // every step alike (L may be large)
+    us += L * (f.lat + f.c * ((W * conc + 3) / 4));
+  } else {
+    for (int s = 0; s < L; ++s) {
+      const int rows = t.ty > 1 ? t.ry - 2 * s : t.ry;
+      const int a = std::max(1, std::min(W, (rows * t.rx + 63) / 64));
+      us += f.lat + f.c * ((a * conc + 3) / 4);
+    }
+  }
+  return f.t0 + rounds * us;
+}
+
+inline double block_us(int st, const BlockShape& b, int L, int cus) {
+  const BlockFit& f = kBlockFit[st];
+  const int tiles = b.tx * b.ty;
+  const int fit = std::max(1, 4 * block_waves_per_simd(st, b.rows) / b.waves);
+  const int need = (tiles + cus - 1) / cus, conc = std::min(fit, need);
+  const int rounds = (tiles + cus * conc - 1) / (cus * conc);
+  double us = f.t1;
+  for (int s = 0; s < L; ++s) {
+    const int rows = b.waves * b.rows - 2 * s;
+    us += std::max(f.lat + f.c1 * std::min(b.rows, rows), 0.5 * f.lat + f.c * rows * conc / 4.0);
+  }
+  return f.t0 + rounds * us;
+}
+
+inline int div_up(int a, int b) { return (a + b - 1) / b; }
+
+// Best tile shape for exactly L steps; us < 0 if there is none.
+inline StepPlan best_tile(int st, int nx, int ny, int L, int cus) {
+  constexpr int kX[] = {0, 4, 8, 16, 24, 32, 40, 48, 56, 64, 96, 128, 192, 256};
+  constexpr int kY[] = {0, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 48, 64};
+  StepPlan best;
+  best.us = -1;
+  for (int wy : kY) {
+    if (wy >= ny) continue;
+    TileShape t;
+    t.oy = wy == 0 ? ny : div_up(ny, div_up(ny, wy));
+    t.ty = div_up(ny, t.oy);
+    t.hy = t.ty == 1 ? 0 : L - 1;
+    t.ry = t.oy + 2 * t.hy;
+    if (t.ry > kTileNodes || t.hy > ny) continue;
+    for (int wx : kX) {
+      if (wx >= nx) continue;
+      t.ox = wx == 0 ? nx : wx;
+      t.tx = div_up(nx, t.ox);
+      t.hx = t.tx == 1 ? 0 : L - 1;
+      t.rx = t.ox + 2 * t.hx;
+      if ((int64_t)t.rx * t.ry > kTileNodes || t.hx > nx) continue;
+      if ((int64_t)t.tx * t.ty > 16 * cus) continue;
+      const double us = tile_us(st, t, L, cus);
+      if (best.us < 0 || us < best.us) {
+        best.kind = StepKind::tile;
+        best.levels = L;
+        best.us = us;
+        best.tile = t;
+      }
+    }
+  }
+  return best;
+}
+
+inline BlockShape block_shape(int nx, int ny, int L, int waves, int rows) {
+  BlockShape b;
+  b.waves = waves;
+  b.rows = rows;
+  const int mx = 64 - 2 * (L - 1), my = waves * rows - 2 * (L - 1);
+  b.ox = div_up(nx, div_up(nx, mx));
+  b.tx = div_up(nx, b.ox);
+  b.oy = div_up(ny, div_up(ny, my));
+  b.ty = div_up(ny, b.oy);
+  return b;
+}
+
+// Lattices of many rounds of tiles run at the issue rate of the row updates,
+// so the halo share decides: 64 x 64 regions in F32S (54 x 54 stored at six
+// steps: 65.6 us per step on 4096^2 against 67.6 at five and 66.9 at seven).
+// The 16-bit formats carry the conversions between steps and fill from less
+// memory: four steps in 64 x 32 regions (2048^2 F16S: 17.6 us per step, best
+// of all shapes; BF16S 4096^2, 64 x 48: 69.4 against 72.9 at six steps).
+inline StepPlan block_large(int st, int nx, int ny, int L, int cus) {
+  StepPlan p;
+  p.kind = StepKind::block;
+  p.levels = L;
+  const int rows = st == LB_F16S ? block_rows_small(st) : block_rows_big(st);
+  p.block = block_shape(nx, ny, L, kBlockWaves, rows);
+  p.us = block_us(st, p.block, L, cus);
+  return p;
+}
+constexpr int block_large_levels(int st) { return st == LB_F16S || st == LB_BF16S ? 4 : 6; }
+
+inline StepPlan best_block(int st, int nx, int ny, int L, int cus) {
+  StepPlan best;
+  best.us = -1;
+  for (int rows : {block_rows_small(st), block_rows_big(st)}) {
+    for (int waves = 1; waves <= kBlockWaves; ++waves) {
+      if (64 - 2 * (L - 1) < 16 || waves * rows - 2 * (L - 1) < 4) continue;
+      const BlockShape b = block_shape(nx, ny, L, waves, rows);
+      const int fit = std::max(1, 4 * block_waves_per_simd(st, rows) / waves);
+      const int64_t tiles = (int64_t)b.tx * b.ty;
+      // More than one round only with every SIMD equally loaded.
+      if (tiles > (int64_t)cus * fit && waves % 4 != 0) continue;
+      if (tiles > (int64_t)3 * cus * fit) continue;
+      const double us = block_us(st, b, L, cus);
+      if (best.us < 0 || us < best.us) {
+        best.kind = StepKind::block;
+        best.levels = L;
+        best.us = us;
+        best.block = b;
+      }
+    }
+  }
+  return best;
+}
+
+}  // namespace plan_detail
+
+// Whether the strip pipeline (fused_impl.hpp) advances this lattice.  A strip
+// pays for its halo rows once per strip, a block once per block, so strips
+// have the smaller halo share where a lattice fills the chip with long ones;
+// below that their pipeline fill (2 K row steps per launch) and the uneven last
+// wave cost more.  Measured, us per step, block : strip, one lattice at a time
+// (and with three lattices on three streams):
+//   F64   512^2 2.84 : 3.48 (2.46 : 2.78), 600^2 4.38 : 4.21 (3.70 : 3.07);
+//   F32S  2500^2 26.7 : 27.6 (25.1 : 25.5), 3000^2 37.9 : 37.1 (34.6 : 34.1),
+//         4096^2 65.0 : 62.5 (63.8 : 58.0);
+//   F16S  2048^2 18.6 : 19.0 (17.0 : 16.6), 2500^2 25.2 : 26.0 (24.4 : 23.0),
+//         4096^2 64.9 : 61.1 (63.4 : 57.3).
+// F64 changes over early: its blocks leave two wavefronts per SIMD, which
+// cannot hide their loads.
+inline bool plan_strips(int st, int nx, int ny) {
+  const int64_t nodes = (int64_t)nx * ny;
+  const int64_t from = st == LB_F64 ? 300000 : st == LB_F32S ? 7500000 : 5000000;
+  return nodes >= from && std::min(nx, ny) > 36;
+}
+
+// Whether the block sweep runs this lattice in many rounds of workgroups.
+inline bool plan_many(int st, int nx, int ny, int cus) {
+  using namespace plan_detail;
+  const int Lb = block_large_levels(st);
+  const StepPlan p = block_large(st, nx, ny, Lb, cus);
+  const int fit = 4 * block_waves_per_simd(st, p.block.rows) / kBlockWaves;
+  return 2 * (int64_t)p.block.tx * p.block.ty > (int64_t)3 * cus * fit;
+}
+
+// The plan for one launch of exactly L steps on a lattice that plan_strips
+// leaves to the tile and block sweeps; us < 0 if neither takes L steps.
+inline StepPlan plan_levels(int st, int nx, int ny, int L, int cus) {
+  using namespace plan_detail;
+  const int64_t nodes = (int64_t)nx * ny;
+  StepPlan best;
+  best.us = -1;
+  // Tiles fill the chip with one small workgroup per CU: up to about 290^2
+  // nodes (256^2 F32S: tile 1.3, block 1.6 us per step; 362^2: 2.3 against
+  // 1.7).  On flat lattices, which leave most of a block's 64 columns or of
+  // its rows empty, at any length.
+  if (nodes <= 81920 || std::min(nx, ny) <= 36) best = best_tile(st, nx, ny, L, cus);
+  if (L <= 16 && nodes >= 4096) {
+    StepPlan b;
+    if (plan_many(st, nx, ny, cus)) {
+      b.us = -1;
+      if (L <= block_large_levels(st)) b = block_large(st, nx, ny, L, cus);
+    } else {
+      b = best_block(st, nx, ny, L, cus);
+    }
+    if (b.us >= 0 && (best.us < 0 || b.us < best.us)) best = b;
+  }
+  return best;
+}
+
+// The launch with the least modelled time per step.
+inline StepPlan plan_best(int st, int nx, int ny, int cus) {
+  StepPlan best;
+  best.us = -1;
+  const bool many = plan_many(st, nx, ny, cus);
+  for (int L : {2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 20, 24, 32, 48, kPlanLevels}) {
+    // In many rounds the number of steps is measured, not modelled.
+    if (many && std::min(nx, ny) > 36 && L != plan_detail::block_large_levels(st)) continue;
+    const StepPlan p = plan_levels(st, nx, ny, L, cus);
+    if (p.us >= 0 && (best.us < 0 || p.us * best.levels < best.us * L)) best = p;
+  }
+  return best;
+}
+
+}  // namespace oreg

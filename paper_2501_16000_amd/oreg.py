@@ -158,9 +158,9 @@ class Lattice:
     Parameters mirror ``lb_options``; string names select the enums:
     equilibrium 'guided' | 'poly2', storage 'f64' | 'f32s' | 'f16s' | 'bf16s',
     collision 'oreg' | 'bgk', boundary_x 'periodic' | 'bounceback'.
-    ``fuse_steps`` 0 lets ``step`` fuse several time steps per launch when the
-    lattice is large enough, 1 runs one sweep launch per step, 2 fuses at any
-    size (identical results in every case).
+    ``fuse_steps`` 0 lets ``step`` advance several time steps per launch (kernel
+    and step count chosen from the lattice's size and storage), 1 runs one sweep
+    launch per step, 2 is as 0 (identical results in every case).
     ``stream`` is a HIP stream handle (int, 0 = the null stream) or a
     ``torch.cuda.Stream``; None lets the lattice create its own stream.
     """

@@ -38,53 +38,17 @@ __host__ __device__ __forceinline__ R axis_w(const Coeffs<R>& k) {
   return c == 0 ? k.a0 : k.a1;
 }
 
-// rho - rho0 (rho when unshifted), j and the raw second moments
-// M_ab = sum_i c_ia c_ib f_i of one node.
-template <typename R>
-__host__ __device__ __forceinline__ void moments(const R (&f)[27], R& drho, R (&j)[3],
-                                                 R (&M)[6]) {
+// Equilibrium of one node, population by population: feq_i (full value) and
+// deq_i = feq_i - w_i rho0 (deq = feq when unshifted).  u2[a] = u_a^2.
+//
+// Guided: per-axis factors Psi(-1) = a1 + (u^2 - u)/2, Psi(0) = a0 - u^2,
+// Psi(+1) = a1 + (u^2 + u)/2, as rest value + difference d[a][c + 1].
+template <int EQ, typename R>
+struct Factors {
+  R d[3][3], F[3][3], rX[3];
+  __host__ __device__ __forceinline__ Factors(R rho, const R (&u)[3], const R (&u2)[3],
+                                              const Coeffs<R>& k) {
 #pragma clang fp contract(off)
-  R L0[9], L1[9], L2[9];  // per line l = 3 (c_z + 1) + (c_y + 1)
-#pragma unroll
-  for (int l = 0; l < 9; ++l) {
-    L2[l] = f[3 * l + 2] + f[3 * l];
-    L0[l] = L2[l] + f[3 * l + 1];
-    L1[l] = f[3 * l + 2] - f[3 * l];
-  }
-  R P0[3], Py[3], Pyy[3], Px[3], Pxy[3], Pxx[3];  // per plane p = c_z + 1
-#pragma unroll
-  for (int p = 0; p < 3; ++p) {
-    Pyy[p] = L0[3 * p + 2] + L0[3 * p];
-    P0[p] = Pyy[p] + L0[3 * p + 1];
-    Py[p] = L0[3 * p + 2] - L0[3 * p];
-    Px[p] = (L1[3 * p + 2] + L1[3 * p]) + L1[3 * p + 1];
-    Pxy[p] = L1[3 * p + 2] - L1[3 * p];
-    Pxx[p] = (L2[3 * p + 2] + L2[3 * p]) + L2[3 * p + 1];
-  }
-  const R Mzz = P0[2] + P0[0];
-  drho = Mzz + P0[1];
-  j[0] = (Px[2] + Px[0]) + Px[1];
-  j[1] = (Py[2] + Py[0]) + Py[1];
-  j[2] = P0[2] - P0[0];
-  M[0] = (Pxx[2] + Pxx[0]) + Pxx[1];  // xx
-  M[1] = (Pyy[2] + Pyy[0]) + Pyy[1];  // yy
-  M[2] = Mzz;                         // zz
-  M[3] = (Pxy[2] + Pxy[0]) + Pxy[1];  // xy
-  M[4] = Px[2] - Px[0];               // xz
-  M[5] = Py[2] - Py[0];               // yz
-}
-
-// Equilibrium: feq_i (full value) and deq_i = feq_i - w_i rho0 (deq = feq
-// when unshifted).  u2[a] = u_a^2.
-template <int EQ, bool SHIFTED, typename R>
-__host__ __device__ __forceinline__ void equilibrium(R drho, R rho, const R (&u)[3],
-                                                     const R (&u2)[3], const Coeffs<R>& k,
-                                                     R (&feq)[27], R (&deq)[27]) {
-#pragma clang fp contract(off)
-  if constexpr (EQ == LB_EQ_GUIDED) {
-    // Per-axis factors Psi(-1) = a1 + (u^2 - u)/2, Psi(0) = a0 - u^2,
-    // Psi(+1) = a1 + (u^2 + u)/2, as rest value + difference d[a][c + 1].
-    R d[3][3], F[3][3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
       const R h = R(0.5) * u2[a];
@@ -95,53 +59,213 @@ __host__ __device__ __forceinline__ void equilibrium(R drho, R rho, const R (&u)
       F[a][1] = k.a0 + d[a][1];
       F[a][2] = k.a1 + d[a][2];
     }
-    R rXY[3][3];
 #pragma unroll
-    for (int ix = 0; ix < 3; ++ix) {
-      const R rX = rho * F[0][ix];
-#pragma unroll
-      for (int iy = 0; iy < 3; ++iy) rXY[ix][iy] = rX * F[1][iy];
-    }
-    if constexpr (SHIFTED) {
-      R YZ[3][3];
-#pragma unroll
-      for (int iy = 0; iy < 3; ++iy)
-#pragma unroll
-        for (int iz = 0; iz < 3; ++iz) YZ[iy][iz] = F[1][iy] * F[2][iz];
-      unroll<0, 27>([&](auto I) {
-        constexpr int ix = cx(I.value) + 1, iy = cy(I.value) + 1, iz = cz(I.value) + 1;
-        const R ax = ix == 1 ? k.a0 : k.a1, ay = iy == 1 ? k.a0 : k.a1;
-        feq[I.value] = rXY[ix][iy] * F[2][iz];
-        const R XYZ = F[0][ix] * YZ[iy][iz];
-        const R t3 = ((k.rho0 * ax) * ay) * d[2][iz];
-        const R t2 = fmadd((k.rho0 * ax) * d[1][iy], F[2][iz], t3);
-        deq[I.value] = fmadd(drho, XYZ, fmadd(k.rho0 * d[0][ix], YZ[iy][iz], t2));
-      });
-    } else {
-      unroll<0, 27>([&](auto I) {
-        constexpr int ix = cx(I.value) + 1, iy = cy(I.value) + 1, iz = cz(I.value) + 1;
-        feq[I.value] = rXY[ix][iy] * F[2][iz];
-        deq[I.value] = feq[I.value];
-      });
-    }
-  } else {
-    // Polynomial equilibrium at theta0 = 1/3: rho W_i (1 + P_i),
-    // P_i = 3 c.u + 9/2 (c.u)^2 - 3/2 u^2.
-    const R u2h = R(1.5) * ((u2[0] + u2[1]) + u2[2]);
-    unroll<0, 27>([&](auto I) {
-      constexpr int ccx = cx(I.value), ccy = cy(I.value), ccz = cz(I.value);
-      R cu = R(0);
-      if constexpr (ccx != 0) cu = ccx > 0 ? u[0] : -u[0];
-      if constexpr (ccy != 0) cu = cu + (ccy > 0 ? u[1] : -u[1]);
-      if constexpr (ccz != 0) cu = cu + (ccz > 0 ? u[2] : -u[2]);
-      const R W = (axis_w<ccx>(k) * axis_w<ccy>(k)) * axis_w<ccz>(k);
-      const R P = fmadd(cu, fmadd(R(4.5), cu, R(3)), -u2h);
-      const R rW = rho * W;
-      feq[I.value] = fmadd(rW, P, rW);
-      if constexpr (SHIFTED) deq[I.value] = fmadd(drho, W, rW * P);
-      else deq[I.value] = feq[I.value];
-    });
+    for (int ix = 0; ix < 3; ++ix) rX[ix] = rho * F[0][ix];
   }
+  template <bool SHIFTED, int ix, int iy, int iz>
+  __host__ __device__ __forceinline__ void at(R drho, R, const Coeffs<R>& k, R& feq, R& deq) const {
+#pragma clang fp contract(off)
+    feq = (rX[ix] * F[1][iy]) * F[2][iz];
+    if constexpr (SHIFTED) {
+      const R ax = ix == 1 ? k.a0 : k.a1, ay = iy == 1 ? k.a0 : k.a1;
+      const R YZ = F[1][iy] * F[2][iz];
+      const R XYZ = F[0][ix] * YZ;
+      const R t3 = ((k.rho0 * ax) * ay) * d[2][iz];
+      const R t2 = fmadd((k.rho0 * ax) * d[1][iy], F[2][iz], t3);
+      deq = fmadd(drho, XYZ, fmadd(k.rho0 * d[0][ix], YZ, t2));
+    } else {
+      deq = feq;
+    }
+  }
+};
+
+// Polynomial equilibrium at theta0 = 1/3: rho W_i (1 + P_i),
+// P_i = 3 c.u + 9/2 (c.u)^2 - 3/2 u^2.
+template <typename R>
+struct Factors<LB_EQ_POLY2, R> {
+  R u[3], u2h;
+  __host__ __device__ __forceinline__ Factors(R, const R (&v)[3], const R (&u2)[3],
+                                              const Coeffs<R>&)
+      : u{v[0], v[1], v[2]} {
+#pragma clang fp contract(off)
+    u2h = R(1.5) * ((u2[0] + u2[1]) + u2[2]);
+  }
+  template <bool SHIFTED, int ix, int iy, int iz>
+  __host__ __device__ __forceinline__ void at(R drho, R rho, const Coeffs<R>& k, R& feq,
+                                              R& deq) const {
+#pragma clang fp contract(off)
+    constexpr int ccx = ix - 1, ccy = iy - 1, ccz = iz - 1;
+    R cu = R(0);
+    if constexpr (ccx != 0) cu = ccx > 0 ? u[0] : -u[0];
+    if constexpr (ccy != 0) cu = cu + (ccy > 0 ? u[1] : -u[1]);
+    if constexpr (ccz != 0) cu = cu + (ccz > 0 ? u[2] : -u[2]);
+    const R W = (axis_w<ccx>(k) * axis_w<ccy>(k)) * axis_w<ccz>(k);
+    const R P = fmadd(cu, fmadd(R(4.5), cu, R(3)), -u2h);
+    const R rW = rho * W;
+    feq = fmadd(rW, P, rW);
+    if constexpr (SHIFTED) deq = fmadd(drho, W, rW * P);
+    else deq = feq;
+  }
+};
+
+template <int EQ, bool SHIFTED, typename R>
+__host__ __device__ __forceinline__ void equilibrium(R drho, R rho, const R (&u)[3],
+                                                     const R (&u2)[3], const Coeffs<R>& k,
+                                                     R (&feq)[27], R (&deq)[27]) {
+  const Factors<EQ, R> fa(rho, u, u2, k);
+  unroll<0, 27>([&](auto I) {
+    constexpr int ix = cx(I.value) + 1, iy = cy(I.value) + 1, iz = cz(I.value) + 1;
+    fa.template at<SHIFTED, ix, iy, iz>(drho, rho, k, feq[I.value], deq[I.value]);
+  });
+}
+
+// What the OReg update keeps of a node's 27 populations: rho - rho0 (rho when
+// unshifted), u, and the stress terms kappa S_aa (xx, yy, zz) and 2 kappa S_ab
+// (xy, xz, yz) of the bracket of Eq. (6).  The post-collision populations are
+// a function of these ten numbers alone (emit), so a node can be stored as
+// them instead.
+constexpr int kParams = 10;
+
+// The six plane sums of the nine populations of one c_z, f[3 (c_y + 1) + (c_x +
+// 1)]: density, x and y momentum, xx, yy and xy moments.
+template <typename R>
+struct PlaneSums {
+  R P0, Px, Py, Pxx, Pyy, Pxy;
+};
+template <typename R>
+__host__ __device__ __forceinline__ PlaneSums<R> plane_sums(const R (&f)[9]) {
+#pragma clang fp contract(off)
+  R L0[3], L1[3], L2[3];  // per line c_y
+#pragma unroll
+  for (int l = 0; l < 3; ++l) {
+    L2[l] = f[3 * l + 2] + f[3 * l];
+    L0[l] = L2[l] + f[3 * l + 1];
+    L1[l] = f[3 * l + 2] - f[3 * l];
+  }
+  PlaneSums<R> s;
+  s.Pyy = L0[2] + L0[0];
+  s.P0 = s.Pyy + L0[1];
+  s.Py = L0[2] - L0[0];
+  s.Px = (L1[2] + L1[0]) + L1[1];
+  s.Pxy = L1[2] - L1[0];
+  s.Pxx = (L2[2] + L2[0]) + L2[1];
+  return s;
+}
+
+// rho - rho0 (rho when unshifted), j and the raw second moments M_ab = sum_i
+// c_ia c_ib f_i (xx, yy, zz, xy, xz, yz) from the sums of the planes c_z = -1,
+// 0, +1; `moments` does the same from all 27 populations of a node.
+template <typename R>
+__host__ __device__ __forceinline__ void combine(const PlaneSums<R>& m, const PlaneSums<R>& z,
+                                                 const PlaneSums<R>& p, R& drho, R (&j)[3],
+                                                 R (&M)[6]) {
+#pragma clang fp contract(off)
+  const R Mzz = p.P0 + m.P0;
+  drho = Mzz + z.P0;
+  j[0] = (p.Px + m.Px) + z.Px;
+  j[1] = (p.Py + m.Py) + z.Py;
+  j[2] = p.P0 - m.P0;
+  M[0] = (p.Pxx + m.Pxx) + z.Pxx;
+  M[1] = (p.Pyy + m.Pyy) + z.Pyy;
+  M[2] = Mzz;
+  M[3] = (p.Pxy + m.Pxy) + z.Pxy;
+  M[4] = p.Px - m.Px;
+  M[5] = p.Py - m.Py;
+}
+
+template <typename R>
+__host__ __device__ __forceinline__ void moments(const R (&f)[27], R& drho, R (&j)[3],
+                                                 R (&M)[6]) {
+  PlaneSums<R> s[3];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    R g[9];
+#pragma unroll
+    for (int i = 0; i < 9; ++i) g[i] = f[9 * c + i];
+    s[c] = plane_sums(g);
+  }
+  combine(s[0], s[1], s[2], drho, j, M);
+}
+
+// The ten numbers of a node from its moments (OReg, any equilibrium).
+template <bool SHIFTED, typename R>
+__host__ __device__ __forceinline__ void reduce(R drho, const R (&j)[3], const R (&M)[6],
+                                                const Coeffs<R>& k, R (&q)[kParams]) {
+#pragma clang fp contract(off)
+  const R rho = SHIFTED ? k.rho0 + drho : drho;
+  const R inv = recip(rho);
+  const R u[3] = {j[0] * inv, j[1] * inv, j[2] * inv};
+  const R u2[3] = {u[0] * u[0], u[1] * u[1], u[2] * u[2]};
+  // Trace-free part of Pi - rho u u (Pi^eq = rho theta I + rho u u).
+  const R Dxx = fmadd(-rho, u2[0], M[0]);
+  const R Dyy = fmadd(-rho, u2[1], M[1]);
+  const R Dzz = fmadd(-rho, u2[2], M[2]);
+  const R tr3 = ((Dxx + Dyy) + Dzz) * R(1.0 / 3.0);
+  const R Sxx = Dxx - tr3, Syy = Dyy - tr3, Szz = Dzz - tr3;
+  const R Sxy = fmadd(-rho, u[0] * u[1], M[3]);
+  const R Sxz = fmadd(-rho, u[0] * u[2], M[4]);
+  const R Syz = fmadd(-rho, u[1] * u[2], M[5]);
+  const R kappa = k.kappa0 * inv;
+  q[0] = drho;
+  q[1] = u[0];
+  q[2] = u[1];
+  q[3] = u[2];
+  q[4] = kappa * Sxx;
+  q[5] = kappa * Syy;
+  q[6] = kappa * Szz;
+  q[7] = kappa * (Sxy + Sxy);
+  q[8] = kappa * (Sxz + Sxz);
+  q[9] = kappa * (Syz + Syz);
+}
+
+// The post-collision populations (shifted by w_i rho0 when SHIFTED) from the
+// ten numbers, handed to put(i, f_i) nine at a time (one c_y), with an
+// ordering point (next()) before each c_y: only one c_y's factors are alive at
+// a time, where evaluating all 27 equilibria first takes 54 more registers in
+// FP64.
+template <int EQ, bool SHIFTED, typename R, class Put, class Next>
+__host__ __device__ __forceinline__ void emit_each(const R (&q)[kParams], const Coeffs<R>& k,
+                                                   Put&& put, Next&& next) {
+#pragma clang fp contract(off)
+  const R drho = q[0], rho = SHIFTED ? k.rho0 + drho : drho;
+  const R u[3] = {q[1], q[2], q[3]};
+  const R u2[3] = {u[0] * u[0], u[1] * u[1], u[2] * u[2]};
+  const R kxx = q[4], kyy = q[5], kzz = q[6], txy = q[7], txz = q[8], tyz = q[9];
+  const Factors<EQ, R> fa(rho, u, u2, k);
+  R Ax[3], Txy[3], Txz[3], Cz[3], Az[3];
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    const R Cx = R(c - 1) - u[0];
+    Ax[c] = (kxx * Cx) * Cx;
+    Txy[c] = txy * Cx;
+    Txz[c] = txz * Cx;
+    Cz[c] = R(c - 1) - u[2];
+    Az[c] = (kzz * Cz[c]) * Cz[c];
+  }
+  unroll<0, 3>([&](auto IY) {
+    constexpr int iy = IY.value;
+    next();
+    const R Cy = R(iy - 1) - u[1];
+    const R Ay = (kyy * Cy) * Cy, Tyz = tyz * Cy;
+    unroll<0, 3>([&](auto IX) {
+      constexpr int ix = IX.value;
+      const R B = fmadd(Txy[ix], Cy, Ax[ix] + Ay);
+      const R U = Txz[ix] + Tyz;
+      unroll<0, 3>([&](auto IZ) {
+        constexpr int iz = IZ.value, i = 9 * iz + 3 * iy + ix;
+        R feq, deq;
+        fa.template at<SHIFTED, ix, iy, iz>(drho, rho, k, feq, deq);
+        const R term = fmadd(U, Cz[iz], B + Az[iz]);
+        put(std::integral_constant<int, i>{}, fmadd(feq, term, deq));
+      });
+    });
+  });
+}
+
+template <int EQ, bool SHIFTED, typename R>
+__host__ __device__ __forceinline__ void emit(const R (&q)[kParams], const Coeffs<R>& k,
+                                              R (&f)[27]) {
+  emit_each<EQ, SHIFTED>(q, k, [&](auto I, R v) { f[I.value] = v; }, [] {});
 }
 
 // Collide one node in place: f holds the pre-collision populations (shifted
@@ -151,56 +275,18 @@ __host__ __device__ __forceinline__ void collide(R (&f)[27], const Coeffs<R>& k)
 #pragma clang fp contract(off)
   R drho, j[3], M[6];
   moments(f, drho, j, M);
-  const R rho = SHIFTED ? k.rho0 + drho : drho;
-  const R inv = recip(rho);
-  const R u[3] = {j[0] * inv, j[1] * inv, j[2] * inv};
-  const R u2[3] = {u[0] * u[0], u[1] * u[1], u[2] * u[2]};
-
-  R feq[27], deq[27];
-  equilibrium<EQ, SHIFTED>(drho, rho, u, u2, k, feq, deq);
-
   if constexpr (COLL == LB_COLL_BGK) {
+    const R rho = SHIFTED ? k.rho0 + drho : drho;
+    const R inv = recip(rho);
+    const R u[3] = {j[0] * inv, j[1] * inv, j[2] * inv};
+    const R u2[3] = {u[0] * u[0], u[1] * u[1], u[2] * u[2]};
+    R feq[27], deq[27];
+    equilibrium<EQ, SHIFTED>(drho, rho, u, u2, k, feq, deq);
     unroll<0, 27>([&](auto I) { f[I.value] = fmadd(k.omega, deq[I.value] - f[I.value], f[I.value]); });
   } else {
-    // Trace-free part of Pi - rho u u (Pi^eq = rho theta I + rho u u).
-    const R Dxx = fmadd(-rho, u2[0], M[0]);
-    const R Dyy = fmadd(-rho, u2[1], M[1]);
-    const R Dzz = fmadd(-rho, u2[2], M[2]);
-    const R tr3 = ((Dxx + Dyy) + Dzz) * R(1.0 / 3.0);
-    const R Sxx = Dxx - tr3, Syy = Dyy - tr3, Szz = Dzz - tr3;
-    const R Sxy = fmadd(-rho, u[0] * u[1], M[3]);
-    const R Sxz = fmadd(-rho, u[0] * u[2], M[4]);
-    const R Syz = fmadd(-rho, u[1] * u[2], M[5]);
-    const R kappa = k.kappa0 * inv;
-    const R kxx = kappa * Sxx, kyy = kappa * Syy, kzz = kappa * Szz;
-    const R txy = kappa * (Sxy + Sxy), txz = kappa * (Sxz + Sxz), tyz = kappa * (Syz + Syz);
-    R Cx[3], Cy[3], Cz[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      Cx[c] = R(c - 1) - u[0];
-      Cy[c] = R(c - 1) - u[1];
-      Cz[c] = R(c - 1) - u[2];
-    }
-    R Az[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) Az[c] = (kzz * Cz[c]) * Cz[c];
-    R B[3][3], U[3][3];
-#pragma unroll
-    for (int ix = 0; ix < 3; ++ix) {
-      const R Ax = (kxx * Cx[ix]) * Cx[ix];
-      const R Txy = txy * Cx[ix], Txz = txz * Cx[ix];
-#pragma unroll
-      for (int iy = 0; iy < 3; ++iy) {
-        const R Ay = (kyy * Cy[iy]) * Cy[iy];
-        B[ix][iy] = fmadd(Txy, Cy[iy], Ax + Ay);
-        U[ix][iy] = Txz + tyz * Cy[iy];
-      }
-    }
-    unroll<0, 27>([&](auto I) {
-      constexpr int ix = cx(I.value) + 1, iy = cy(I.value) + 1, iz = cz(I.value) + 1;
-      const R term = fmadd(U[ix][iy], Cz[iz], B[ix][iy] + Az[iz]);
-      f[I.value] = fmadd(feq[I.value], term, deq[I.value]);
-    });
+    R q[kParams];
+    reduce<SHIFTED>(drho, j, M, k, q);
+    emit<EQ, SHIFTED>(q, k, f);
   }
 }
 

@@ -12,6 +12,7 @@
 // column (x, x - 1 or x + 1 with the periodic wrap).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "kernels3.hpp"
@@ -60,8 +61,9 @@ __host__ __device__ __forceinline__ int wrap_sub(int v, int c, int n) {
 }
 
 // ---------------------------------------------------------------- sweep --
-// Wavefronts per workgroup of the sweep, per storage (measured on 256^3:
+// Most wavefronts per workgroup of the sweep, per storage (measured on 256^3:
 // 8 for F64 and 16 for F32S beat 4 by 2 %; 4 is best for the 16-bit formats).
+// Smaller boxes take four (sweep3_waves).
 template <int ST> struct Sweep3Waves { static constexpr int N = 4; };
 template <> struct Sweep3Waves<LB_F64> { static constexpr int N = 8; };
 template <> struct Sweep3Waves<LB_F32S> { static constexpr int N = 16; };
@@ -73,7 +75,7 @@ __global__ __launch_bounds__(64 * Sweep3Waves<ST>::N) void sweep3_kernel(
   using S = Storage<ST>;
   using R = typename S::R;
   using T = typename S::T;
-  const unsigned int task = blockIdx.x * Sweep3Waves<ST>::N +
+  const unsigned int task = blockIdx.x * (blockDim.x >> 6) +
                             (unsigned int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (task >= tasks) return;
   const unsigned int row = task / nseg;
@@ -135,11 +137,13 @@ __global__ __launch_bounds__(kThreads) void init3_kernel(const double* __restric
                                                          const double* __restrict__ uz,
                                                          typename Storage<ST>::T* __restrict__ dst,
                                                          Geometry3 g, Coef64 c,
-                                                         unsigned int* __restrict__ bad) {
+                                                         unsigned int* __restrict__ bad,
+                                                         unsigned int* __restrict__ fmt) {
   using S = Storage<ST>;
   using R = typename S::R;
   const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (idx >= g.cells) return;
+  if (fmt && idx == 0) *fmt = 0;  // the buffer holds populations
   double r = rho[idx];
   double u[3] = {ux[idx], uy[idx], uz[idx]};
   if (!(isfinite(r) && isfinite(u[0]) && isfinite(u[1]) && isfinite(u[2]) && r > 0.0)) {
@@ -159,11 +163,13 @@ __global__ __launch_bounds__(kThreads) void init3_kernel(const double* __restric
 template <int ST>
 __global__ __launch_bounds__(kThreads) void import3_kernel(int i, const double* __restrict__ fin,
                                                            typename Storage<ST>::T* __restrict__ dst,
-                                                           Geometry3 g, Coef64 c) {
+                                                           Geometry3 g, Coef64 c,
+                                                           unsigned int* __restrict__ fmt) {
   using S = Storage<ST>;
   using R = typename S::R;
   const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (idx >= g.cells) return;
+  if (fmt && idx == 0) *fmt = 0;  // the buffer holds populations
   const double w = S::shifted ? d3::shift64(d3::cx(i), d3::cy(i), d3::cz(i), c) : 0.0;
   dst[i * g.cells + upwind(node_of(idx, g), i, g)] = S::store((R)(fin[idx] - w));
 }
@@ -171,9 +177,12 @@ __global__ __launch_bounds__(kThreads) void import3_kernel(int i, const double* 
 template <int ST>
 __global__ __launch_bounds__(kThreads) void export3_kernel(int i,
                                                            const typename Storage<ST>::T* __restrict__ src,
+                                                           const typename Storage<ST>::T* __restrict__ alt,
+                                                           const unsigned int* __restrict__ fmt,
                                                            double* __restrict__ fout, Geometry3 g,
                                                            Coef64 c) {
   using S = Storage<ST>;
+  if (fmt && *fmt != 0) src = alt;  // see launch_expand3
   const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (idx >= g.cells) return;
   const double w = S::shifted ? d3::shift64(d3::cx(i), d3::cy(i), d3::cz(i), c) : 0.0;
@@ -235,8 +244,11 @@ __device__ __forceinline__ void block_sum(double (&v)[kSums]) {
 
 template <int ST>
 __global__ __launch_bounds__(kThreads) void diag3_kernel(const typename Storage<ST>::T* __restrict__ src,
+                                                         const typename Storage<ST>::T* __restrict__ alt,
+                                                         const unsigned int* __restrict__ fmt,
                                                          double* __restrict__ partials, Geometry3 g,
                                                          Coef64 c, double theta) {
+  if (fmt && *fmt != 0) src = alt;  // see launch_expand3
   double acc[kSums] = {0, 0, 0, 0, 0, 0, 0};
   const int64_t stride = (int64_t)gridDim.x * kThreads;
   for (int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x; idx < g.cells; idx += stride) {
@@ -284,6 +296,14 @@ unsigned int blocks_for(int64_t n) { return (unsigned int)((n + kThreads - 1) / 
 
 }  // namespace
 
+// Wavefronts per workgroup.  Boxes of less than 8 M nodes run faster with
+// four, which spread small boxes over more CUs (us per step, F64 eight / four:
+// 32^3 6.9 / 5.6, 128^3 189 / 173; F32S sixteen / four: 32^3 7.8 / 4.3, 128^3
+// 98 / 87).
+unsigned int sweep3_waves(const Geometry3& g, unsigned int most) {
+  return g.cells < (8 << 20) ? std::min(4u, most) : most;
+}
+
 // ------------------------------------------------------------ launchers --
 int64_t sweep3_tasks(const Geometry3& g) {
   return (int64_t)((g.nx + 63) / 64) * g.ny * g.nz;
@@ -295,7 +315,7 @@ hipError_t launch_sweep3(int eq, int coll, int st, const void* src, void* dst, c
   const unsigned int tasks = (unsigned int)sweep3_tasks(g);
   return with_storage(st, [&](auto ST) {
     using T = typename Storage<ST.value>::T;
-    constexpr int W = Sweep3Waves<ST.value>::N;
+    const unsigned int W = sweep3_waves(g, Sweep3Waves<ST.value>::N);
     const unsigned int nblocks = (tasks + W - 1) / W;
     return with_eq(eq, [&](auto EQ) {
       return with_coll(coll, [&](auto CO) {
@@ -309,32 +329,33 @@ hipError_t launch_sweep3(int eq, int coll, int st, const void* src, void* dst, c
 
 hipError_t launch_init3(int eq, int st, const double* rho, const double* ux, const double* uy,
                         const double* uz, void* dst, const Geometry3& g, const Coef64& c,
-                        unsigned int* bad, hipStream_t s) {
+                        unsigned int* bad, unsigned int* fmt, hipStream_t s) {
   return with_storage(st, [&](auto ST) {
     using T = typename Storage<ST.value>::T;
     return with_eq(eq, [&](auto EQ) {
       init3_kernel<EQ.value, ST.value><<<blocks_for(g.cells), kThreads, 0, s>>>(
-          rho, ux, uy, uz, static_cast<T*>(dst), g, c, bad);
+          rho, ux, uy, uz, static_cast<T*>(dst), g, c, bad, fmt);
       return hipGetLastError();
     });
   });
 }
 
 hipError_t launch_import3(int st, int i, const double* fin, void* dst, const Geometry3& g,
-                          const Coef64& c, hipStream_t s) {
+                          const Coef64& c, unsigned int* fmt, hipStream_t s) {
   return with_storage(st, [&](auto ST) {
     using T = typename Storage<ST.value>::T;
-    import3_kernel<ST.value><<<blocks_for(g.cells), kThreads, 0, s>>>(i, fin, static_cast<T*>(dst), g, c);
+    import3_kernel<ST.value><<<blocks_for(g.cells), kThreads, 0, s>>>(i, fin, static_cast<T*>(dst), g, c, fmt);
     return hipGetLastError();
   });
 }
 
-hipError_t launch_export3(int st, int i, const void* src, double* fout, const Geometry3& g,
+hipError_t launch_export3(int st, int i, const void* src, const void* alt,
+                          const unsigned int* fmt, double* fout, const Geometry3& g,
                           const Coef64& c, hipStream_t s) {
   return with_storage(st, [&](auto ST) {
     using T = typename Storage<ST.value>::T;
-    export3_kernel<ST.value><<<blocks_for(g.cells), kThreads, 0, s>>>(i, static_cast<const T*>(src),
-                                                                       fout, g, c);
+    export3_kernel<ST.value><<<blocks_for(g.cells), kThreads, 0, s>>>(
+        i, static_cast<const T*>(src), static_cast<const T*>(alt), fmt, fout, g, c);
     return hipGetLastError();
   });
 }
@@ -349,13 +370,13 @@ hipError_t launch_moments3(int st, const void* src, double* out, const Geometry3
   });
 }
 
-hipError_t launch_diagnostics3(int st, const void* src, double* partials, double* out,
-                               const Geometry3& g, const Coef64& c, double theta_energy,
+hipError_t launch_diagnostics3(int st, const void* src, const void* alt, const unsigned int* fmt,
+                               double* partials, double* out, const Geometry3& g, const Coef64& c, double theta_energy,
                                hipStream_t s) {
   return with_storage(st, [&](auto ST) {
     using T = typename Storage<ST.value>::T;
-    diag3_kernel<ST.value><<<kDiag3Blocks, kThreads, 0, s>>>(static_cast<const T*>(src), partials, g,
-                                                             c, theta_energy);
+    diag3_kernel<ST.value><<<kDiag3Blocks, kThreads, 0, s>>>(
+        static_cast<const T*>(src), static_cast<const T*>(alt), fmt, partials, g, c, theta_energy);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     diag3_final_kernel<<<1, kThreads, 0, s>>>(partials, kDiag3Blocks, out);

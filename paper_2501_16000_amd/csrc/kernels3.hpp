@@ -11,6 +11,7 @@
 #include <stdint.h>
 
 #include "d3q27.hpp"
+#include "plan3.hpp"
 
 namespace oreg {
 
@@ -30,15 +31,32 @@ int64_t sweep3_tasks(const Geometry3& g);
 hipError_t launch_sweep3(int eq, int coll, int st, const void* src, void* dst, const Geometry3& g,
                          const Coef64& c, hipStream_t s);
 
+// OReg boxes whose buffers hold populations or ten numbers per node
+// (march3.hip); *fmt says which (0: populations, 1: ten numbers).
+// One time step src -> dst (ten numbers; sets *fmt_dst).
+hipError_t launch_march3(int eq, int st, const void* src, void* dst, const unsigned int* fmt_src,
+                         unsigned int* fmt_dst, const Geometry3& g, const Coef64& c,
+                         const MarchShape& s, hipStream_t q);
+// rho, ux, uy, uz into out[4][cells].
+hipError_t launch_march3_moments(int eq, int st, const void* src, double* out,
+                                 const unsigned int* fmt, const Geometry3& g, const Coef64& c,
+                                 const MarchShape& s, hipStream_t q);
+// The populations of src into alt, if src holds ten numbers per node.
+hipError_t launch_expand3(int eq, int st, const void* src, void* alt, const unsigned int* fmt,
+                          const Geometry3& g, const Coef64& c, hipStream_t s);
+
 // g from device FP64 fields [nz][ny][nx]; invalid nodes are counted in *bad.
+// fmt (also below): the buffer's format flag, or null where a box always holds
+// populations; alt holds the expanded populations when the flag is set.
 hipError_t launch_init3(int eq, int st, const double* rho, const double* ux, const double* uy,
                         const double* uz, void* dst, const Geometry3& g, const Coef64& c,
-                        unsigned int* bad, hipStream_t s);
+                        unsigned int* bad, unsigned int* fmt, hipStream_t s);
 
 // Plane i of pre-collision FP64 populations in/out of a buffer.
 hipError_t launch_import3(int st, int i, const double* fin, void* dst, const Geometry3& g,
-                          const Coef64& c, hipStream_t s);
-hipError_t launch_export3(int st, int i, const void* src, double* fout, const Geometry3& g,
+                          const Coef64& c, unsigned int* fmt, hipStream_t s);
+hipError_t launch_export3(int st, int i, const void* src, const void* alt,
+                          const unsigned int* fmt, double* fout, const Geometry3& g,
                           const Coef64& c, hipStream_t s);
 
 // rho, ux, uy, uz into out[4][cells].
@@ -47,8 +65,8 @@ hipError_t launch_moments3(int st, const void* src, double* out, const Geometry3
 
 // The seven FP64 sums of lb3_diagnostics into out[7]; partials holds
 // kDiag3Blocks * 7 doubles.
-hipError_t launch_diagnostics3(int st, const void* src, double* partials, double* out,
-                               const Geometry3& g, const Coef64& c, double theta_energy,
+hipError_t launch_diagnostics3(int st, const void* src, const void* alt, const unsigned int* fmt,
+                               double* partials, double* out, const Geometry3& g, const Coef64& c, double theta_energy,
                                hipStream_t s);
 
 }  // namespace oreg

@@ -28,7 +28,11 @@ struct lb3_lattice {
   int64_t t = 0;
   double* tmp = nullptr;              // 4 * cells FP64 staging (lazy)
   double* aux = nullptr;              // kDiag3Blocks * 7 partials + 8 results
-  unsigned int* counter = nullptr;
+  unsigned int* counter = nullptr;    // invalid-input count, then the buffers' format flags
+  bool march = false;                 // steps store ten numbers per node (march3.hip)
+  MarchShape shape{};
+  // Format flag of buffer b (null where every buffer holds populations).
+  unsigned int* fmt(int b) const { return march ? counter + 1 + b : nullptr; }
   std::string err;
 };
 
@@ -140,6 +144,21 @@ lb_status ready(lb3_lattice* h, const void* ptr, bool need_init) {
   return LB_OK;
 }
 
+hipError_t enqueue_moments(lb3_lattice* h, double* out) {
+  if (h->march)
+    return launch_march3_moments(h->opt.equilibrium, h->opt.storage, h->buf[h->cur], out,
+                                 h->fmt(h->cur), h->geo, h->coef, h->shape, h->stream);
+  return launch_moments3(h->opt.storage, h->buf[h->cur], out, h->geo, h->coef, h->stream);
+}
+
+// The current populations into the other buffer (whose state the next step
+// overwrites anyway), if the current one holds ten numbers per node.
+hipError_t expand(lb3_lattice* h) {
+  if (!h->march) return hipSuccess;
+  return launch_expand3(h->opt.equilibrium, h->opt.storage, h->buf[h->cur], h->buf[1 - h->cur],
+                        h->fmt(h->cur), h->geo, h->coef, h->stream);
+}
+
 lb_status finish_init(lb3_lattice* h) {
   unsigned int bad = 0;
   HIP_TRY(h, hipMemcpyAsync(&bad, h->counter, sizeof bad, hipMemcpyDeviceToHost, h->stream));
@@ -220,8 +239,15 @@ lb_status lb3_create(const lb3_options* opt, lb3_lattice** out) {
   }
   e = hipMalloc((void**)&h->aux, (kDiag3Blocks * 7 + 8) * sizeof(double));
   if (e != hipSuccess) return cleanup(hip_fail(nullptr, e, "hipMalloc(aux)"));
-  e = hipMalloc((void**)&h->counter, sizeof(unsigned int));
+  e = hipMalloc((void**)&h->counter, 3 * sizeof(unsigned int));
   if (e != hipSuccess) return cleanup(hip_fail(nullptr, e, "hipMalloc(counter)"));
+  int cus = 256;
+  (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  h->march = march_worthwhile(opt->collision, opt->storage, h->geo.cells);
+  if (h->march) {
+    h->shape = march_shape(opt->storage, opt->nx, opt->ny, opt->nz, cus);
+    h->march = march_shape_ok(h->shape, opt->nx, opt->ny, opt->nz);
+  }
   *out = h;
   return LB_OK;
 }
@@ -245,7 +271,8 @@ lb_status lb3_init(lb3_lattice* h, const double* rho, const double* ux, const do
     HIP_TRY(h, hipMemcpyAsync(h->tmp + a * n, src[a], bytes, hipMemcpyHostToDevice, h->stream));
   HIP_TRY(h, hipMemsetAsync(h->counter, 0, sizeof(unsigned int), h->stream));
   HIP_TRY(h, launch_init3(h->opt.equilibrium, h->opt.storage, h->tmp, h->tmp + n, h->tmp + 2 * n,
-                          h->tmp + 3 * n, h->buf[h->cur], h->geo, h->coef, h->counter, h->stream));
+                          h->tmp + 3 * n, h->buf[h->cur], h->geo, h->coef, h->counter,
+                          h->fmt(h->cur), h->stream));
   return finish_init(h);
 }
 
@@ -257,7 +284,8 @@ lb_status lb3_init_device(lb3_lattice* h, const double* rho, const double* ux, c
   if (!ds.ok) return fail(h, LB_EDEVICE, "cannot select device %d", h->device);
   HIP_TRY(h, hipMemsetAsync(h->counter, 0, sizeof(unsigned int), h->stream));
   HIP_TRY(h, launch_init3(h->opt.equilibrium, h->opt.storage, rho, ux, uy, uz, h->buf[h->cur],
-                          h->geo, h->coef, h->counter, h->stream));
+                          h->geo, h->coef, h->counter,
+                          h->fmt(h->cur), h->stream));
   return finish_init(h);
 }
 
@@ -269,8 +297,13 @@ lb_status lb3_step(lb3_lattice* h, int64_t n) {
   DeviceScope ds(h->device);
   if (!ds.ok) return fail(h, LB_EDEVICE, "cannot select device %d", h->device);
   for (int64_t s = 0; s < n; ++s) {
-    HIP_TRY(h, launch_sweep3(h->opt.equilibrium, h->opt.collision, h->opt.storage, h->buf[h->cur],
-                             h->buf[1 - h->cur], h->geo, h->coef, h->stream));
+    if (h->march)
+      HIP_TRY(h, launch_march3(h->opt.equilibrium, h->opt.storage, h->buf[h->cur],
+                               h->buf[1 - h->cur], h->fmt(h->cur), h->fmt(1 - h->cur), h->geo,
+                               h->coef, h->shape, h->stream));
+    else
+      HIP_TRY(h, launch_sweep3(h->opt.equilibrium, h->opt.collision, h->opt.storage,
+                               h->buf[h->cur], h->buf[1 - h->cur], h->geo, h->coef, h->stream));
     h->cur = 1 - h->cur;
     h->t += 1;
   }
@@ -282,7 +315,7 @@ lb_status lb3_moments_device(lb3_lattice* h, double* out_dev) {
   if (st != LB_OK) return st;
   DeviceScope ds(h->device);
   if (!ds.ok) return fail(h, LB_EDEVICE, "cannot select device %d", h->device);
-  HIP_TRY(h, launch_moments3(h->opt.storage, h->buf[h->cur], out_dev, h->geo, h->coef, h->stream));
+  HIP_TRY(h, enqueue_moments(h, out_dev));
   return LB_OK;
 }
 
@@ -292,7 +325,7 @@ lb_status lb3_moments(lb3_lattice* h, double* out) {
   DeviceScope ds(h->device);
   if (!ds.ok) return fail(h, LB_EDEVICE, "cannot select device %d", h->device);
   if ((st = ensure_tmp(h)) != LB_OK) return st;
-  HIP_TRY(h, launch_moments3(h->opt.storage, h->buf[h->cur], h->tmp, h->geo, h->coef, h->stream));
+  HIP_TRY(h, enqueue_moments(h, h->tmp));
   HIP_TRY(h, hipMemcpyAsync(out, h->tmp, 4 * (size_t)h->geo.cells * sizeof(double),
                             hipMemcpyDeviceToHost, h->stream));
   HIP_TRY(h, hipStreamSynchronize(h->stream));
@@ -306,11 +339,13 @@ lb_status lb3_populations(lb3_lattice* h, double* out) {
   if (!ds.ok) return fail(h, LB_EDEVICE, "cannot select device %d", h->device);
   if ((st = ensure_tmp(h)) != LB_OK) return st;
   const int64_t n = h->geo.cells;
+  HIP_TRY(h, expand(h));
   for (int i = 0; i < 27; ++i) {
     // Four staging planes, used in turn, so a plane is not overwritten
     // before its copy has been issued (same stream, so ordered).
     double* stage = h->tmp + (i % 4) * n;
-    HIP_TRY(h, launch_export3(h->opt.storage, i, h->buf[h->cur], stage, h->geo, h->coef, h->stream));
+    HIP_TRY(h, launch_export3(h->opt.storage, i, h->buf[h->cur], h->buf[1 - h->cur],
+                              h->fmt(h->cur), stage, h->geo, h->coef, h->stream));
     HIP_TRY(h, hipMemcpyAsync(out + (size_t)i * n, stage, (size_t)n * sizeof(double),
                               hipMemcpyDeviceToHost, h->stream));
   }
@@ -339,7 +374,8 @@ lb_status lb3_set_populations(lb3_lattice* h, const double* in) {
     double* stage = h->tmp + (i % 4) * n;
     HIP_TRY(h, hipMemcpyAsync(stage, in + (size_t)i * n, (size_t)n * sizeof(double),
                               hipMemcpyHostToDevice, h->stream));
-    HIP_TRY(h, launch_import3(h->opt.storage, i, stage, h->buf[h->cur], h->geo, h->coef, h->stream));
+    HIP_TRY(h, launch_import3(h->opt.storage, i, stage, h->buf[h->cur], h->geo, h->coef,
+                              h->fmt(h->cur), h->stream));
   }
   HIP_TRY(h, hipStreamSynchronize(h->stream));
   h->initialized = true;
@@ -353,8 +389,10 @@ lb_status lb3_diagnostics(lb3_lattice* h, double out[7]) {
   DeviceScope ds(h->device);
   if (!ds.ok) return fail(h, LB_EDEVICE, "cannot select device %d", h->device);
   double* result = h->aux + kDiag3Blocks * 7;
-  HIP_TRY(h, launch_diagnostics3(h->opt.storage, h->buf[h->cur], h->aux, result, h->geo, h->coef,
-                                 h->coef.theta, h->stream));
+  HIP_TRY(h, expand(h));
+  HIP_TRY(h, launch_diagnostics3(h->opt.storage, h->buf[h->cur], h->buf[1 - h->cur],
+                                 h->fmt(h->cur), h->aux, result, h->geo, h->coef, h->coef.theta,
+                                 h->stream));
   HIP_TRY(h, hipMemcpyAsync(out, result, 7 * sizeof(double), hipMemcpyDeviceToHost, h->stream));
   HIP_TRY(h, hipStreamSynchronize(h->stream));
   return LB_OK;
@@ -373,7 +411,7 @@ int64_t lb3_time(const lb3_lattice* h) { return h ? h->t : -1; }
 int64_t lb3_device_bytes(const lb3_lattice* h) {
   if (!h) return 0;
   int64_t b = 2 * 27 * h->geo.cells * (int64_t)h->elem;
-  b += (kDiag3Blocks * 7 + 8) * (int64_t)sizeof(double) + (int64_t)sizeof(unsigned int);
+  b += (kDiag3Blocks * 7 + 8) * (int64_t)sizeof(double) + 3 * (int64_t)sizeof(unsigned int);
   if (h->tmp) b += 4 * h->geo.cells * (int64_t)sizeof(double);
   return b;
 }

@@ -1,5 +1,5 @@
 // Walks lattice sizes and step counts and checks that every plan of plan.hpp
-// is one that the tile and block kernels can run: the region fits the
+// and plan3.hpp is one that the kernels can run: the region fits the
 // workgroup, halos are deep enough and no deeper than the lattice, and the
 // tiles cover the lattice without an empty one.  Prints the number of plans,
 // or the first broken one.
@@ -7,6 +7,7 @@
 #include <cstdlib>
 
 #include "plan.hpp"
+#include "plan3.hpp"
 
 using namespace oreg;
 
@@ -63,6 +64,20 @@ int main() {
           if (q.us >= 0) check(st, nx, ny, q.levels, q);
         }
       }
+  const int m[] = {1, 2, 3, 7, 16, 17, 40, 64, 66, 100, 197, 198, 199, 256, 300, 512, 1000, 4096, 70000};
+  for (int st = 0; st < 2; ++st)
+    for (int nx : m)
+      for (int ny : m)
+        for (int nz : m) {
+          const long long cells = (long long)nx * ny * nz;
+          if (cells > 4000000000LL || !march_worthwhile(LB_COLL_OREG, st, cells)) continue;
+          const MarchShape s = march_shape(st, nx, ny, nz, 256);
+          if (!march_shape_ok(s, nx, ny, nz)) fail("march", st, nx, ny, nz);
+          if ((s.ntx - 1) * (long long)s.tx >= nx || (s.nty - 1) * (long long)s.ty >= ny ||
+              (s.nzc - 1) * (long long)s.zc >= nz)
+            fail("empty march tile", st, nx, ny, nz);
+          ++plans;
+        }
   std::printf("plans %lld\n", plans);
   return 0;
 }

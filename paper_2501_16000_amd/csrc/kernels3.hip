@@ -95,12 +95,18 @@ __global__ __launch_bounds__(64 * Sweep3Waves<ST>::N) void sweep3_kernel(
 #pragma unroll
     for (int a = 0; a < 3; ++a)
       rows[a][b] = ((int64_t)wrap_sub(z, b - 1, g.nz) * g.ny + wrap_sub(y, a - 1, g.ny)) * g.nx;
-  R f[27];
+  T raw[27];
   unroll<0, 27>([&](auto I) {
     constexpr int vx = d3::cx(I.value), vy = d3::cy(I.value), vz = d3::cz(I.value);
     const T* p = src + I.value * P + rows[vy + 1][vz + 1];
-    f[I.value] = S::load(p[vx == 0 ? xc : (vx > 0 ? xm : xp)]);
+    raw[I.value] = p[vx == 0 ? xc : (vx > 0 ? xm : xp)];
   });
+  // All 27 loads before the first use: without the ordering point the compiler
+  // paired every F16S load with its conversion and waited for each in turn.
+  __builtin_amdgcn_sched_barrier(0);
+  R f[27];
+#pragma unroll
+  for (int i = 0; i < 27; ++i) f[i] = S::load(raw[i]);
   const Coeffs<R> k(c);
   d3::collide<EQ, COLL, S::shifted>(f, k);
   if (active) {

@@ -16,7 +16,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "liboreg.so")
-SOURCES = ["lattice.hip", "kernels.hip", "tile.hip", "block.hip", "fused_f64.hip", "fused_f32s.hip", "fused_f16s.hip",
+SOURCES = ["lattice.hip", "kernels.hip", "tile.hip", "block.hip", "readers_f64.hip", "fused_f64.hip", "fused_f32s.hip", "fused_f16s.hip",
            "fused_bf16s.hip", "serve.hip", "lattice3.hip", "kernels3.hip", "march3.hip", "copy.hip"]
 
 ARCH = "gfx950"

@@ -289,22 +289,33 @@ __host__ __device__ __forceinline__ void equilibrium(R drho, R rho, R ux, R uy, 
   }
 }
 
-// OReg update with the guided equilibrium, written on the per-axis factors:
-// f^eq_i = (rho X) Y with X = Psi(c_ix, u_x), Y = Psi(c_iy, u_y), and
-// f^post_i = f^eq_i (1 + ax - by + tx Cy) (Eqs. 6, 7; the bracket terms are
-// defined in collide below), evaluated as
+// What the OReg update keeps of a node's nine populations: rho - rho0 (rho when
+// unshifted), u, and the bracket coefficients ks, kt of Eq. (6) (see reduce).
+// The post-collision populations are a function of these five numbers alone
+// (emit), so a node can be stored as them instead.
+constexpr int kParams = 5;
+template <typename R>
+struct Params {
+  R drho, ux, uy, ks, kt;
+};
+
+// Post-collision populations of the OReg update with the guided equilibrium,
+// written on the per-axis factors: f^eq_i = (rho X) Y with X = Psi(c_ix, u_x),
+// Y = Psi(c_iy, u_y), and f^post_i = f^eq_i (1 + ax - by + tx Cy) (Eqs. 6, 7;
+// the bracket terms are defined in collide below), evaluated as
 //   rho X (Y (1 - by) + Y ax + (Y Cy) tx)                  (unshifted), or
 //   Y (E + rho X ax - rho X by) + (rho X tx) (Y Cy) + (rho0 ax) dY
 //                                                          (shifted, with
 //   deq_i = f^eq_i - w_i rho0 folded in: see below),
 // with the per-x and per-y products formed once: three operations per
 // population.
-// d13 = f1 + f3 - f2 - f4 and d57 = f5 + f7 - f6 - f8 (second moments).
 template <bool SHIFTED, typename R>
-__host__ __device__ __forceinline__ void collide_guided_oreg(R (&f)[9], const Coeffs<R>& k, R drho,
-                                                             R rho, R inv, R jx, R ux, R uy,
-                                                             R uxx, R uyy, R d13, R d57) {
+__host__ __device__ __forceinline__ void emit_guided(const Params<R>& p, const Coeffs<R>& k,
+                                                     R (&f)[9]) {
 #pragma clang fp contract(off)
+  const R drho = p.drho, rho = SHIFTED ? k.rho0 + drho : drho;
+  const R ux = p.ux, uy = p.uy, ks = p.ks, kt = p.kt;
+  const R uxx = ux * ux, uyy = uy * uy;
   R rXm, rX0, rXp, Ym, Y0, Yp;  // rho X and Y
   // Shifted storage only: E = drho X + rho0 dX (per x) and (rho0 a) dY.
   R Exm = 0, Ex0 = 0, Exp = 0, a0dYm = 0, a0dY0 = 0, a0dYp = 0, a1dYm = 0, a1dY0 = 0, a1dYp = 0;
@@ -329,12 +340,6 @@ __host__ __device__ __forceinline__ void collide_guided_oreg(R (&f)[9], const Co
     a0dYm = k.r0a0 * dYm, a0dY0 = k.r0a0 * dY0, a0dYp = k.r0a0 * dYp;
     a1dYm = k.r0a1 * dYm, a1dY0 = k.r0a1 * dY0, a1dYp = k.r0a1 * dYp;
   }
-  // Non-equilibrium stress (2 s = Pi_xx - Pi_yy, S_xy) and the bracket of
-  // Eq. (6): kappa [..] = ks Cx^2 - ks Cy^2 + (kt Cx) Cy, C = c_i - u.
-  // (rho ux uy = jx uy.)
-  const R s2 = fmadd(-rho, uxx - uyy, d13);
-  const R sxy = fmadd(-jx, uy, d57);
-  const R ks = (k.kappa_h * inv) * s2, kt = (k.kappa_2 * inv) * sxy;
   // With C = -1 - u, -u, 1 - u:  ks C^2 = ks (1 +- 2 u) + ks u^2, ks u^2;
   // kt C = -kt - kt u, -kt u, kt - kt u;  Y C = -(Y + Y u), -Y u, Y - Y u.
   const R ax0 = ks * uxx;
@@ -426,42 +431,42 @@ __host__ __device__ __forceinline__ Moments<float> moments_delta(const float (&f
   return m;
 }
 
-// Collide one node in place.  f holds the pre-collision populations (shifted
-// by w_i rho0 when SHIFTED) and receives the post-collision ones (same
-// shift).  DELTA_U: moments by moments_delta (shifted FP32 only).
-template <int EQ, int COLL, bool SHIFTED, bool DELTA_U = false, typename R>
-__host__ __device__ __forceinline__ void collide(R (&f)[9], const Coeffs<R>& k) {
+template <bool SHIFTED, bool DELTA_U, typename R>
+__host__ __device__ __forceinline__ Moments<R> node_moments(const R (&f)[9], const Coeffs<R>& k) {
+  if constexpr (DELTA_U && SHIFTED && std::is_same<R, float>::value) return moments_delta(f, k);
+  else return moments<SHIFTED>(f, k);
+}
+
+// The five numbers of a node.  Trace-free non-equilibrium stress of Eq. (6)
+// from second moments: 2 s = (Pi_xx - Pi_yy) of f^neq, S_xx = -S_yy = s, and
+// S_xy.  Eqs. (6), (7): f^post_i = f^eq_i + kappa f^eq_i [s (Cx^2 - Cy^2) + 2
+// S_xy Cx Cy], kappa = (1 - 1/tau)/(2 rho theta^2), C = c_i - u.  With ks =
+// kappa s and kt = 2 kappa S_xy the bracket splits into per-axis factors:
+// kappa [..] = ks Cx^2 - ks Cy^2 + (kt Cx) Cy.  (kappa0/2) and (2 kappa0) are
+// exact rescalings, so ks and kt round as kappa (s2/2) and kappa (2 S_xy).
+template <int EQ, typename R>
+__host__ __device__ __forceinline__ Params<R> reduce(const Moments<R>& m, const Coeffs<R>& k) {
 #pragma clang fp contract(off)
-  Moments<R> m;
-  if constexpr (DELTA_U && SHIFTED && std::is_same<R, float>::value) m = moments_delta(f, k);
-  else m = moments<SHIFTED>(f, k);
-  const R drho = m.drho, rho = m.rho, inv = m.inv, jx = m.jx, ux = m.ux, uy = m.uy;
-  const R uxx = ux * ux, uyy = uy * uy;
+  const R uxx = m.ux * m.ux, uyy = m.uy * m.uy;
+  const R s2 = fmadd(-m.rho, uxx - uyy, m.d13);
+  // rho ux uy = jx uy in the guided form.
+  const R sxy = EQ == LB_EQ_GUIDED ? fmadd(-m.jx, m.uy, m.d57) : fmadd(-m.rho, m.ux * m.uy, m.d57);
+  return Params<R>{m.drho, m.ux, m.uy, (k.kappa_h * m.inv) * s2, (k.kappa_2 * m.inv) * sxy};
+}
 
-  if constexpr (EQ == LB_EQ_GUIDED && COLL == LB_COLL_OREG) {
-    collide_guided_oreg<SHIFTED>(f, k, drho, rho, inv, jx, ux, uy, uxx, uyy, m.d13, m.d57);
-    return;
-  }
-
-  R feq[9], deq[9];
-  equilibrium<EQ, SHIFTED>(drho, rho, ux, uy, uxx, uyy, k, feq, deq);
-
-  if constexpr (COLL == LB_COLL_BGK) {
-    // Eq. (1): f + (f^eq - f) / tau (the shift cancels in the difference).
-    unroll<0, 9>([&](auto I) { f[I.value] = fmadd(k.omega, deq[I.value] - f[I.value], f[I.value]); });
-    return;
+// The post-collision populations from the five numbers (shifted by w_i rho0
+// when SHIFTED).
+template <int EQ, bool SHIFTED, typename R>
+__host__ __device__ __forceinline__ void emit(const Params<R>& p, const Coeffs<R>& k, R (&f)[9]) {
+#pragma clang fp contract(off)
+  if constexpr (EQ == LB_EQ_GUIDED) {
+    emit_guided<SHIFTED>(p, k, f);
   } else {
-    // Trace-free non-equilibrium stress of Eq. (6) from second moments:
-    // S_xx = -S_yy = s, S_xy.
-    // 2 s = (Pi_xx - Pi_yy) of f^neq and S_xy.
-    const R s2 = fmadd(-rho, uxx - uyy, m.d13);
-    const R sxy = fmadd(-rho, ux * uy, m.d57);
-    // Eqs. (6), (7): f^post_i = f^eq_i + kappa f^eq_i [s (Cx^2 - Cy^2) + 2 S_xy Cx Cy],
-    // kappa = (1 - 1/tau)/(2 rho theta^2), C = c_i - u.  With ks = kappa s and
-    // kt = 2 kappa S_xy the bracket splits into per-axis factors:
-    // kappa [..] = ks Cx^2 - ks Cy^2 + (kt Cx) Cy.  (kappa0/2) and (2 kappa0)
-    // are exact rescalings, so ks and kt round as kappa (s2/2) and kappa (2 S_xy).
-    const R ks = (k.kappa_h * inv) * s2, kt = (k.kappa_2 * inv) * sxy;
+    const R drho = p.drho, rho = SHIFTED ? k.rho0 + drho : drho;
+    const R ux = p.ux, uy = p.uy, ks = p.ks, kt = p.kt;
+    const R uxx = ux * ux, uyy = uy * uy;
+    R feq[9], deq[9];
+    equilibrium<EQ, SHIFTED>(drho, rho, ux, uy, uxx, uyy, k, feq, deq);
     const R Cxm = R(-1) - ux, Cx0 = -ux, Cxp = R(1) - ux;
     const R Cym = R(-1) - uy, Cy0 = -uy, Cyp = R(1) - uy;
     const R axm = (ks * Cxm) * Cxm, ax0 = ks * uxx, axp = (ks * Cxp) * Cxp;
@@ -473,6 +478,23 @@ __host__ __device__ __forceinline__ void collide(R (&f)[9], const Coeffs<R>& k) 
                            pick<cx>(axm, ax0, axp) - pick<cy>(bym, by0, byp));
       f[I.value] = fmadd(feq[I.value], term, deq[I.value]);
     });
+  }
+}
+
+// Collide one node in place.  f holds the pre-collision populations (shifted
+// by w_i rho0 when SHIFTED) and receives the post-collision ones (same
+// shift).  DELTA_U: moments by moments_delta (shifted FP32 only).
+template <int EQ, int COLL, bool SHIFTED, bool DELTA_U = false, typename R>
+__host__ __device__ __forceinline__ void collide(R (&f)[9], const Coeffs<R>& k) {
+#pragma clang fp contract(off)
+  const Moments<R> m = node_moments<SHIFTED, DELTA_U>(f, k);
+  if constexpr (COLL == LB_COLL_OREG) {
+    emit<EQ, SHIFTED>(reduce<EQ>(m, k), k, f);
+  } else {
+    R feq[9], deq[9];
+    equilibrium<EQ, SHIFTED>(m.drho, m.rho, m.ux, m.uy, m.ux * m.ux, m.uy * m.uy, k, feq, deq);
+    // Eq. (1): f + (f^eq - f) / tau (the shift cancels in the difference).
+    unroll<0, 9>([&](auto I) { f[I.value] = fmadd(k.omega, deq[I.value] - f[I.value], f[I.value]); });
   }
 }
 

@@ -72,15 +72,14 @@ __device__ __forceinline__ int xcd_block() {
   return xcd * per + (xcd < extra ? xcd : extra) + b / 8;
 }
 
-// Fused launches per storage.  K: steps per launch.  FP64: seven.  Its
-// launch time is set by the memory traffic of the strip pipeline (a
-// streaming-only copy of the kernel, with the collision removed, ran within
-// 2 % of it at K = 6, and launches of 2 to 6 steps all took 0.57-0.61 ms on
-// 4096^2), so a further level is nearly free: 4096^2 ran at 169 (K = 6), 178
-// (K = 7) and 179 (K = 8) GLUPS, and K = 7 wastes fewer halo columns and
-// splits short step counts better.  The FP32 formats are bound by their
-// collisions at K = 6 (0.44 ms per launch against 0.30 ms for two steps in
-// F32S) and keep six.
+// Fused launches per storage.  K: steps per launch.  FP64: seven.  Stored as
+// five numbers per node, 4096^2 launches of 1 .. 7 steps take 317, 334, 323,
+// 331, 401, 476 and 559 us: up to four steps the strips' memory traffic sets
+// the time, beyond that each step adds the 80 us of its collisions, so five to
+// seven steps cost the same per step (80 us; stored as populations, seven steps
+// took 655 us) and seven needs the fewest launches where these count (1024^2).
+// The FP32 formats are bound by their collisions at K = 6 (0.44 ms per launch
+// against 0.30 ms for two steps in F32S) and keep six.
 // NW: wavefronts per strip.  F32S shares one
 // 256-column strip per workgroup (measured 9 % faster than a strip per
 // wavefront: 12 % fewer instructions per node update against six workgroup
@@ -98,13 +97,22 @@ constexpr bool short_fused(int coll, int bc) {
   return coll == LB_COLL_OREG && bc == LB_BC_PERIODIC;
 }
 
+// Whether strip launches store the five numbers of a node instead of its nine
+// populations (fused_strip): periodic OReg in FP64, whose strips are bound by
+// their memory traffic.  F32S strips are bound by VALU issue, and the 16-bit
+// formats' nine populations (18 bytes) are smaller than five FP32 numbers.
+constexpr bool stores_numbers(int coll, int bc, int st) {
+  return short_fused(coll, bc) && st == LB_F64;
+}
+
 }  // namespace detail
 
 // The fused sweeps of one storage format (fused_*.hip, one translation unit
 // per format so that they compile in parallel).
 template <int ST>
 hipError_t fused_launch_st(int eq, int coll, int bc, const void* src, void* dst, const Geometry& g,
-                           const Coef64& c, int rows, int levels, hipStream_t s);
+                           const Coef64& c, int rows, int levels, const unsigned int* fmt_src,
+                           unsigned int* fmt_dst, hipStream_t s);
 template <int ST>
 hipError_t fused_occupancy_st(int levels, int* blocks);
 template <int ST>

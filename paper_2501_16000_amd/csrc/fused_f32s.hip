@@ -5,7 +5,8 @@
 namespace oreg {
 
 template hipError_t fused_launch_st<LB_F32S>(int, int, int, const void*, void*, const Geometry&,
-                                           const Coef64&, int, int, hipStream_t);
+                                           const Coef64&, int, int, const unsigned int*,
+                                           unsigned int*, hipStream_t);
 template hipError_t fused_occupancy_st<LB_F32S>(int, int*);
 template hipError_t batched_fused_launch_st<LB_F32S>(int, const LatticeDesc*, const int*, int64_t,
                                                    int64_t, hipStream_t);

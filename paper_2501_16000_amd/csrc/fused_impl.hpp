@@ -6,6 +6,7 @@
 #pragma once
 
 #include "dispatch.hpp"
+#include "lanes.hpp"
 
 namespace oreg {
 namespace {
@@ -28,28 +29,6 @@ using namespace detail;
 // per trip) has no branches apart from the store predicate.  H is a runtime
 // multiple of 3 chosen per lattice (fused_rows).
 
-
-// lane l <- lane l - 1 (wave_shr:1) and lane l <- lane l + 1 (wave_shl:1).
-// Lanes without a source are outside the valid region of the next level: in
-// FP32 they read zero (bound_ctrl), which lets the compiler fold the shift
-// into the arithmetic instruction that consumes it; in FP64 (two 32-bit
-// moves, no folding) they keep their own value.
-__device__ __forceinline__ float from_left(float v) {
-  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x138, 0xF, 0xF, true));
-}
-__device__ __forceinline__ float from_right(float v) {
-  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x130, 0xF, 0xF, true));
-}
-__device__ __forceinline__ double from_left(double v) {
-  const int lo = __double2loint(v), hi = __double2hiint(v);
-  return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, 0x138, 0xF, 0xF, false),
-                          __builtin_amdgcn_update_dpp(lo, lo, 0x138, 0xF, 0xF, false));
-}
-__device__ __forceinline__ double from_right(double v) {
-  const int lo = __double2loint(v), hi = __double2hiint(v);
-  return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, 0x130, 0xF, 0xF, false),
-                          __builtin_amdgcn_update_dpp(lo, lo, 0x130, 0xF, 0xF, false));
-}
 
 // The same shifts, with lane 0 (from_left_or) or lane 63 (from_right_or)
 // taking `e` instead: the value of the column beyond the wavefront's edge,
@@ -150,12 +129,26 @@ constexpr int64_t kBufferFormBytes = 0x7fffffff;
 // (SHARE): the four wavefronts of a workgroup sweep one 256-column strip
 // together and hand each other the populations that cross their edges
 // through LDS, so only the workgroup's outer edges carry a halo.
-template <int K, int KS, int EQ, int COLL, int BC, int ST, bool SHARE = false, bool BUF = false>
+//
+// IN, OUT: what a buffer holds.  kPops: the nine populations.  kNums: the five
+// numbers of the OReg update (d2q9.hpp: Params), which the last level stores
+// instead of the populations it would form from them, and from which the next
+// launch forms them when a row arrives: the same arithmetic, one launch later,
+// with 40 instead of 72 bytes per node read and written in FP64.  OUT = kVisit:
+// nothing is stored; the last level hands the populations pulled to each of
+// its rows to visit(N, y) instead.
+enum { kPops = 0, kNums = 1, kVisit = 2 };
+struct NoVisit {
+  template <typename R>
+  __device__ void operator()(const R (&)[9], int) const {}
+};
+template <int K, int KS, int EQ, int COLL, int BC, int ST, bool SHARE = false, bool BUF = false,
+          int IN = kPops, int OUT = kPops, class Visit = NoVisit>
 __device__ __forceinline__ void fused_strip(const typename Storage<ST>::T* __restrict__ src,
                                             typename Storage<ST>::T* __restrict__ dst, int nx,
                                             int ny, int64_t P, int X0, int Y0, int H,
                                             const Coeffs<typename Storage<ST>::R>& k, int lane,
-                                            int wv = 0) {
+                                            int wv = 0, Visit&& visit = Visit{}) {
   using S = Storage<ST>;
   using R = typename S::R;
   using Tt = typename S::T;
@@ -221,9 +214,14 @@ __device__ __forceinline__ void fused_strip(const typename Storage<ST>::T* __res
   const PlaneIO<Tt, BUF> io(src, dst, P, nx);
   int row = (Y0 - K) % ny;
   if (row < 0) row += ny;
-  Tt nb[3][9];  // level-0 rows: row j is loaded into nb[j % 3] one row ahead
+  static_assert((IN == kPops && OUT != kNums) || (COLL == LB_COLL_OREG && BC == LB_BC_PERIODIC &&
+                                                  std::is_same<Tt, R>::value),
+                "five numbers: periodic OReg, stored in the collision's type");
+  constexpr int NI = IN == kNums ? kParams : 9;
+  constexpr int NO = OUT == kNums ? kParams : OUT == kVisit ? 1 : 9;
+  Tt nb[3][NI];  // level-0 rows: row j is loaded into nb[j % 3] one row ahead
 #pragma unroll
-  for (int i = 0; i < 9; ++i) nb[0][i] = io.load(i, row, col);
+  for (int i = 0; i < NI; ++i) nb[0][i] = io.load(i, row, col);
   // Output row y is stored one step after it is computed, before that step's
   // prefetch: the wait for the prefetched row then covers only stores issued
   // a whole step earlier, never the ones just issued.  Plain stores, not
@@ -233,11 +231,11 @@ __device__ __forceinline__ void fused_strip(const typename Storage<ST>::T* __res
   // 4 % (F16S) and 2 % (BF16S) slower and the served FP64 stream 7 % slower
   // (F32S unchanged).  The single-step sweep keeps nontemporal stores (3-6 %
   // faster there).
-  Tt pend[9];
+  Tt pend[NO];
   auto store_row = [&](int y) {
-    if (store_lane && y >= Y0 && y < ny) {
+    if (OUT != kVisit && store_lane && y >= Y0 && y < ny) {
 #pragma unroll
-      for (int i = 0; i < 9; ++i) io.store(i, y, col, pend[i]);
+      for (int i = 0; i < NO; ++i) io.store(i, y, col, pend[i]);
     }
   };
 
@@ -251,11 +249,17 @@ __device__ __forceinline__ void fused_strip(const typename Storage<ST>::T* __res
     constexpr int qb = (q + 2) % 3;           // slot of row j - 1
     constexpr int NP = decltype(NPROD)::value;
     R C[9];
-#pragma unroll
-    for (int i = 0; i < 9; ++i) C[i] = S::load(nb[q][i]);
     // Keep the first use of the row that arrives here at this step: without
     // the ordering point the compiler hoists it into the previous step, right
     // behind the load, and the wavefront waits for memory.
+    if constexpr (IN == kNums) {
+      Params<R> p{nb[q][0], nb[q][1], nb[q][2], nb[q][3], nb[q][4]};
+      __asm__ volatile("" : "+v"(p.drho), "+v"(p.ux), "+v"(p.uy), "+v"(p.ks), "+v"(p.kt));
+      emit<EQ, S::shifted>(p, k, C);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 9; ++i) C[i] = S::load(nb[q][i]);
+    }
     __asm__ volatile("" : "+v"(C[0]), "+v"(C[1]), "+v"(C[2]), "+v"(C[3]), "+v"(C[4]), "+v"(C[5]),
                      "+v"(C[6]), "+v"(C[7]), "+v"(C[8]));
     if constexpr (NP == K) store_row(Y0 + j - 1 - 2 * K);  // the previous step's output row
@@ -265,7 +269,7 @@ __device__ __forceinline__ void fused_strip(const typename Storage<ST>::T* __res
     // leaves nothing of the old buffer alive.
     if (j + 1 < J) row = wrap_inc(row, ny);
 #pragma unroll
-    for (int i = 0; i < 9; ++i) nb[qa][i] = io.load(i, row, col);
+    for (int i = 0; i < NI; ++i) nb[qa][i] = io.load(i, row, col);
 #pragma unroll
     for (int lv = 0; lv < K; ++lv) {
       // Slot q held row j - 3 of the level, which is no longer read.  With
@@ -299,6 +303,19 @@ __device__ __forceinline__ void fused_strip(const typename Storage<ST>::T* __res
         N[7] = from_right(C[7]);
         N[8] = from_left(C[8]);
       }
+      if constexpr (OUT == kNums) {
+        if (lv + 1 == K) {
+          const Params<R> p = reduce<EQ>(node_moments<S::shifted, S::delta_u>(N, k), k);
+          pend[0] = p.drho, pend[1] = p.ux, pend[2] = p.uy, pend[3] = p.ks, pend[4] = p.kt;
+          break;
+        }
+      } else if constexpr (OUT == kVisit) {
+        if (lv + 1 == K) {
+          const int y = Y0 + j - 2 * K;
+          if (store_lane && y >= Y0 && y < ny) visit(N, y);
+          break;
+        }
+      }
       if (wall) {
         R r[9];
         unroll<0, 9>([&](auto I) { r[I.value] = N[opp_of(I.value)]; });
@@ -307,6 +324,7 @@ __device__ __forceinline__ void fused_strip(const typename Storage<ST>::T* __res
         collide<EQ, COLL, S::shifted, S::delta_u>(N, k);
       }
       if (lv + 1 == K) {
+        if constexpr (OUT == kPops)
 #pragma unroll
         for (int i = 0; i < 9; ++i) pend[i] = S::store(N[i]);  // output row Y0 + j - 2K
       } else {
@@ -337,10 +355,13 @@ __device__ __forceinline__ void fused_strip(const typename Storage<ST>::T* __res
   store_row(Y0 + J - 1 - 2 * K);
 }
 
-template <int K, int EQ, int COLL, int BC, int ST, bool BUF = false>
+// fmt_src, fmt_dst: the format flags of the two buffers (0: populations, 1: five
+// numbers) of lattices that store five numbers after a launch, else null.
+template <int K, int EQ, int COLL, int BC, int ST, bool BUF = false, bool NUMS = false>
 __global__ __launch_bounds__(256) void fused_sweep_kernel(
     const typename Storage<ST>::T* __restrict__ src, typename Storage<ST>::T* __restrict__ dst,
-    Geometry g, Coef64 c, int strips, int items, int H) {
+    Geometry g, Coef64 c, int strips, int items, int H, const unsigned int* __restrict__ fmt_src,
+    unsigned int* __restrict__ fmt_dst) {
   constexpr int NW = FusedLevels<ST>::NW;
   constexpr int W = 64 * NW - 2 * K;
   // Neighbouring strips share their halo columns, which then come from the
@@ -359,8 +380,19 @@ __global__ __launch_bounds__(256) void fused_sweep_kernel(
     const int wave = xcd_block() * 4 + wv;
     if (wave >= items) return;  // whole wavefronts leave together
     const int strip = wave % strips, seg = wave / strips;
-    fused_strip<K, K, EQ, COLL, BC, ST, false, BUF>(src, dst, g.nx, g.ny, g.plane, strip * W,
-                                                    seg * H, H, k, lane);
+    if constexpr (NUMS) {
+      if (wave == 0 && lane == 0) *fmt_dst = 1;
+      // Uniform over the launch: the pipeline of the buffer's format.
+      if (*fmt_src != 0)
+        fused_strip<K, K, EQ, COLL, BC, ST, false, BUF, kNums, kNums>(
+            src, dst, g.nx, g.ny, g.plane, strip * W, seg * H, H, k, lane);
+      else
+        fused_strip<K, K, EQ, COLL, BC, ST, false, BUF, kPops, kNums>(
+            src, dst, g.nx, g.ny, g.plane, strip * W, seg * H, H, k, lane);
+    } else {
+      fused_strip<K, K, EQ, COLL, BC, ST, false, BUF>(src, dst, g.nx, g.ny, g.plane, strip * W,
+                                                      seg * H, H, k, lane);
+    }
   }
 }
 
@@ -405,17 +437,18 @@ __global__ __launch_bounds__(256) void batched_fused_kernel(const LatticeDesc* _
 
 template <int ST>
 hipError_t fused_launch_st(int eq, int coll, int bc, const void* src, void* dst, const Geometry& g,
-                           const Coef64& c, int rows, int levels, hipStream_t s) {
+                           const Coef64& c, int rows, int levels, const unsigned int* fmt_src,
+                           unsigned int* fmt_dst, hipStream_t s) {
   using T = typename Storage<ST>::T;
   constexpr int K = FusedLevels<ST>::K;
   constexpr int NW = FusedLevels<ST>::NW;
   return with_eq(eq, [&](auto EQ) {
     return with_coll(coll, [&](auto CO) {
       return with_bc(bc, [&](auto BC) -> hipError_t {
-        // The buffer form of the plane access (PlaneIO) for the guided
-        // periodic OReg sweep, the configuration of the benchmark, when the
-        // population buffer is below 2 GiB.
-        constexpr bool buf_config = EQ.value == LB_EQ_GUIDED && short_fused(CO.value, BC.value);
+        // The buffer form of the plane access (PlaneIO) for the periodic OReg
+        // sweeps, when the population buffer is below 2 GiB.
+        constexpr bool buf_config = short_fused(CO.value, BC.value);
+        constexpr bool nums = stores_numbers(CO.value, BC.value, ST);
         const bool buf = buf_config && 9 * g.plane * (int64_t)sizeof(T) <= kBufferFormBytes;
         auto go = [&](auto L) -> hipError_t {
           constexpr int W = 64 * NW - 2 * L.value;
@@ -425,20 +458,22 @@ hipError_t fused_launch_st(int eq, int coll, int bc, const void* src, void* dst,
           const unsigned int nblocks = (unsigned int)((items + 4 / NW - 1) / (4 / NW));
           if constexpr (buf_config) {
             if (buf) {
-              fused_sweep_kernel<L.value, EQ.value, CO.value, BC.value, ST, true>
+              fused_sweep_kernel<L.value, EQ.value, CO.value, BC.value, ST, true, nums>
                   <<<nblocks, 256, 0, s>>>(static_cast<const T*>(src), static_cast<T*>(dst), g, c,
-                                           strips, items, rows);
+                                           strips, items, rows, fmt_src, fmt_dst);
               return hipGetLastError();
             }
           }
-          fused_sweep_kernel<L.value, EQ.value, CO.value, BC.value, ST><<<nblocks, 256, 0, s>>>(
-              static_cast<const T*>(src), static_cast<T*>(dst), g, c, strips, items, rows);
+          fused_sweep_kernel<L.value, EQ.value, CO.value, BC.value, ST, false, nums>
+              <<<nblocks, 256, 0, s>>>(static_cast<const T*>(src), static_cast<T*>(dst), g, c,
+                                       strips, items, rows, fmt_src, fmt_dst);
           return hipGetLastError();
         };
+        if (nums && (!fmt_src || !fmt_dst)) return hipErrorInvalidValue;
         if (levels == K) return go(IC<K>{});
         hipError_t e = hipErrorInvalidValue;
         if constexpr (short_fused(CO.value, BC.value)) {
-          unroll<2, K>([&](auto L) {
+          unroll<nums ? 1 : 2, K>([&](auto L) {
             if (levels == L.value) e = go(L);
           });
         }
@@ -450,15 +485,16 @@ hipError_t fused_launch_st(int eq, int coll, int bc, const void* src, void* dst,
 
 template <int ST>
 hipError_t fused_occupancy_st(int levels, int* blocks) {
+  constexpr bool nums = stores_numbers(LB_COLL_OREG, LB_BC_PERIODIC, ST);
   auto occ = [&](auto L) {
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(
         blocks,
-        reinterpret_cast<const void*>(
-            &fused_sweep_kernel<L.value, LB_EQ_GUIDED, LB_COLL_OREG, LB_BC_PERIODIC, ST>),
+        reinterpret_cast<const void*>(&fused_sweep_kernel<L.value, LB_EQ_GUIDED, LB_COLL_OREG,
+                                                          LB_BC_PERIODIC, ST, false, nums>),
         256, 0);
   };
   hipError_t e = hipErrorInvalidValue;
-  unroll<2, FusedLevels<ST>::K + 1>([&](auto L) {
+  unroll<nums ? 1 : 2, FusedLevels<ST>::K + 1>([&](auto L) {
     if (levels == L.value) e = occ(L);
   });
   return e;

@@ -7,6 +7,7 @@
 // 2 * 9 * sizeof(storage) bytes per node and is bound by HBM bandwidth.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "dispatch.hpp"
@@ -157,11 +158,13 @@ __global__ __launch_bounds__(kThreads) void init_kernel(const double* __restrict
                                                         const double* __restrict__ uy,
                                                         typename Storage<ST>::T* __restrict__ dst,
                                                         Geometry g, Coef64 c,
-                                                        unsigned int* __restrict__ bad) {
+                                                        unsigned int* __restrict__ bad,
+                                                        unsigned int* __restrict__ fmt) {
   using S = Storage<ST>;
   using R = typename S::R;
   const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (idx >= g.plane) return;
+  if (fmt && idx == 0) *fmt = 0;  // the buffer holds populations
   const int y = (int)(idx / g.nx);
   const int x = (int)(idx - (int64_t)y * g.nx);
   double r = rho[idx], vx = ux[idx], vy = uy[idx];
@@ -185,11 +188,13 @@ __global__ __launch_bounds__(kThreads) void init_kernel(const double* __restrict
 template <int ST>
 __global__ __launch_bounds__(kThreads) void import_kernel(int i, const double* __restrict__ fin,
                                                           typename Storage<ST>::T* __restrict__ dst,
-                                                          Geometry g, Coef64 c) {
+                                                          Geometry g, Coef64 c,
+                                                          unsigned int* __restrict__ fmt) {
   using S = Storage<ST>;
   using R = typename S::R;
   const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (idx >= g.plane) return;
+  if (fmt && idx == 0) *fmt = 0;  // the buffer holds populations
   const int y = (int)(idx / g.nx);
   const int x = (int)(idx - (int64_t)y * g.nx);
   const int cx = cx_of(i), cy = cy_of(i);
@@ -198,11 +203,37 @@ __global__ __launch_bounds__(kThreads) void import_kernel(int i, const double* _
   dst[i * g.plane + (int64_t)yd * g.nx + xd] = S::store((R)(fin[idx] - w));
 }
 
-template <int ST>
+// The readers below take a lattice's equilibrium (NEQ) where its buffers may
+// hold the five numbers of a node (d2q9.hpp: Params) instead of populations,
+// as the format flag *fmt says; kPopsOnly otherwise (fmt unused).
+constexpr int kPopsOnly = -1;
+template <int NEQ>
+__device__ __forceinline__ bool holds_numbers(const unsigned int* __restrict__ fmt) {
+  if constexpr (NEQ == kPopsOnly) return false;
+  else return *fmt != 0;
+}
+
+// Population I that node (xs, ys) sends out, from its five numbers: emit with
+// the eight others dropped by the compiler.
+template <int NEQ, int ST, int I>
+__device__ __forceinline__ typename Storage<ST>::T emitted(const typename Storage<ST>::T* __restrict__ src,
+                                                           const Geometry& g, int xs, int ys,
+                                                           const Coeffs<typename Storage<ST>::R>& k) {
+  using S = Storage<ST>;
+  const typename S::T* const q = src + (int64_t)ys * g.nx + xs;
+  typename S::R f[9];
+  emit<NEQ, S::shifted>(Params<typename S::R>{q[0], q[g.plane], q[2 * g.plane], q[3 * g.plane],
+                                              q[4 * g.plane]},
+                        k, f);
+  return S::store(f[I]);
+}
+
+template <int ST, int NEQ>
 __global__ __launch_bounds__(kThreads) void export_kernel(int i,
                                                           const typename Storage<ST>::T* __restrict__ src,
                                                           double* __restrict__ fout, Geometry g,
-                                                          Coef64 c) {
+                                                          Coef64 c,
+                                                          const unsigned int* __restrict__ fmt) {
   using S = Storage<ST>;
   const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (idx >= g.plane) return;
@@ -211,16 +242,37 @@ __global__ __launch_bounds__(kThreads) void export_kernel(int i,
   const int cx = cx_of(i), cy = cy_of(i);
   const double w = S::shifted ? shift64(cx, cy, c) : 0.0;
   const int xs = wrap_sub(x, cx, g.nx), ys = wrap_sub(y, cy, g.ny);
+  if constexpr (NEQ != kPopsOnly) {
+    if (holds_numbers<NEQ>(fmt)) {
+      const Coeffs<typename S::R> k(c);
+      unroll<0, 9>([&](auto I) {
+        if (i == I.value) fout[idx] = (double)S::load(emitted<NEQ, ST, I.value>(src, g, xs, ys, k)) + w;
+      });
+      return;
+    }
+  }
   fout[idx] = (double)S::load(src[i * g.plane + (int64_t)ys * g.nx + xs]) + w;
 }
 
 // Pre-collision populations of node (x, y) in FP64, still shifted by w_i rho0.
-template <int ST>
+template <int ST, int NEQ>
 __device__ __forceinline__ void gather64(const typename Storage<ST>::T* __restrict__ src,
-                                         const Geometry& g, int x, int y, double (&d)[9]) {
+                                         const Geometry& g, int x, int y, const Coef64& c,
+                                         bool numbers, double (&d)[9]) {
   using S = Storage<ST>;
   const int xm = wrap_dec(x, g.nx), xp = wrap_inc(x, g.nx);
   const int ym = wrap_dec(y, g.ny), yp = wrap_inc(y, g.ny);
+  if constexpr (NEQ != kPopsOnly) {
+    if (numbers) {
+      const Coeffs<typename S::R> k(c);
+      unroll<0, 9>([&](auto I) {
+        constexpr int cx = cx_of(I.value), cy = cy_of(I.value);
+        d[I.value] = (double)S::load(emitted<NEQ, ST, I.value>(
+            src, g, cx == 0 ? x : (cx > 0 ? xm : xp), cy == 0 ? y : (cy > 0 ? ym : yp), k));
+      });
+      return;
+    }
+  }
   const int64_t P = g.plane;
   const int64_t r0 = (int64_t)y * g.nx, rm = (int64_t)ym * g.nx, rp = (int64_t)yp * g.nx;
   d[0] = (double)S::load(src[0 * P + r0 + x]);
@@ -251,7 +303,7 @@ __global__ __launch_bounds__(kThreads) void moments_kernel(const typename Storag
   const int y = (int)(idx / g.nx);
   const int x = (int)(idx - (int64_t)y * g.nx);
   double d[9], drho, jx, jy;
-  gather64<ST>(src, g, x, y, d);
+  gather64<ST, kPopsOnly>(src, g, x, y, c, false, d);
   moments64(d, drho, jx, jy);
   const double rho = c.rho0 + drho;
   out[idx] = rho;
@@ -297,7 +349,7 @@ __global__ __launch_bounds__(kThreads) void diag_kernel(const typename Storage<S
     const int y = (int)(idx / g.nx);
     const int x = (int)(idx - (int64_t)y * g.nx);
     double d[9], drho, jx, jy;
-    gather64<ST>(src, g, x, y, d);
+    gather64<ST, kPopsOnly>(src, g, x, y, c, false, d);
     bool finite = true;
 #pragma unroll
     for (int i = 0; i < 9; ++i) finite = finite && isfinite(d[i]);
@@ -335,20 +387,37 @@ __global__ __launch_bounds__(kThreads) void diag_final_kernel(const double* __re
   }
 }
 
-template <int ST>
+// Density summed over the rows of one chunk (grid.y), per column; the chunks
+// are added in order by profile_final_kernel.  One chunk of all rows leaves a
+// thread with ny dependent row reads and the chip with nx / 256 workgroups
+// (4096^2 F64: 4.4 ms).
+template <int ST, int NEQ>
 __global__ __launch_bounds__(kThreads) void profile_kernel(const typename Storage<ST>::T* __restrict__ src,
-                                                           double* __restrict__ out, Geometry g,
-                                                           Coef64 c) {
+                                                           double* __restrict__ partials, Geometry g,
+                                                           Coef64 c, int rows,
+                                                           const unsigned int* __restrict__ fmt) {
   const int x = blockIdx.x * kThreads + threadIdx.x;
   if (x >= g.nx) return;
+  const bool numbers = holds_numbers<NEQ>(fmt);
+  const int y0 = blockIdx.y * rows, y1 = min(y0 + rows, g.ny);
   double sum = 0.0;
-  for (int y = 0; y < g.ny; ++y) {
+  for (int y = y0; y < y1; ++y) {
     double d[9], drho, jx, jy;
-    gather64<ST>(src, g, x, y, d);
+    gather64<ST, NEQ>(src, g, x, y, c, numbers, d);
     moments64(d, drho, jx, jy);
     sum += c.rho0 + drho;
   }
-  out[x] = sum / g.ny;
+  partials[(int64_t)blockIdx.y * g.nx + x] = sum;
+}
+
+__global__ __launch_bounds__(kThreads) void profile_final_kernel(const double* __restrict__ partials,
+                                                                 double* __restrict__ out, int nx,
+                                                                 int ny, int chunks) {
+  const int x = blockIdx.x * kThreads + threadIdx.x;
+  if (x >= nx) return;
+  double sum = 0.0;
+  for (int i = 0; i < chunks; ++i) sum += partials[(int64_t)i * nx + x];
+  out[x] = sum / ny;
 }
 
 // ------------------------------------------------------ batched sweep --
@@ -413,19 +482,24 @@ int fused_levels(int st) {
   }
 }
 
+bool fused_numbers(int coll, int bc, int st) { return stores_numbers(coll, bc, st); }
+
 bool fused_levels_available(int coll, int bc, int st, int levels) {
   const int K = fused_levels(st);
+  if (levels == 1) return stores_numbers(coll, bc, st);
   if (K < 2 || levels < 2 || levels > K) return false;
   return levels == K || short_fused(coll, bc);
 }
 
 hipError_t launch_fused_sweep(int eq, int coll, int bc, int st, const void* src, void* dst,
                               const Geometry& g, const Coef64& c, int rows, int levels,
+                              const unsigned int* fmt_src, unsigned int* fmt_dst,
                               hipStream_t s) {
   if (rows < 3 || rows % 3 != 0) return hipErrorInvalidValue;
   if (!fused_levels_available(coll, bc, st, levels)) return hipErrorInvalidValue;
   return with_storage(st, [&](auto ST) {
-    return fused_launch_st<ST.value>(eq, coll, bc, src, dst, g, c, rows, levels, s);
+    return fused_launch_st<ST.value>(eq, coll, bc, src, dst, g, c, rows, levels, fmt_src,
+                                     fmt_dst, s);
   });
 }
 
@@ -486,39 +560,49 @@ int fused_rows(int st, int nx, int ny, const FusedShape& sh, int levels) {
 
 hipError_t launch_init(int eq, int st, const double* rho, const double* ux, const double* uy,
                        void* dst, const Geometry& g, const Coef64& c, unsigned int* bad,
-                       hipStream_t s) {
+                       unsigned int* fmt, hipStream_t s) {
   return with_storage(st, [&](auto ST) {
     using T = typename Storage<ST.value>::T;
     return with_eq(eq, [&](auto EQ) {
       init_kernel<EQ.value, ST.value><<<blocks_for(g.plane), kThreads, 0, s>>>(
-          rho, ux, uy, static_cast<T*>(dst), g, c, bad);
+          rho, ux, uy, static_cast<T*>(dst), g, c, bad, fmt);
       return hipGetLastError();
     });
   });
 }
 
 hipError_t launch_import_plane(int st, int i, const double* fin, void* dst, const Geometry& g,
-                               const Coef64& c, hipStream_t s) {
+                               const Coef64& c, unsigned int* fmt, hipStream_t s) {
   return with_storage(st, [&](auto ST) {
     using T = typename Storage<ST.value>::T;
     import_kernel<ST.value><<<blocks_for(g.plane), kThreads, 0, s>>>(i, fin, static_cast<T*>(dst),
-                                                                      g, c);
+                                                                      g, c, fmt);
     return hipGetLastError();
   });
 }
 
-hipError_t launch_export_plane(int st, int i, const void* src, double* fout, const Geometry& g,
-                               const Coef64& c, hipStream_t s) {
-  return with_storage(st, [&](auto ST) {
+// Runs f(storage, equilibrium of five-number nodes or kPopsOnly).
+template <class F>
+hipError_t with_form(int eq, int st, const unsigned int* fmt, F&& f) {
+  if (!fmt) return with_storage(st, [&](auto ST) { return f(ST, IC<kPopsOnly>{}); });
+  if (st != LB_F64) return hipErrorInvalidValue;
+  return with_eq(eq, [&](auto EQ) { return f(IC<LB_F64>{}, EQ); });
+}
+
+hipError_t launch_export_plane(int eq, int st, int i, const void* src, double* fout,
+                               const Geometry& g, const Coef64& c, const unsigned int* fmt,
+                               hipStream_t s) {
+  return with_form(eq, st, fmt, [&](auto ST, auto NEQ) {
     using T = typename Storage<ST.value>::T;
-    export_kernel<ST.value><<<blocks_for(g.plane), kThreads, 0, s>>>(
-        i, static_cast<const T*>(src), fout, g, c);
+    export_kernel<ST.value, NEQ.value><<<blocks_for(g.plane), kThreads, 0, s>>>(
+        i, static_cast<const T*>(src), fout, g, c, fmt);
     return hipGetLastError();
   });
 }
 
-hipError_t launch_moments(int st, const void* src, double* out, const Geometry& g,
-                          const Coef64& c, hipStream_t s) {
+hipError_t launch_moments(int eq, int st, const void* src, double* out, const Geometry& g,
+                          const Coef64& c, const unsigned int* fmt, hipStream_t s) {
+  if (fmt) return launch_strip_moments(eq, src, out, g, c, fmt, s);
   return with_storage(st, [&](auto ST) {
     using T = typename Storage<ST.value>::T;
     moments_kernel<ST.value><<<blocks_for(g.plane), kThreads, 0, s>>>(static_cast<const T*>(src),
@@ -527,18 +611,21 @@ hipError_t launch_moments(int st, const void* src, double* out, const Geometry& 
   });
 }
 
-hipError_t launch_diagnostics(int st, const void* src, double* partials, double* out,
+hipError_t launch_diagnostics(int eq, int st, const void* src, double* partials, double* out,
                               const Geometry& g, const Coef64& c, double theta_energy,
-                              hipStream_t s) {
-  return with_storage(st, [&](auto ST) {
-    using T = typename Storage<ST.value>::T;
-    diag_kernel<ST.value><<<kDiagBlocks, kThreads, 0, s>>>(static_cast<const T*>(src), partials, g,
-                                                           c, theta_energy);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    diag_final_kernel<<<1, kThreads, 0, s>>>(partials, kDiagBlocks, out);
-    return hipGetLastError();
-  });
+                              const unsigned int* fmt, hipStream_t s) {
+  int blocks = kDiagBlocks;
+  const hipError_t e =
+      fmt ? launch_strip_diagnostics(eq, src, partials, &blocks, g, c, theta_energy, fmt, s)
+          : with_storage(st, [&](auto ST) {
+              using T = typename Storage<ST.value>::T;
+              diag_kernel<ST.value><<<kDiagBlocks, kThreads, 0, s>>>(static_cast<const T*>(src),
+                                                                     partials, g, c, theta_energy);
+              return hipGetLastError();
+            });
+  if (e != hipSuccess) return e;
+  diag_final_kernel<<<1, kThreads, 0, s>>>(partials, blocks, out);
+  return hipGetLastError();
 }
 
 hipError_t launch_tile_map(const LatticeDesc* d, int n, int* tile_map, int64_t tiles,
@@ -557,14 +644,22 @@ hipError_t launch_batched_fused(int eq, int st, const LatticeDesc* d, const int*
   });
 }
 
-hipError_t launch_profile(int st, const void* src, double* out, const Geometry& g,
-                          const Coef64& c, hipStream_t s) {
-  return with_storage(st, [&](auto ST) {
+hipError_t launch_profile(int eq, int st, const void* src, double* out, double* partials,
+                          const Geometry& g, const Coef64& c, const unsigned int* fmt,
+                          hipStream_t s) {
+  // About four workgroups per CU, and at least eight rows per chunk.
+  const int xblocks = (int)blocks_for(g.nx);
+  const int want = std::max(1, std::min(1024 / xblocks, g.ny / 8));
+  const int rows = (g.ny + want - 1) / want, chunks = (g.ny + rows - 1) / rows;
+  const hipError_t e = with_form(eq, st, fmt, [&](auto ST, auto NEQ) {
     using T = typename Storage<ST.value>::T;
-    profile_kernel<ST.value><<<blocks_for(g.nx), kThreads, 0, s>>>(static_cast<const T*>(src),
-                                                                    out, g, c);
+    profile_kernel<ST.value, NEQ.value><<<dim3(xblocks, chunks), kThreads, 0, s>>>(
+        static_cast<const T*>(src), partials, g, c, rows, fmt);
     return hipGetLastError();
   });
+  if (e != hipSuccess) return e;
+  profile_final_kernel<<<xblocks, kThreads, 0, s>>>(partials, out, g.nx, g.ny, chunks);
+  return hipGetLastError();
 }
 
 }  // namespace oreg

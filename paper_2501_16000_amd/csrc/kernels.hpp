@@ -39,9 +39,17 @@ int fused_levels(int st);
 // Wavefronts that sweep one strip of a fused launch together (1 or 4).
 int fused_wavefronts(int st);
 
-// Whether a fused launch of `levels` steps (2 .. fused_levels(st)) is
+// Whether strip launches of this configuration store the five numbers of a
+// node (d2q9.hpp: Params) instead of its populations: periodic OReg in F64.  A
+// device flag per buffer then says what it holds (0: populations, as after an
+// init or a restored checkpoint, 1: five numbers); the kernels read and set the
+// flags, so that captured launches follow the state.  The launchers below take
+// null flags where every buffer holds populations.
+bool fused_numbers(int coll, int bc, int st);
+
+// Whether a fused launch of `levels` steps (1 .. fused_levels(st)) is
 // compiled for this collision and boundary: the full count always, fewer
-// steps for periodic OReg lattices.
+// steps for periodic OReg lattices, a single one where it stores numbers.
 bool fused_levels_available(int coll, int bc, int st, int levels);
 
 // `levels` time steps in one launch: src -> dst; each column strip (of one
@@ -49,6 +57,7 @@ bool fused_levels_available(int coll, int bc, int st, int levels);
 // multiple of 3) output rows.
 hipError_t launch_fused_sweep(int eq, int coll, int bc, int st, const void* src, void* dst,
                               const Geometry& g, const Coef64& c, int rows, int levels,
+                              const unsigned int* fmt_src, unsigned int* fmt_dst,
                               hipStream_t s);
 
 // SIMDs of the current device and wavefronts of the `levels`-step fused sweep
@@ -79,29 +88,40 @@ hipError_t launch_block_sweep(int eq, int coll, int bc, int st, const void* src,
 // (non-finite value or rho <= 0) into *bad.
 hipError_t launch_init(int eq, int st, const double* rho, const double* ux, const double* uy,
                        void* dst, const Geometry& g, const Coef64& c, unsigned int* bad,
-                       hipStream_t s);
+                       unsigned int* fmt, hipStream_t s);
 
 // Plane i of g from plane i of pre-collision FP64 populations (device).
 hipError_t launch_import_plane(int st, int i, const double* fin, void* dst, const Geometry& g,
-                               const Coef64& c, hipStream_t s);
+                               const Coef64& c, unsigned int* fmt, hipStream_t s);
 
 // Plane i of the pre-collision FP64 populations (device) from g.
-hipError_t launch_export_plane(int st, int i, const void* src, double* fout, const Geometry& g,
-                               const Coef64& c, hipStream_t s);
+hipError_t launch_export_plane(int eq, int st, int i, const void* src, double* fout,
+                               const Geometry& g, const Coef64& c, const unsigned int* fmt,
+                               hipStream_t s);
 
 // rho, ux, uy of the pre-collision state into out[3][ny][nx] (device FP64).
-hipError_t launch_moments(int st, const void* src, double* out, const Geometry& g,
-                          const Coef64& c, hipStream_t s);
+hipError_t launch_moments(int eq, int st, const void* src, double* out, const Geometry& g,
+                          const Coef64& c, const unsigned int* fmt, hipStream_t s);
 
 // Diagnostics of the pre-collision state: partials[kDiagBlocks][6] scratch,
 // out[6] result (device FP64).
-hipError_t launch_diagnostics(int st, const void* src, double* partials, double* out,
+hipError_t launch_diagnostics(int eq, int st, const void* src, double* partials, double* out,
                               const Geometry& g, const Coef64& c, double theta_energy,
-                              hipStream_t s);
+                              const unsigned int* fmt, hipStream_t s);
 
-// y-average of rho(x): out[nx] (device FP64).
-hipError_t launch_profile(int st, const void* src, double* out, const Geometry& g,
-                          const Coef64& c, hipStream_t s);
+// The two readers of lattices with format flags (readers_f64.hip); *blocks
+// receives the number of partial rows (at most kDiagBlocks).
+hipError_t launch_strip_moments(int eq, const void* src, double* out, const Geometry& g,
+                                const Coef64& c, const unsigned int* fmt, hipStream_t s);
+hipError_t launch_strip_diagnostics(int eq, const void* src, double* partials, int* blocks,
+                                    const Geometry& g, const Coef64& c, double theta_energy,
+                                    const unsigned int* fmt, hipStream_t s);
+
+// y-average of rho(x): out[nx] (device FP64); partials holds nx * ny doubles
+// at most.
+hipError_t launch_profile(int eq, int st, const void* src, double* out, double* partials,
+                          const Geometry& g, const Coef64& c, const unsigned int* fmt,
+                          hipStream_t s);
 
 // ------------------------------------------------------------ serving --
 // One resident lattice of a server, as the batched sweep reads it.

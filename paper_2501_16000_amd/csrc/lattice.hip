@@ -37,7 +37,10 @@ struct lb_lattice {
   int64_t t = 0;
   double* tmp = nullptr;              // 3 * plane FP64 staging (lazy)
   double* aux = nullptr;              // kDiagBlocks*6 partials + 8 results
-  unsigned int* counter = nullptr;    // invalid-input count of lb_init*
+  unsigned int* counter = nullptr;    // invalid-input count of lb_init*, then the format flags
+  bool numbers = false;               // steps store five numbers per node (see fused_numbers)
+  // Format flag of buffer b (null where every buffer holds populations).
+  unsigned int* fmt(int b) const { return numbers ? counter + 1 + b : nullptr; }
   std::string err;
 };
 
@@ -290,13 +293,14 @@ lb_status lb_create_ex(const lb_options* opt, lb_lattice** out) {
   }
   e = hipMalloc((void**)&h->aux, (kDiagBlocks * 6 + 8) * sizeof(double));
   if (e != hipSuccess) return cleanup(hip_fail(nullptr, e, "hipMalloc(aux)"));
-  e = hipMalloc((void**)&h->counter, sizeof(unsigned int));
+  e = hipMalloc((void**)&h->counter, 3 * sizeof(unsigned int));
   if (e != hipSuccess) return cleanup(hip_fail(nullptr, e, "hipMalloc(counter)"));
   if (hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     h->cus = 256;
   h->strips = plan_strips(h->opt.storage, h->geo.nx, h->geo.ny);
+  h->numbers = h->strips && fused_numbers(h->opt.collision, h->opt.boundary_x, h->opt.storage);
   if (h->strips) {
-    for (int L = 2; L <= fused_levels(h->opt.storage); ++L)
+    for (int L = 1; L <= fused_levels(h->opt.storage); ++L)
       if (fused_levels_available(h->opt.collision, h->opt.boundary_x, h->opt.storage, L))
         h->fused_rows[L] = fused_rows(h->opt.storage, h->geo.nx, h->geo.ny,
                                       fused_shape(h->opt.storage, L), L);
@@ -325,7 +329,7 @@ lb_status lb_init(lb_lattice* h, const double* rho, const double* ux, const doub
   HIP_TRY(h, hipMemcpyAsync(h->tmp + 2 * n, uy, bytes, hipMemcpyHostToDevice, h->stream));
   HIP_TRY(h, hipMemsetAsync(h->counter, 0, sizeof(unsigned int), h->stream));
   HIP_TRY(h, launch_init(h->opt.equilibrium, h->opt.storage, h->tmp, h->tmp + n, h->tmp + 2 * n,
-                         h->buf[h->cur], h->geo, h->coef, h->counter, h->stream));
+                         h->buf[h->cur], h->geo, h->coef, h->counter, h->fmt(h->cur), h->stream));
   return finish_init(h);
 }
 
@@ -336,7 +340,7 @@ lb_status lb_init_device(lb_lattice* h, const double* rho, const double* ux, con
   if (!ds.ok) return fail(h, LB_EDEVICE, "cannot select device %d", h->device);
   HIP_TRY(h, hipMemsetAsync(h->counter, 0, sizeof(unsigned int), h->stream));
   HIP_TRY(h, launch_init(h->opt.equilibrium, h->opt.storage, rho, ux, uy, h->buf[h->cur], h->geo,
-                         h->coef, h->counter, h->stream));
+                         h->coef, h->counter, h->fmt(h->cur), h->stream));
   return finish_init(h);
 }
 
@@ -353,18 +357,19 @@ lb_status lb_step(lb_lattice* h, int64_t n) {
     h->t += L;
     left -= L;
   };
-  if (h->opt.fuse_steps != 1 && h->strips) {
-    // Strip launches advance K steps each.  A remainder of two or more steps
-    // runs as one shorter launch where that is compiled (periodic OReg: it
-    // reads and writes the state once, where single steps would do so per
-    // step), otherwise, and for a single step, one step per launch.
-    const int64_t K = fused_levels(h->opt.storage);
-    while (left >= 2) {
+  if (h->strips && (h->numbers || h->opt.fuse_steps != 1)) {
+    // Strip launches advance K steps each.  A remainder runs as one shorter
+    // launch where that is compiled (periodic OReg: it reads and writes the
+    // state once, where single steps would do so per step), otherwise, and for
+    // a single step of a lattice stored as populations, one step per launch.
+    const int64_t K = h->opt.fuse_steps == 1 ? 1 : fused_levels(h->opt.storage);
+    while (left > 0) {
       const int L = (int)std::min<int64_t>(K, left);
       if (!fused_levels_available(h->opt.collision, h->opt.boundary_x, h->opt.storage, L)) break;
       HIP_TRY(h, launch_fused_sweep(h->opt.equilibrium, h->opt.collision, h->opt.boundary_x,
                                     h->opt.storage, h->buf[h->cur], h->buf[1 - h->cur], h->geo,
-                                    h->coef, h->fused_rows[L], L, h->stream));
+                                    h->coef, h->fused_rows[L], L, h->fmt(h->cur),
+                                    h->fmt(1 - h->cur), h->stream));
       done(L);
     }
   } else if (h->opt.fuse_steps != 1 && h->best.us >= 0) {
@@ -410,7 +415,8 @@ lb_status lb_moments_device(lb_lattice* h, double* out_dev) {
   if (!h->initialized) return fail(h, LB_ESTATE, "lattice is not initialized");
   DeviceScope ds(h->device);
   if (!ds.ok) return fail(h, LB_EDEVICE, "cannot select device %d", h->device);
-  HIP_TRY(h, launch_moments(h->opt.storage, h->buf[h->cur], out_dev, h->geo, h->coef, h->stream));
+  HIP_TRY(h, launch_moments(h->opt.equilibrium, h->opt.storage, h->buf[h->cur], out_dev, h->geo,
+                           h->coef, h->fmt(h->cur), h->stream));
   return LB_OK;
 }
 
@@ -422,7 +428,8 @@ lb_status lb_moments(lb_lattice* h, double* out) {
   if (!ds.ok) return fail(h, LB_EDEVICE, "cannot select device %d", h->device);
   lb_status st = ensure_tmp(h);
   if (st != LB_OK) return st;
-  HIP_TRY(h, launch_moments(h->opt.storage, h->buf[h->cur], h->tmp, h->geo, h->coef, h->stream));
+  HIP_TRY(h, launch_moments(h->opt.equilibrium, h->opt.storage, h->buf[h->cur], h->tmp, h->geo,
+                           h->coef, h->fmt(h->cur), h->stream));
   HIP_TRY(h, hipMemcpyAsync(out, h->tmp, 3 * (size_t)h->geo.plane * sizeof(double),
                             hipMemcpyDeviceToHost, h->stream));
   HIP_TRY(h, hipStreamSynchronize(h->stream));
@@ -442,8 +449,8 @@ lb_status lb_populations(lb_lattice* h, double* out) {
     // The staging buffer holds three planes; cycle through them so that a
     // plane is not overwritten before its copy has been issued.
     double* stage = h->tmp + (i % 3) * n;
-    HIP_TRY(h, launch_export_plane(h->opt.storage, i, h->buf[h->cur], stage, h->geo, h->coef,
-                                   h->stream));
+    HIP_TRY(h, launch_export_plane(h->opt.equilibrium, h->opt.storage, i, h->buf[h->cur], stage,
+                                   h->geo, h->coef, h->fmt(h->cur), h->stream));
     HIP_TRY(h, hipMemcpyAsync(out + (size_t)i * n, stage, (size_t)n * sizeof(double),
                               hipMemcpyDeviceToHost, h->stream));
   }
@@ -473,7 +480,7 @@ lb_status lb_set_populations(lb_lattice* h, const double* in) {
     HIP_TRY(h, hipMemcpyAsync(stage, in + (size_t)i * n, (size_t)n * sizeof(double),
                               hipMemcpyHostToDevice, h->stream));
     HIP_TRY(h, launch_import_plane(h->opt.storage, i, stage, h->buf[h->cur], h->geo, h->coef,
-                                   h->stream));
+                                   h->fmt(h->cur), h->stream));
   }
   HIP_TRY(h, hipStreamSynchronize(h->stream));
   h->initialized = true;
@@ -488,8 +495,8 @@ lb_status lb_diagnostics(lb_lattice* h, double out[6]) {
   DeviceScope ds(h->device);
   if (!ds.ok) return fail(h, LB_EDEVICE, "cannot select device %d", h->device);
   double* result = h->aux + kDiagBlocks * 6;
-  HIP_TRY(h, launch_diagnostics(h->opt.storage, h->buf[h->cur], h->aux, result, h->geo, h->coef,
-                                h->theta_energy, h->stream));
+  HIP_TRY(h, launch_diagnostics(h->opt.equilibrium, h->opt.storage, h->buf[h->cur], h->aux, result,
+                                h->geo, h->coef, h->theta_energy, h->fmt(h->cur), h->stream));
   HIP_TRY(h, hipMemcpyAsync(out, result, 6 * sizeof(double), hipMemcpyDeviceToHost, h->stream));
   HIP_TRY(h, hipStreamSynchronize(h->stream));
   return LB_OK;
@@ -506,8 +513,8 @@ lb_status lb_diagnostics_device_noalloc(lb_lattice* h, double* out_dev) {
   if (st != LB_OK) return st;
   // The same two kernels as lb_diagnostics, in the same reduction order; every
   // partial is written before the final kernel reads it, so nothing is cleared.
-  HIP_TRY(h, launch_diagnostics(h->opt.storage, h->buf[h->cur], partials, out_dev, h->geo,
-                                h->coef, h->theta_energy, h->stream));
+  HIP_TRY(h, launch_diagnostics(h->opt.equilibrium, h->opt.storage, h->buf[h->cur], partials, out_dev,
+                                h->geo, h->coef, h->theta_energy, h->fmt(h->cur), h->stream));
   return LB_OK;
 }
 
@@ -519,7 +526,8 @@ lb_status lb_density_profile(lb_lattice* h, double* out) {
   if (!ds.ok) return fail(h, LB_EDEVICE, "cannot select device %d", h->device);
   lb_status st = ensure_tmp(h);
   if (st != LB_OK) return st;
-  HIP_TRY(h, launch_profile(h->opt.storage, h->buf[h->cur], h->tmp, h->geo, h->coef, h->stream));
+  HIP_TRY(h, launch_profile(h->opt.equilibrium, h->opt.storage, h->buf[h->cur], h->tmp,
+                            h->tmp + h->geo.nx, h->geo, h->coef, h->fmt(h->cur), h->stream));
   HIP_TRY(h, hipMemcpyAsync(out, h->tmp, (size_t)h->geo.nx * sizeof(double),
                             hipMemcpyDeviceToHost, h->stream));
   HIP_TRY(h, hipStreamSynchronize(h->stream));
@@ -545,7 +553,7 @@ lb_status lb_get_options(const lb_lattice* h, lb_options* out) {
 int64_t lb_device_bytes(const lb_lattice* h) {
   if (!h) return 0;
   int64_t b = 2 * 9 * h->geo.plane * (int64_t)h->elem;
-  b += (kDiagBlocks * 6 + 8) * (int64_t)sizeof(double) + (int64_t)sizeof(unsigned int);
+  b += (kDiagBlocks * 6 + 8) * (int64_t)sizeof(double) + 3 * (int64_t)sizeof(unsigned int);
   if (h->tmp) b += 3 * h->geo.plane * (int64_t)sizeof(double);
   return b;
 }

@@ -294,8 +294,8 @@ lb_status retire(lb_server* s, ServedLattice* L) {
   const size_t bytes = 3 * (size_t)cells * sizeof(double);
   const bool pinned = s->pin_out_arena.alloc(bytes, &L->out_off);
   L->out_bytes = bytes;
-  STRY(s, launch_moments(s->opt.storage, d.buf[L->nlaunch & 1], d.fields, g, d.coef,
-                         s->compute));
+  STRY(s, launch_moments(s->opt.equilibrium, s->opt.storage, d.buf[L->nlaunch & 1], d.fields, g,
+                         d.coef, nullptr, s->compute));
   hipEvent_t gathered;
   STRY(s, hipEventCreateWithFlags(&gathered, hipEventDisableTiming));
   STRY(s, hipEventRecord(gathered, s->compute));
@@ -497,7 +497,8 @@ lb_status lb_server_submit(lb_server* s, const lb_request* r) {
   // The fields were validated above, so init_kernel's invalid-node counter
   // is never incremented and not read back.
   e = launch_init(s->opt.equilibrium, s->opt.storage, d.fields, d.fields + cells,
-                  d.fields + 2 * cells, d.buf[0], g, d.coef, s->d_bad, s->compute);
+                  d.fields + 2 * cells, d.buf[0], g, d.coef, s->d_bad, nullptr,
+                  s->compute);
   if (e != hipSuccess) return undo(hfail(s, e, "launch_init"));
   L->upload_pending = true;
   s->uploading.push_back(L);

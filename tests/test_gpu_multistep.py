@@ -61,3 +61,69 @@ def test_multi_step_launches_equal_single_steps(nx, ny, steps, eq, coll, bc, sto
             assert L.time == steps
             out.append(L.populations())
     np.testing.assert_array_equal(out[0], out[1])
+
+
+NUMBER_CASES = [
+    # nx, ny, steps, equilibrium: F64 lattices large enough for strips, which
+    # store five numbers per node after every launch
+    (548, 548, 15, "guided"),        # 7 + 7 + 1 steps
+    (701, 613, 10, "poly2"),         # ragged strips and row blocks
+    (40, 8000, 9, "guided"),         # narrower than a strip
+    (8000, 40, 6, "poly2"),
+]
+
+
+@pytest.mark.parametrize("nx,ny,steps,eq", NUMBER_CASES)
+def test_steps_from_numbers_equal_steps_from_populations(nx, ny, steps, eq):
+    """A step that starts from the five numbers of every node equals, bit for
+    bit, one that starts from the populations, which a checkpoint forces."""
+    from paper_2501_16000_amd import oreg
+    print(f"[numbers] {nx}x{ny} {steps} {eq}", flush=True)
+    f0 = populations(eq, 1 / 3, ny, nx, seed=nx + 3 * ny)
+    with oreg.Lattice(nx, ny, 0.7, equilibrium=eq) as A, \
+            oreg.Lattice(nx, ny, 0.7, equilibrium=eq) as B:
+        A.set_populations(f0)
+        A.step(steps)
+        B.set_populations(f0)
+        for _ in range(steps):
+            B.step(1)
+            B.set_populations(B.populations())
+        fa = A.populations()
+        np.testing.assert_array_equal(fa, B.populations())
+        # A holds five numbers per node, B populations
+        np.testing.assert_array_equal(A.moments(), B.moments())
+        np.testing.assert_array_equal(A.diagnostics(), B.diagnostics())
+        np.testing.assert_array_equal(A.density_profile(), B.density_profile())
+        ref = oracle.run(f0, steps, 0.7, 1 / 3, eq)
+        assert float(np.max(np.abs(fa - ref) / np.abs(ref))) <= 1e-12
+        m = oracle.moments(ref)
+        np.testing.assert_allclose(A.moments(), m, rtol=0, atol=1e-12)
+        np.testing.assert_allclose(A.density_profile(), m[0].mean(0), rtol=1e-12)
+        np.testing.assert_allclose(A.diagnostics()[:5], oracle.diagnostics(ref, 1 / 3)[:5],
+                                   rtol=1e-11, atol=1e-9)
+
+
+def test_captured_steps_follow_a_new_init():
+    """A captured graph of steps replayed on a state that was initialized after
+    the capture: the kernels read the buffers' format on the device."""
+    import torch
+    from paper_2501_16000_amd import oreg
+    n = 560
+    stream = torch.cuda.Stream()
+    f = [workloads.shear_wave(n, u) for u in (0.02, 0.03)]
+    with torch.cuda.stream(stream), oreg.Lattice(n, n, 0.7, stream=stream) as A, \
+            oreg.Lattice(n, n, 0.7, stream=stream) as B:
+        A.init(*f[0])
+        A.step(14)
+        A.sync()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            A.step(14)
+        for fields in f:
+            A.init(*fields)
+            B.init(*fields)
+            for k in range(3):
+                graph.replay()
+                torch.cuda.synchronize()
+                B.step(14)
+                np.testing.assert_array_equal(A.populations(), B.populations(), err_msg=str(k))

@@ -17,7 +17,7 @@ INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "liboreg.so")
 SOURCES = ["lattice.hip", "kernels.hip", "tile.hip", "block.hip", "readers_f64.hip", "fused_f64.hip", "fused_f32s.hip", "fused_f16s.hip",
-           "fused_bf16s.hip", "serve.hip", "lattice3.hip", "kernels3.hip", "march3.hip", "copy.hip"]
+           "fused_bf16s.hip", "serve_strips.hip", "serve.hip", "lattice3.hip", "kernels3.hip", "march3.hip", "copy.hip"]
 
 ARCH = "gfx950"
 # -packed-fp32-ops: keep the compiler from forming packed FP32 instructions.

@@ -168,8 +168,49 @@ __global__ __launch_bounds__(64 * kBlockWaves) void block_kernel(
                                    blockDim.x >> 6, L);
 }
 
+// The server's batched launch: each workgroup takes one tile of one resident
+// lattice and advances it by that lattice's own step count kl.  The tiles are
+// laid out for the most steps a launch takes, so a lattice's last launch, of
+// fewer steps, has the same ones.
+template <int RR, int EQ, int ST>
+__global__ __launch_bounds__(64 * kBlockWaves) void batched_block_kernel(
+    const LatticeDesc* __restrict__ d, const int* __restrict__ map, int64_t T) {
+  using Tt = typename Storage<ST>::T;
+  const int item = xcd_block();
+  const LatticeDesc& L = d[map[item]];
+  const int local = (int)(item - L.tile_begin);
+  const int by = local / L.strips, bx = local - by * L.strips;
+  const int64_t t = T - L.admit_T;
+  const Coeffs<typename Storage<ST>::R> k(L.coef);
+  block_tile<RR, EQ, LB_COLL_OREG, LB_BC_PERIODIC, ST>(
+      static_cast<const Tt*>(L.buf[t & 1]), static_cast<Tt*>(L.buf[(t + 1) & 1]), L.nx, L.ny,
+      L.plane, k, bx * L.cols, by * L.rows, L.cols, L.rows, blockDim.x >> 6, L.kl);
+}
+
 }  // namespace
 using namespace detail;
+
+hipError_t launch_batched_block(int eq, int st, const LatticeDesc* d, const int* item_map,
+                                int64_t items, int64_t T, int waves, int rows, hipStream_t s) {
+  if (items <= 0) return hipSuccess;
+  if (waves < 1 || waves > kBlockWaves) return hipErrorInvalidValue;
+  return with_eq(eq, [&](auto EQ) {
+    auto go = [&](auto RR, auto ST) {
+      batched_block_kernel<RR.value, EQ.value, ST.value>
+          <<<(unsigned int)items, 64 * waves, 0, s>>>(d, item_map, T);
+      return hipGetLastError();
+    };
+    auto rr = [&](auto ST) -> hipError_t {
+      if (rows == block_rows_small(ST.value)) return go(IC<block_rows_small(ST.value)>{}, ST);
+      if (rows == block_rows_big(ST.value)) return go(IC<block_rows_big(ST.value)>{}, ST);
+      return hipErrorInvalidValue;
+    };
+    if (st == LB_F32S) return rr(IC<LB_F32S>{});
+    if (st == LB_F16S) return rr(IC<LB_F16S>{});
+    if (st == LB_BF16S) return rr(IC<LB_BF16S>{});
+    return hipErrorInvalidValue;
+  });
+}
 
 hipError_t launch_block_sweep(int eq, int coll, int bc, int st, const void* src, void* dst,
                               const Geometry& g, const Coef64& c, const BlockShape& b, int levels,

@@ -115,8 +115,4 @@ hipError_t fused_launch_st(int eq, int coll, int bc, const void* src, void* dst,
                            unsigned int* fmt_dst, hipStream_t s);
 template <int ST>
 hipError_t fused_occupancy_st(int levels, int* blocks);
-template <int ST>
-hipError_t batched_fused_launch_st(int eq, const LatticeDesc* d, const int* item_map, int64_t items,
-                                   int64_t T, hipStream_t s);
-
 }  // namespace oreg

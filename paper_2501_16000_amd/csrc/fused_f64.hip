@@ -1,4 +1,4 @@
-// fused_f64.hip -- the fused multi-step sweeps (lb_step and the server) for
+// fused_f64.hip -- the fused multi-step sweeps of lb_step for
 // FP64 storage: instantiations of fused_impl.hpp.
 #include "fused_impl.hpp"
 
@@ -8,7 +8,5 @@ template hipError_t fused_launch_st<LB_F64>(int, int, int, const void*, void*, c
                                            const Coef64&, int, int, const unsigned int*,
                                            unsigned int*, hipStream_t);
 template hipError_t fused_occupancy_st<LB_F64>(int, int*);
-template hipError_t batched_fused_launch_st<LB_F64>(int, const LatticeDesc*, const int*, int64_t,
-                                                   int64_t, hipStream_t);
 
 }  // namespace oreg

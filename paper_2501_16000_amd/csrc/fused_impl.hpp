@@ -1,8 +1,8 @@
 // fused_impl.hpp -- the fused multi-step D2Q9 sweep (K time steps per
-// launch, register-resident row pipeline) and its batched serving form, with
-// their host launchers as templates over the storage format.  Included only
-// by fused_f64.hip, fused_f32s.hip, fused_f16s.hip and fused_bf16s.hip, which
-// instantiate them for one format each.
+// launch, register-resident row pipeline) with its host launcher as templates
+// over the storage format.  Included by fused_f64.hip, fused_f32s.hip,
+// fused_f16s.hip and fused_bf16s.hip, which instantiate them for one format
+// each, by serve_strips.hip (its batched form) and by readers_f64.hip.
 #pragma once
 
 #include "dispatch.hpp"
@@ -396,43 +396,6 @@ __global__ __launch_bounds__(256) void fused_sweep_kernel(
   }
 }
 
-// Batched form of fused_sweep_kernel for the server: each wavefront takes one
-// work item (lattice, column strip, row block) of a descriptor table and runs
-// the same pipeline with that lattice's own step count kl <= KMAX and row
-// block height.  Strips are KMAX-wide at every kl, so the item layout of a
-// lattice does not change when its last launch has fewer steps.
-template <int KMAX, int EQ, int ST>
-__global__ __launch_bounds__(256) void batched_fused_kernel(const LatticeDesc* __restrict__ d,
-                                                            const int* __restrict__ map,
-                                                            int64_t items, int64_t T) {
-  using S = Storage<ST>;
-  using Tt = typename S::T;
-  constexpr int W = 64 - 2 * KMAX;
-  // The wavefront index is uniform: with readfirstlane the descriptor loads
-  // become scalar loads and the lattice's parameters stay in scalar
-  // registers (without it they took 26-30 VGPRs, one wavefront per SIMD
-  // fewer in F32S, F16S and BF16S).
-  const int64_t item =
-      (int64_t)xcd_block() * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (item >= items) return;  // whole wavefronts leave together
-  const LatticeDesc& L = d[map[item]];
-  const int local = (int)(item - L.tile_begin);
-  const int strip = local % L.strips, seg = local / L.strips;
-  const int H = L.rows;
-  const int64_t t = T - L.admit_T;
-  const Tt* __restrict__ src = static_cast<const Tt*>(L.buf[t & 1]);
-  Tt* __restrict__ dst = static_cast<Tt*>(L.buf[(t + 1) & 1]);
-  const Coeffs<typename S::R> k(L.coef);
-  // The step count is uniform over the wavefront: branch to the pipeline
-  // compiled for it.
-  unroll<1, KMAX + 1>([&](auto KL) {
-    if (L.kl == KL.value)
-      fused_strip<KL.value, KMAX, EQ, LB_COLL_OREG, LB_BC_PERIODIC, ST>(
-          src, dst, L.nx, L.ny, L.plane, strip * W, seg * H, H, k, lane);
-  });
-}
-
 }  // namespace
 
 template <int ST>
@@ -498,17 +461,6 @@ hipError_t fused_occupancy_st(int levels, int* blocks) {
     if (levels == L.value) e = occ(L);
   });
   return e;
-}
-
-template <int ST>
-hipError_t batched_fused_launch_st(int eq, const LatticeDesc* d, const int* item_map, int64_t items,
-                                   int64_t T, hipStream_t s) {
-  constexpr int K = FusedLevels<ST>::K;
-  return with_eq(eq, [&](auto EQ) {
-    batched_fused_kernel<K, EQ.value, ST><<<(unsigned int)((items + 3) / 4), 256, 0, s>>>(
-        d, item_map, items, T);
-    return hipGetLastError();
-  });
 }
 
 }  // namespace oreg

@@ -636,14 +636,6 @@ hipError_t launch_tile_map(const LatticeDesc* d, int n, int* tile_map, int64_t t
 
 int fused_strip_width(int st) { return 64 - 2 * fused_levels(st); }
 
-hipError_t launch_batched_fused(int eq, int st, const LatticeDesc* d, const int* item_map,
-                                int64_t items, int64_t T, hipStream_t s) {
-  if (items <= 0) return hipSuccess;
-  return with_storage(st, [&](auto ST) {
-    return batched_fused_launch_st<ST.value>(eq, d, item_map, items, T, s);
-  });
-}
-
 hipError_t launch_profile(int eq, int st, const void* src, double* out, double* partials,
                           const Geometry& g, const Coef64& c, const unsigned int* fmt,
                           hipStream_t s) {

@@ -133,9 +133,9 @@ struct LatticeDesc {
   int64_t admit_T;     // server launch counter at admission; the state is in
                        // buf[(T - admit_T) % 2] before launch T
   int64_t tile_begin;  // first work item of this lattice
-  int kl;              // fused launches: time steps this launch advances the lattice
-  int rows;            // fused launches: output rows per work item
-  int strips;          // fused launches: column strips
+  int kl;              // time steps this launch advances the lattice
+  int rows, cols;      // output rows and columns of a work item
+  int strips;          // work items side by side
   Coef64 coef;
 };
 
@@ -144,12 +144,16 @@ struct LatticeDesc {
 hipError_t launch_tile_map(const LatticeDesc* d, int n, int* tile_map, int64_t tiles,
                            hipStream_t s);
 
-// Fused batched launches: up to fused_levels(st) steps per lattice per launch
-// (d[i].kl each), one wavefront per work item (a column strip x a row block).
-// Column strip width of the fused sweep for storage st.
+// Batched launches: up to fused_levels(st) steps per lattice per launch (d[i].kl
+// each).  launch_batched_fused (F64, F16S, BF16S): one wavefront per work item,
+// a column strip of fused_strip_width(st) columns x a row block.
+// launch_batched_block (shifted formats): one workgroup of `waves` wavefronts
+// of `rows` rows per work item, a tile of the block sweep.
 int fused_strip_width(int st);
 hipError_t launch_batched_fused(int eq, int st, const LatticeDesc* d, const int* item_map,
                                 int64_t items, int64_t T, hipStream_t s);
+hipError_t launch_batched_block(int eq, int st, const LatticeDesc* d, const int* item_map,
+                                int64_t items, int64_t T, int waves, int rows, hipStream_t s);
 
 // Plain streaming copy of bytes / 16 16-byte words (copy.hip).
 hipError_t launch_copy(const void* src, void* dst, int64_t bytes, hipStream_t s);

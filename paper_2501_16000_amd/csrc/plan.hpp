@@ -282,4 +282,84 @@ inline StepPlan plan_best(int st, int nx, int ny, int cus) {
   return best;
 }
 
+// Server launches (serve.hip) advance every resident lattice up to K steps, so
+// one work split has to suit the whole set.
+//
+// Block tiles: the shape of the least modelled time for the set's tiles, 64 x
+// 64 regions when they fill the chip, smaller ones when few lattices are
+// resident and the launch would otherwise last as long as one workgroup with
+// many rows.
+struct ServeShape {
+  int waves, rows;  // block tiles (waves > 0)
+  int strip_rows;   // strips (waves = 0): most output rows per work item
+};
+struct LatticeSize {
+  int nx, ny;
+};
+template <class Sizes>
+inline ServeShape serve_blocks(int st, const Sizes& sizes, int K, int cus) {
+  using namespace plan_detail;
+  ServeShape best{kBlockWaves, block_rows_big(st), 0};
+  double best_us = -1;
+  for (int waves : {8, 4, 2}) {
+    for (int rows : {block_rows_big(st), block_rows_small(st)}) {
+      if (waves * rows - 2 * (K - 1) < 4) continue;
+      int64_t tiles = 0;
+      for (const LatticeSize n : sizes) {
+        const BlockShape b = block_shape(n.nx, n.ny, K, waves, rows);
+        tiles += (int64_t)b.tx * b.ty;
+      }
+      BlockShape all{};
+      all.tx = (int)std::min<int64_t>(tiles, 1 << 30);
+      all.ty = 1;
+      all.waves = waves;
+      all.rows = rows;
+      const double us = block_us(st, all, K, cus);
+      if (best_us < 0 || us < best_us) {
+        best_us = us;
+        best.waves = waves;
+        best.rows = rows;
+      }
+    }
+  }
+  return best;
+}
+
+// Column strips of equal row blocks.  Blocks of at most 132 rows when the set
+// fills the chip (2 - 3 % more capacity than 66), fewer rows when it does
+// not: a launch lasts as long as its longest strips, K (rows + 2 K) row
+// collisions, times the strips that share a SIMD (the model of fused_cost).
+template <class Sizes>
+inline int serve_strip_rows(const Sizes& sizes, int K, int width, int cus) {
+  int best = 132;
+  double best_cost = -1;
+  for (int most : {132, 99, 66, 48, 33, 24, 18, 12, 9, 6, 3}) {
+    int64_t items = 0;
+    for (const LatticeSize n : sizes)
+      items += (int64_t)((n.nx + width - 1) / width) * ((n.ny + most - 1) / most);
+    const double w = (double)((items + 4 * cus - 1) / (4 * cus));
+    const double cost = w / (1 + 0.08 * (std::min(w, 2.0) - 1)) * (K * (most + 2 * K) - K * (K + 1) + 2 * K);
+    if (best_cost < 0 || cost < best_cost) {
+      best_cost = cost;
+      best = most;
+    }
+  }
+  return best;
+}
+
+// Capacity of the 2000-request mix (32^2 to 1024^2), GLUPS, blocks : strips, by
+// resident lattices: F16S 256: 180 : 187, 128: 192 : 199, 64: 186 : 187; BF16S
+// 168 : 186, 176 : 193, 173 : 181, and 16: 147 : 62, 4: 68 : 10 (strips of fixed
+// 132 rows); F32S 256: 185 : 173, 64: 188 : 149.  So F32S takes blocks, the
+// 16-bit formats strips from about 60 average lattices on.  F64 takes strips:
+// its blocks leave two wavefronts per SIMD.
+template <class Sizes>
+inline ServeShape serve_shape(int st, const Sizes& sizes, int K, int width, int cus) {
+  int64_t nodes = 0;
+  for (const LatticeSize n : sizes) nodes += (int64_t)n.nx * n.ny;
+  const bool strips = st == LB_F64 || (st != LB_F32S && nodes >= 8000000);
+  if (strips) return ServeShape{0, 0, serve_strip_rows(sizes, K, width, cus)};
+  return serve_blocks(st, sizes, K, cus);
+}
+
 }  // namespace oreg

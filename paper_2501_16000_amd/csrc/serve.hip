@@ -138,6 +138,8 @@ struct lb_server {
   LatticeDesc* h_desc[2] = {nullptr, nullptr};  // pinned staging
   hipEvent_t desc_done[2] = {nullptr, nullptr};
   int desc_slot = 0;
+  ServeShape shape{0, 0, 132};  // work split of the resident set
+  int cus = 256;
   bool dirty = true;
   int64_t tiles = 0;
   int64_t T = 0;
@@ -203,20 +205,42 @@ LatticeDesc describe(const lb_server* s, const ServedLattice* L) {
   d.ny = L->ny;
   d.plane = cells;
   d.admit_T = L->admit_T;
-  const int W = fused_strip_width(s->opt.storage);
   d.kl = L->kl;
-  // Rows per work item: the lattice's rows in equal blocks of at most 132
-  // (rounded up to a multiple of 3, the strip loop's unroll).  Measured on
-  // the 2000-request stream: 2 % (F32S) and 3 % (FP64) more capacity than
-  // blocks of 66 rows with a ragged last one.
-  const int nblk = (L->ny + 131) / 132;
-  d.rows = ((L->ny + nblk - 1) / nblk + 2) / 3 * 3;
-  d.strips = (L->nx + W - 1) / W;
+  if (s->shape.waves == 0) {
+    // Strips of equal row blocks, rounded up to a multiple of 3 (the strip
+    // loop's unroll).
+    d.cols = fused_strip_width(s->opt.storage);
+    const int nblk = (L->ny + s->shape.strip_rows - 1) / s->shape.strip_rows;
+    d.rows = ((L->ny + nblk - 1) / nblk + 2) / 3 * 3;
+  } else {
+    const BlockShape b = plan_detail::block_shape(L->nx, L->ny, fused_levels(s->opt.storage),
+                                                  s->shape.waves, s->shape.rows);
+    d.cols = b.ox;
+    d.rows = b.oy;
+  }
+  d.strips = (L->nx + d.cols - 1) / d.cols;
   d.coef = s->base;
   d.coef.kappa0 = (1.0 - 1.0 / L->tau) / (2.0 * s->base.theta * s->base.theta);
   d.coef.omega = 1.0 / L->tau;
   return d;
 }
+
+// The sizes of the resident lattices, for the work split (plan.hpp).
+struct ActiveSizes {
+  ServedLattice* const* first;
+  ServedLattice* const* last;
+  struct It {
+    ServedLattice* const* p;
+    LatticeSize operator*() const { return {(*p)->nx, (*p)->ny}; }
+    It& operator++() {
+      ++p;
+      return *this;
+    }
+    bool operator!=(const It& o) const { return p != o.p; }
+  };
+  It begin() const { return {first}; }
+  It end() const { return {last}; }
+};
 
 // Reclaim pinned upload blocks whose copies have finished.
 lb_status reclaim_uploads(lb_server* s) {
@@ -258,6 +282,9 @@ lb_status upload_descriptors(lb_server* s) {
   int64_t tiles = 0;
   const int slot = s->desc_slot;
   STRY(s, hipEventSynchronize(s->desc_done[slot]));  // staging slot free again
+  const ActiveSizes sizes{s->active.data(), s->active.data() + n};
+  const int K = fused_levels(s->opt.storage);
+  s->shape = serve_shape(s->opt.storage, sizes, K, fused_strip_width(s->opt.storage), s->cus);
   for (int i = 0; i < n; ++i) {
     LatticeDesc d = describe(s, s->active[i]);
     d.tile_begin = tiles;
@@ -387,6 +414,8 @@ lb_status lb_server_create(const lb_server_options* o, lb_server** out) {
   s->base.a0 = 1.0 - th;
   s->base.a1 = 0.5 * th;
   s->base.rho0 = o->storage == LB_F64 ? 0.0 : o->rho0;
+
+  (void)hipDeviceGetAttribute(&s->cus, hipDeviceAttributeMultiprocessorCount, dev);
 
   DeviceScope ds(dev);
   auto bail = [&](lb_status st) {
@@ -528,8 +557,12 @@ lb_status lb_server_step(lb_server* s, int64_t n) {
       lb_status st = upload_descriptors(s);
       if (st != LB_OK) return st;
     }
-    STRY(s, launch_batched_fused(s->opt.equilibrium, s->opt.storage, s->d_desc, s->d_map,
-                                 s->tiles, s->T, s->compute));
+    if (s->shape.waves == 0)
+      STRY(s, launch_batched_fused(s->opt.equilibrium, s->opt.storage, s->d_desc, s->d_map,
+                                   s->tiles, s->T, s->compute));
+    else
+      STRY(s, launch_batched_block(s->opt.equilibrium, s->opt.storage, s->d_desc, s->d_map,
+                                   s->tiles, s->T, s->shape.waves, s->shape.rows, s->compute));
     s->T += 1;
     s->launches += 1;
     // retire lattices that have run their steps

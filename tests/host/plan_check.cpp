@@ -5,6 +5,7 @@
 // or the first broken one.
 #include <cstdio>
 #include <cstdlib>
+#include <vector>
 
 #include "plan.hpp"
 #include "plan3.hpp"
@@ -76,6 +77,20 @@ int main() {
           if ((s.ntx - 1) * (long long)s.tx >= nx || (s.nty - 1) * (long long)s.ty >= ny ||
               (s.nzc - 1) * (long long)s.zc >= nz)
             fail("empty march tile", st, nx, ny, nz);
+          ++plans;
+        }
+  // server launches: sets of one to many lattices
+  for (int st = 0; st < 4; ++st)
+    for (int count : {1, 3, 40, 300})
+      for (int nx : {1, 32, 65, 500, 1024})
+        for (int ny : {1, 33, 200, 1024}) {
+          const std::vector<LatticeSize> set(count, LatticeSize{nx, ny});
+          const int K = st == 0 ? 7 : 6;
+          const ServeShape s = serve_shape(st, set, K, 64 - 2 * K, 256);
+          if (s.waves == 0 ? s.strip_rows < 3
+                           : (s.waves > kBlockWaves || s.waves * s.rows - 2 * (K - 1) < 4 || st == 0 ||
+                              (s.rows != block_rows_small(st) && s.rows != block_rows_big(st))))
+            fail("server split", st, nx, ny, count);
           ++plans;
         }
   std::printf("plans %lld\n", plans);

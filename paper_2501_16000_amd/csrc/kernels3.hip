@@ -250,11 +250,8 @@ __device__ __forceinline__ void block_sum(double (&v)[kSums]) {
 
 template <int ST>
 __global__ __launch_bounds__(kThreads) void diag3_kernel(const typename Storage<ST>::T* __restrict__ src,
-                                                         const typename Storage<ST>::T* __restrict__ alt,
-                                                         const unsigned int* __restrict__ fmt,
                                                          double* __restrict__ partials, Geometry3 g,
                                                          Coef64 c, double theta) {
-  if (fmt && *fmt != 0) src = alt;  // see launch_expand3
   double acc[kSums] = {0, 0, 0, 0, 0, 0, 0};
   const int64_t stride = (int64_t)gridDim.x * kThreads;
   for (int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x; idx < g.cells; idx += stride) {
@@ -376,17 +373,20 @@ hipError_t launch_moments3(int st, const void* src, double* out, const Geometry3
   });
 }
 
-hipError_t launch_diagnostics3(int st, const void* src, const void* alt, const unsigned int* fmt,
-                               double* partials, double* out, const Geometry3& g, const Coef64& c, double theta_energy,
+hipError_t launch_diagnostics3_final(const double* partials, int n, double* out, hipStream_t s) {
+  diag3_final_kernel<<<1, kThreads, 0, s>>>(partials, n, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_diagnostics3(int st, const void* src, double* partials, double* out,
+                               const Geometry3& g, const Coef64& c, double theta_energy,
                                hipStream_t s) {
   return with_storage(st, [&](auto ST) {
     using T = typename Storage<ST.value>::T;
-    diag3_kernel<ST.value><<<kDiag3Blocks, kThreads, 0, s>>>(
-        static_cast<const T*>(src), static_cast<const T*>(alt), fmt, partials, g, c, theta_energy);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    diag3_final_kernel<<<1, kThreads, 0, s>>>(partials, kDiag3Blocks, out);
-    return hipGetLastError();
+    diag3_kernel<ST.value><<<kDiag3Blocks, kThreads, 0, s>>>(static_cast<const T*>(src), partials,
+                                                             g, c, theta_energy);
+    const hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : launch_diagnostics3_final(partials, kDiag3Blocks, out, s);
   });
 }
 

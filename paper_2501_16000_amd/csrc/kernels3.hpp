@@ -41,6 +41,11 @@ hipError_t launch_march3(int eq, int st, const void* src, void* dst, const unsig
 hipError_t launch_march3_moments(int eq, int st, const void* src, double* out,
                                  const unsigned int* fmt, const Geometry3& g, const Coef64& c,
                                  const MarchShape& s, hipStream_t q);
+// The seven sums of lb3_diagnostics by workgroup, s.ntx s.nty s.nzc of them, into
+// partials[][7].
+hipError_t launch_march3_sums(int eq, int st, const void* src, double* partials,
+                              const unsigned int* fmt, const Geometry3& g, const Coef64& c,
+                              double theta_energy, const MarchShape& s, hipStream_t q);
 // The populations of src into alt, if src holds ten numbers per node.
 hipError_t launch_expand3(int eq, int st, const void* src, void* alt, const unsigned int* fmt,
                           const Geometry3& g, const Coef64& c, hipStream_t s);
@@ -65,8 +70,10 @@ hipError_t launch_moments3(int st, const void* src, double* out, const Geometry3
 
 // The seven FP64 sums of lb3_diagnostics into out[7]; partials holds
 // kDiag3Blocks * 7 doubles.
-hipError_t launch_diagnostics3(int st, const void* src, const void* alt, const unsigned int* fmt,
-                               double* partials, double* out, const Geometry3& g, const Coef64& c, double theta_energy,
+hipError_t launch_diagnostics3(int st, const void* src, double* partials, double* out,
+                               const Geometry3& g, const Coef64& c, double theta_energy,
                                hipStream_t s);
+// Its second half: the sum of partials[n][7].
+hipError_t launch_diagnostics3_final(const double* partials, int n, double* out, hipStream_t s);
 
 }  // namespace oreg

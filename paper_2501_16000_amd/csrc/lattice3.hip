@@ -389,10 +389,19 @@ lb_status lb3_diagnostics(lb3_lattice* h, double out[7]) {
   DeviceScope ds(h->device);
   if (!ds.ok) return fail(h, LB_EDEVICE, "cannot select device %d", h->device);
   double* result = h->aux + kDiag3Blocks * 7;
-  HIP_TRY(h, expand(h));
-  HIP_TRY(h, launch_diagnostics3(h->opt.storage, h->buf[h->cur], h->buf[1 - h->cur],
-                                 h->fmt(h->cur), h->aux, result, h->geo, h->coef, h->coef.theta,
-                                 h->stream));
+  if (h->march) {
+    // The partial sums, one set per workgroup, go to the buffer that the next
+    // step overwrites: a workgroup has a node or more, of 27 elements.
+    double* partials = static_cast<double*>(h->buf[1 - h->cur]);
+    const int groups = h->shape.ntx * h->shape.nty * h->shape.nzc;
+    HIP_TRY(h, launch_march3_sums(h->opt.equilibrium, h->opt.storage, h->buf[h->cur], partials,
+                                  h->fmt(h->cur), h->geo, h->coef, h->coef.theta, h->shape,
+                                  h->stream));
+    HIP_TRY(h, launch_diagnostics3_final(partials, groups, result, h->stream));
+  } else {
+    HIP_TRY(h, launch_diagnostics3(h->opt.storage, h->buf[h->cur], h->aux, result, h->geo, h->coef,
+                                   h->coef.theta, h->stream));
+  }
   HIP_TRY(h, hipMemcpyAsync(out, result, 7 * sizeof(double), hipMemcpyDeviceToHost, h->stream));
   HIP_TRY(h, hipStreamSynchronize(h->stream));
   return LB_OK;

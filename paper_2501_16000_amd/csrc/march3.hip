@@ -24,6 +24,11 @@
 // phases of a plane, which share one workgroup per CU.  256^3, us per step,
 // population sweep / march: F64 1322 / 552, F32S 648 / 352; 128^3: 195 / 83,
 // 98 / 41.
+//
+// The same march reads rho and u (kMoments) and the sums of lb3_diagnostics
+// (kSums) in one pass.  A step and diagnostics, with the sums from
+// populations / written out for the purpose / formed here: 256^3 F64 1920 / 2099
+// / 1039 us, F32S 978 / 1174 / 706; 64^3 F64 57 / 71 / 57.
 #include <hip/hip_runtime.h>
 
 #include "dispatch.hpp"
@@ -33,7 +38,8 @@ namespace oreg {
 namespace {
 using namespace detail;
 
-enum { kStep = 0, kMoments = 1 };
+enum { kStep = 0, kMoments = 1, kSums = 2 };
+constexpr int kNSums = 7;
 
 // Cell (x, y, z) with one periodic wrap per axis.
 __device__ __forceinline__ int wrap1(int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); }
@@ -43,11 +49,11 @@ __global__ __launch_bounds__(kMarchThreads) void march3_kernel(const void* __res
                                                            void* __restrict__ dst,
                                                            const unsigned int* __restrict__ fmt_src,
                                                            unsigned int* __restrict__ fmt_dst,
-                                                           Geometry3 g, Coef64 c, MarchShape s) {
+                                                           Geometry3 g, Coef64 c, double theta, MarchShape s) {
   using S = Storage<ST>;
   using R = typename S::R;
   using T = typename S::T;
-  using A = typename std::conditional<MODE == kMoments, double, R>::type;  // type of the sums
+  using A = typename std::conditional<MODE == kStep, R, double>::type;  // type of the sums
   constexpr int NR = kMarchRegion;
   // Two LDS buffers where they fit save the barrier between a plane's reads
   // and the next plane's writes (64 x 8 tiles, 256^3: F32S 405 -> 399 us).
@@ -67,10 +73,7 @@ __global__ __launch_bounds__(kMarchThreads) void march3_kernel(const void* __res
   const bool out = tid < s.tx * s.ty && X0 + ox < g.nx && Y0 + oy < g.ny;
   const int64_t ocell = (int64_t)(Y0 + oy) * g.nx + (X0 + ox);
   const int64_t plane = (int64_t)g.nx * g.ny;
-  auto finish = [&](int z, const d3::PlaneSums<A>& m, const d3::PlaneSums<A>& o,
-                    const d3::PlaneSums<A>& p) {
-    A drho, j[3], M[6];
-    d3::combine(m, o, p, drho, j, M);
+  [[maybe_unused]] auto store = [&](int z, A drho, const A(&j)[3], const A(&M)[6]) {
     const int64_t cell = z * plane + ocell;
     if constexpr (MODE == kMoments) {
       double* const q = static_cast<double*>(dst);
@@ -78,7 +81,7 @@ __global__ __launch_bounds__(kMarchThreads) void march3_kernel(const void* __res
       q[cell] = rho;
 #pragma unroll
       for (int a = 0; a < 3; ++a) q[(a + 1) * g.cells + cell] = j[a] / rho;
-    } else {
+    } else if constexpr (MODE == kStep) {
       R v[d3::kParams];
       d3::reduce<S::shifted>(drho, j, M, k, v);
       R* const q = static_cast<R*>(dst) + cell;
@@ -86,17 +89,64 @@ __global__ __launch_bounds__(kMarchThreads) void march3_kernel(const void* __res
       for (int i = 0; i < d3::kParams; ++i) q[i * g.cells] = v[i];
     }
   };
+  [[maybe_unused]] double acc[kNSums] = {0, 0, 0, 0, 0, 0, 0};
+  // finite: whether the node's 27 populations are (kSums only).
+  auto finish = [&](int z, const d3::PlaneSums<A>& m, const d3::PlaneSums<A>& o,
+                    const d3::PlaneSums<A>& p, [[maybe_unused]] bool finite) {
+    A drho, j[3], M[6];
+    d3::combine(m, o, p, drho, j, M);
+    if constexpr (MODE == kSums) {
+      if (!finite) {
+        acc[6] += 1.0;
+        return;
+      }
+      const double rho = c.rho0 + drho;
+      const double ke = 0.5 * (j[0] * j[0] + j[1] * j[1] + j[2] * j[2]) / rho;
+      acc[0] += rho;
+      acc[1] += j[0];
+      acc[2] += j[1];
+      acc[3] += j[2];
+      acc[4] += ke;
+      acc[5] += 1.5 * rho * theta + ke;
+    } else {
+      store(z, drho, j, M);
+    }
+  };
+  // The workgroup's sums, in a fixed order, to dst[block].
+  [[maybe_unused]] auto write_sums = [&] {
+    __shared__ double part[kMarchThreads / 64][kNSums];
+#pragma unroll
+    for (int i = 0; i < kNSums; ++i) {
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) acc[i] += __shfl_down(acc[i], o, 64);
+      if ((tid & 63) == 0) part[tid >> 6][i] = acc[i];
+    }
+    __syncthreads();
+    if (tid < kNSums) {
+      double v = part[0][tid];
+      for (int w = 1; w < kMarchThreads / 64; ++w) v += part[w][tid];
+      static_cast<double*>(dst)[block * kNSums + tid] = v;
+    }
+  };
+  [[maybe_unused]] auto all_finite = [](const A (&a)[9]) {
+    bool f = true;
+    if constexpr (MODE == kSums) {
+#pragma unroll
+      for (int i = 0; i < 9; ++i) f = f && isfinite(a[i]);
+    }
+    return f;
+  };
   if (MODE == kStep && block == 0 && tid == 0) *fmt_dst = 1;
 
   if (*fmt_src == 0) {
     // Populations: every output node pulls its 27.
-    if (!out) return;
     const T* const f = static_cast<const T*>(src);
     const int x = X0 + ox, y = Y0 + oy;
     const int xs[3] = {wrap1(x + 1, g.nx), x, wrap1(x - 1, g.nx)};  // by c_x + 1
     const int ys[3] = {wrap1(y + 1, g.ny), y, wrap1(y - 1, g.ny)};
-    for (int z = z0; z < z1; ++z) {
+    for (int z = z0; out && z < z1; ++z) {
       d3::PlaneSums<A> sums[3];
+      bool finite = true;
 #pragma unroll
       for (int cz = 0; cz < 3; ++cz) {
         const int zs = wrap1(z + 1 - cz, g.nz);
@@ -105,9 +155,11 @@ __global__ __launch_bounds__(kMarchThreads) void march3_kernel(const void* __res
         for (int i = 0; i < 9; ++i)
           v[i] = (A)S::load(f[(9 * cz + i) * g.cells + zs * plane + (int64_t)ys[i / 3] * g.nx + xs[i % 3]]);
         sums[cz] = d3::plane_sums(v);
+        finite = finite && all_finite(v);
       }
-      finish(z, sums[0], sums[1], sums[2]);
+      finish(z, sums[0], sums[1], sums[2], finite);
     }
+    if constexpr (MODE == kSums) write_sums();
     return;
   }
 
@@ -132,6 +184,7 @@ __global__ __launch_bounds__(kMarchThreads) void march3_kernel(const void* __res
   for (int i = 0; i < d3::kParams; ++i) v[i] = R(0);
   fetch(z0 - 1);
   d3::PlaneSums<A> up1{}, up2{}, mid{};  // c_z = +1 of planes p - 1 and p - 2, c_z = 0 of p - 1
+  [[maybe_unused]] bool up1_finite = true, up2_finite = true, mid_finite = true;
   for (int p = z0 - 1; p <= z1; ++p) {
     R w[d3::kParams];
 #pragma unroll
@@ -145,25 +198,32 @@ __global__ __launch_bounds__(kMarchThreads) void march3_kernel(const void* __res
     }
     __syncthreads();
     if (out) {
-      auto group = [&](auto CZ) {
+      auto group = [&](auto CZ, bool& finite) {
         A a[9];
         unroll<0, 9>([&](auto I) {
           constexpr int cx = I.value % 3 - 1, cy = I.value / 3 - 1;
           a[I.value] = (A)S::load(lds[(9 * CZ.value + I.value) * NR + from - cy * rx - cx]);
         });
         const d3::PlaneSums<A> sums = d3::plane_sums(a);
+        finite = all_finite(a);
         __builtin_amdgcn_sched_barrier(0);
         return sums;
       };
-      if (p > z0) finish(p - 1, group(IC<0>{}), mid, up2);
+      if (p > z0) {
+        bool down_finite;
+        const d3::PlaneSums<A> down = group(IC<0>{}, down_finite);
+        finish(p - 1, down, mid, up2, down_finite && mid_finite && up2_finite);
+      }
       up2 = up1;
+      up2_finite = up1_finite;
       if (p < z1) {
-        mid = group(IC<1>{});
-        up1 = group(IC<2>{});
+        mid = group(IC<1>{}, mid_finite);
+        up1 = group(IC<2>{}, up1_finite);
       }
     }
     if (BUFS == 1 && p < z1) __syncthreads();
   }
+  if constexpr (MODE == kSums) write_sums();
 }
 
 // The populations of a buffer that holds ten numbers per node, into alt (left
@@ -189,13 +249,13 @@ __global__ __launch_bounds__(kThreads) void expand3_kernel(const void* __restric
 template <int MODE>
 hipError_t launch_march(int eq, int st, const void* src, void* dst, const unsigned int* fmt_src,
                         unsigned int* fmt_dst, const Geometry3& g, const Coef64& c,
-                        const MarchShape& s, hipStream_t q) {
+                        double theta, const MarchShape& s, hipStream_t q) {
   if (!march_shape_ok(s, g.nx, g.ny, g.nz)) return hipErrorInvalidValue;
   const unsigned int blocks = (unsigned int)((int64_t)s.ntx * s.nty * s.nzc);
   return with_eq(eq, [&](auto EQ) {
     auto go = [&](auto ST) {
       march3_kernel<EQ.value, ST.value, MODE>
-          <<<blocks, kMarchThreads, 0, q>>>(src, dst, fmt_src, fmt_dst, g, c, s);
+          <<<blocks, kMarchThreads, 0, q>>>(src, dst, fmt_src, fmt_dst, g, c, theta, s);
       return hipGetLastError();
     };
     if (st == LB_F64) return go(IC<LB_F64>{});
@@ -209,13 +269,19 @@ hipError_t launch_march(int eq, int st, const void* src, void* dst, const unsign
 hipError_t launch_march3(int eq, int st, const void* src, void* dst, const unsigned int* fmt_src,
                          unsigned int* fmt_dst, const Geometry3& g, const Coef64& c,
                          const MarchShape& s, hipStream_t q) {
-  return launch_march<kStep>(eq, st, src, dst, fmt_src, fmt_dst, g, c, s, q);
+  return launch_march<kStep>(eq, st, src, dst, fmt_src, fmt_dst, g, c, 0.0, s, q);
 }
 
 hipError_t launch_march3_moments(int eq, int st, const void* src, double* out,
                                  const unsigned int* fmt, const Geometry3& g, const Coef64& c,
                                  const MarchShape& s, hipStream_t q) {
-  return launch_march<kMoments>(eq, st, src, out, fmt, nullptr, g, c, s, q);
+  return launch_march<kMoments>(eq, st, src, out, fmt, nullptr, g, c, 0.0, s, q);
+}
+
+hipError_t launch_march3_sums(int eq, int st, const void* src, double* partials,
+                              const unsigned int* fmt, const Geometry3& g, const Coef64& c,
+                              double theta_energy, const MarchShape& s, hipStream_t q) {
+  return launch_march<kSums>(eq, st, src, partials, fmt, nullptr, g, c, theta_energy, s, q);
 }
 
 hipError_t launch_expand3(int eq, int st, const void* src, void* alt, const unsigned int* fmt,

@@ -35,14 +35,15 @@ inline bool march_shape_ok(const MarchShape& s, int nx, int ny, int nz) {
 // and a barrier per plane), so small boxes keep their populations: us per step,
 // populations : ten numbers, F64 32^3 5.6 : 7.1, 17 x 28 x 200 18.2 : 12.0,
 // 64^3 23.5 : 16.8, 256^3 1322 : 552; F32S 17 x 28 x 200 8.7 : 9.5, 64^3 12.5
-// : 11.8, 100 x 84 x 60 25.5 : 17.8, 256^3 648 : 352.  The 16-bit formats would
+// : 11.8 (and diagnostics then 32 : 38), 100 x 84 x 60 25.5 : 17.8, 256^3 648 :
+// 352.  The 16-bit formats would
 // store ten FP32 numbers (40 bytes) for 27 populations (54), and the march's
 // arithmetic then costs more than the bytes save (256^3 BF16S 376 : 417).
 // BGK keeps all 27 numbers of a node.
 inline bool march_worthwhile(int coll, int st, int64_t cells) {
   if (coll != LB_COLL_OREG) return false;
   if (st == LB_F64) return cells >= 60000;
-  if (st == LB_F32S) return cells >= 200000;
+  if (st == LB_F32S) return cells >= 300000;
   return false;
 }
 

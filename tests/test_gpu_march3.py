@@ -1,5 +1,5 @@
 """D3Q27 boxes stored as ten numbers per node (F64 from 60,000 nodes, F32S from
-200,000): every step equals, bit for bit, the same step from the populations,
+300,000): every step equals, bit for bit, the same step from the populations,
 which a checkpoint before each step forces; and FP64 equals the oracle.
 
 The checkpoint round trip is exact in both formats, and both paths form every
@@ -22,9 +22,9 @@ CASES = [
     (1, 250, 250, "f64", "guided"),     # flat in x
     (251, 250, 1, "f64", "poly2"),      # one plane: its own neighbour
     (2, 3, 10007, "f64", "guided"),     # a single tile, many chunks
-    (64, 64, 50, "f32s", "guided"),
-    (71, 53, 59, "f32s", "poly2"),
-    (500, 2, 203, "f32s", "guided"),
+    (64, 64, 80, "f32s", "guided"),
+    (71, 73, 59, "f32s", "poly2"),
+    (500, 2, 307, "f32s", "guided"),
 ]
 
 

@@ -78,16 +78,23 @@ __device__ __forceinline__ int xcd_block() {
 // the time, beyond that each step adds the 80 us of its collisions, so five to
 // seven steps cost the same per step (80 us; stored as populations, seven steps
 // took 655 us) and seven needs the fewest launches where these count (1024^2).
-// The FP32 formats are bound by their collisions at K = 6 (0.44 ms per launch
-// against 0.30 ms for two steps in F32S) and keep six.
-// NW: wavefronts per strip.  F32S shares one
-// 256-column strip per workgroup (measured 9 % faster than a strip per
-// wavefront: 12 % fewer instructions per node update against six workgroup
-// barriers per row step); in F64 the same layout measured 2 % slower, and
-// the 16-bit formats pre-shift their windows inside the wavefront.
-template <int ST> struct FusedLevels { static constexpr int K = 6, NW = 1; };
-template <> struct FusedLevels<LB_F64> { static constexpr int K = 7, NW = 1; };
-template <> struct FusedLevels<LB_F32S> { static constexpr int K = 6, NW = 4; };
+// The FP32 formats are bound by their collisions at K = 6 (F32S 4096^2: 0.33 ms
+// per launch) and keep six.
+// NW: wavefronts per strip.  The 32- and 16-bit formats share one 256-column
+// strip per workgroup, whose rows pass through LDS at every level: their
+// sweeps are bound by VALU issue, and the LDS reads replace the lane shifts
+// (F32S 116 -> 107 instructions per collision) while the halo is 2K of 256
+// instead of 64 columns.  us per step, a wavefront per strip with shifts in
+// the wavefront / two wavefronts / four / eight: 4096^2 F16S 57.2 / 54.0 /
+// 50.8 / 56.7, BF16S 59.7 / 57.5 / 54.9 / 60.3, 8192^2 polynomial F16S 263 /
+// 237 / 219 / 233; F32S (four, edges only through LDS: 58.0) 58.2 / 55.4 /
+// 61.5.  Fewer wavefronts have more halo, more wait longer at each barrier.
+// F64 has registers for two wavefronts per SIMD only, which the six or seven
+// barriers of a row stop too often: 2048^2 21.8 / 36.8 / 28.1, 4096^2 80.3 /
+// 84.1 / 77.5.
+template <int ST> struct FusedLevels {
+  static constexpr int K = ST == LB_F64 ? 7 : 6, NW = ST == LB_F64 ? 1 : 4;
+};
 
 // Fused launches of fewer than FusedLevels<ST>::K steps (lb_step's remainder)
 // are compiled for periodic OReg lattices, the configuration the benchmark

@@ -13,14 +13,15 @@ namespace {
 using namespace detail;
 
 // ------------------------------------------------ multi-step (fused) sweep --
-// K time steps per launch.  Each wavefront owns a strip of 64 columns (in
-// F32S each workgroup one of 256, see fused_strip) and marches down H output
-// rows; lane l holds column X0 - K + l.  The rows of
-// time level 0 come from memory; level k + 1 of row y is computed from the
-// last three rows of level k (a sliding window kept in registers), the x
-// neighbours arrive by one-lane shifts (DPP, or ds_bpermute for window rows
-// of the 16-bit formats).  Every level loses one column on
-// each side, so the 64 - 2K (256 - 2K) middle columns of level K are stored.  The rows
+// K time steps per launch.  A strip of 64 columns belongs to a wavefront (FP64,
+// and the server's strips), or one of 256 to a workgroup (NW in FusedLevels),
+// and is marched down H output rows; lane l holds column X0 - K + l.  The rows
+// of time level 0 come from memory; level k + 1 of row y is computed from the
+// last three rows of level k (a sliding window kept in registers).  The x
+// neighbours' populations arrive by one-lane shifts (DPP, or ds_bpermute for
+// window rows of the 16-bit formats) in a wavefront's strip and through LDS in
+// a workgroup's.  Every level loses one column on each side, so the 64 - 2K
+// (256 - 2K) middle columns of level K are stored.  The rows
 // needed above and below the strip's H rows (K on each side) are recomputed
 // by the neighbouring strips.  Between levels the populations are rounded
 // through the storage format, so the result equals K single-step sweeps bit
@@ -29,30 +30,7 @@ using namespace detail;
 // per trip) has no branches apart from the store predicate.  H is a runtime
 // multiple of 3 chosen per lattice (fused_rows).
 
-
-// The same shifts, with lane 0 (from_left_or) or lane 63 (from_right_or)
-// taking `e` instead: the value of the column beyond the wavefront's edge,
-// handed over by the neighbouring wavefront of the workgroup.
-__device__ __forceinline__ float from_left_or(float v, float e) {
-  return __int_as_float(
-      __builtin_amdgcn_update_dpp(__float_as_int(e), __float_as_int(v), 0x138, 0xF, 0xF, false));
-}
-__device__ __forceinline__ float from_right_or(float v, float e) {
-  return __int_as_float(
-      __builtin_amdgcn_update_dpp(__float_as_int(e), __float_as_int(v), 0x130, 0xF, 0xF, false));
-}
-__device__ __forceinline__ double from_left_or(double v, double e) {
-  return __hiloint2double(
-      __builtin_amdgcn_update_dpp(__double2hiint(e), __double2hiint(v), 0x138, 0xF, 0xF, false),
-      __builtin_amdgcn_update_dpp(__double2loint(e), __double2loint(v), 0x138, 0xF, 0xF, false));
-}
-__device__ __forceinline__ double from_right_or(double v, double e) {
-  return __hiloint2double(
-      __builtin_amdgcn_update_dpp(__double2hiint(e), __double2hiint(v), 0x130, 0xF, 0xF, false),
-      __builtin_amdgcn_update_dpp(__double2loint(e), __double2loint(v), 0x130, 0xF, 0xF, false));
-}
-
-// The same shifts through the LDS crossbar (ds_bpermute: no LDS memory, no
+// One-lane shifts (from_left, from_right in lanes.hpp) through the LDS crossbar (ds_bpermute: no LDS memory, no
 // VALU issue slot), for values that are needed a step after they are
 // shifted: the latency is hidden and the VALU keeps its slots for the
 // collision.  src_byte is 4 x the source lane (wrapped, so edge lanes read
@@ -125,10 +103,10 @@ constexpr int64_t kBufferFormBytes = 0x7fffffff;
 // One strip: K time steps over the rows Y0 .. Y0 + H - 1 of the columns
 // X0 .. X0 + 64 NW - 1 - 2 KS.  Lane l of wavefront w holds column
 // X0 - KS + 64 w + l; KS >= K is the strip's halo width, so strip columns
-// KS .. 64 NW - 1 - KS are stored.  NW = 1: one wavefront per strip.  NW = 4
-// (SHARE): the four wavefronts of a workgroup sweep one 256-column strip
-// together and hand each other the populations that cross their edges
-// through LDS, so only the workgroup's outer edges carry a halo.
+// KS .. 64 NW - 1 - KS are stored.  NW = 1: one wavefront per strip.  NW > 1
+// (SHARE): the NW wavefronts of a workgroup sweep one strip together, and every
+// lane takes its neighbours' populations from LDS: only the workgroup's outer
+// edges carry a halo, and no VALU instruction is spent on a lane shift.
 //
 // IN, OUT: what a buffer holds.  kPops: the nine populations.  kNums: the five
 // numbers of the OReg update (d2q9.hpp: Params), which the last level stores
@@ -142,7 +120,7 @@ struct NoVisit {
   template <typename R>
   __device__ void operator()(const R (&)[9], int) const {}
 };
-template <int K, int KS, int EQ, int COLL, int BC, int ST, bool SHARE = false, bool BUF = false,
+template <int K, int KS, int EQ, int COLL, int BC, int ST, int NW = 1, bool BUF = false,
           int IN = kPops, int OUT = kPops, class Visit = NoVisit>
 __device__ __forceinline__ void fused_strip(const typename Storage<ST>::T* __restrict__ src,
                                             typename Storage<ST>::T* __restrict__ dst, int nx,
@@ -152,18 +130,18 @@ __device__ __forceinline__ void fused_strip(const typename Storage<ST>::T* __res
   using S = Storage<ST>;
   using R = typename S::R;
   using Tt = typename S::T;
-  constexpr int NW = SHARE ? 4 : 1;
+  constexpr bool SHARE = NW > 1;
   const int J = H + 2 * K;  // rows of level 0 read (H is a multiple of 3)
   const int cs = 64 * wv + lane;  // column within the strip, halo included
   int col = (X0 - KS + cs) % nx;
   if (col < 0) col += nx;
   const bool store_lane = cs >= KS && cs < 64 * NW - KS && X0 - KS + cs < nx;
   const int left_byte = ((lane - 1) & 63) << 2, right_byte = ((lane + 1) & 63) << 2;
-  // Window shifts through ds_bpermute for the 16-bit formats (measured 16 %
-  // faster for F16S and 7 % for BF16S); F64 and F32S keep all shifts on DPP
-  // (no gain there).
-  constexpr bool PERM = ST == LB_F16S || ST == LB_BF16S;
-  static_assert(!(SHARE && PERM), "pre-shifted windows take their edge values in-wave");
+  // Window shifts of one wavefront's strip through ds_bpermute for the 16-bit
+  // formats (measured 16 % faster for F16S and 7 % for BF16S).  F64 shifts by
+  // DPP: with ds_bpermute 4096^2 takes 83.4 instead of 78.9 us per step, through
+  // LDS as with SHARE 86.9.
+  constexpr bool PERM = !SHARE && (ST == LB_F16S || ST == LB_BF16S);
   // A window population as stored (pre-shifted with PERM) and as pulled at
   // the gather (shifted there without PERM).
   auto enter = [&](R v, int src_byte) -> R {
@@ -171,11 +149,11 @@ __device__ __forceinline__ void fused_strip(const typename Storage<ST>::T* __res
     else return v;
   };
   auto pull_left = [&](R v) -> R {
-    if constexpr (PERM) return v;
+    if constexpr (SHARE || PERM) return v;
     else return from_left(v);
   };
   auto pull_right = [&](R v) -> R {
-    if constexpr (PERM) return v;
+    if constexpr (SHARE || PERM) return v;
     else return from_right(v);
   };
   const bool wall = BC == LB_BC_BOUNCEBACK && (col == 0 || col == nx - 1);
@@ -186,29 +164,32 @@ __device__ __forceinline__ void fused_strip(const typename Storage<ST>::T* __res
   // roles are compile-time constants and the window slides without register
   // moves.
   R Sl[K][3][6];
-  // Edge exchange (SHARE): edge[lv][q][e][w] holds pops 1, 5, 8, 3, 6, 7 of
-  // the row of level lv in ring slot q at the left (e = 0: lane 0) or right
-  // (e = 1: lane 63) edge of wavefront w.  Lane 0 of w pulls pops 1, 5, 8 from
-  // the right edge of w - 1, lane 63 pops 3, 6, 7 from the left edge of w + 1.
-  // A row is published when it arrives at its level; the barrier after each
-  // publication orders it before the other wavefronts' reads, and a slot is
-  // rewritten three rows later, after the barriers of the steps that read it.
-  __shared__ R edge[SHARE ? K : 1][3][2][4][6];
-  const bool at_edge = lane == 0 || lane == 63;
-  const int side = lane == 63 ? 1 : 0;
-  const int wl = (wv + 3) & 3, wr = (wv + 1) & 3;  // neighbours (wrapped ones feed halo lanes)
-  auto publish = [&](int lv, int q, const R(&v)[9]) {
+  // Exchange (SHARE): a row that arrives at a level goes through LDS, from
+  // which every lane takes its neighbours' populations; x.l: 1, 5, 8 of the
+  // column to the left, x.r: 3, 6, 7 of the one to the right.  Two exchanges in
+  // a row use different buffers, so one barrier each suffices: a wavefront that
+  // writes the buffer again has passed the barrier that the others reach after
+  // their reads.
+  struct Neighbours {
+    R l[3], r[3];
+  };
+  constexpr int XP = 64 * NW;  // plane of an exchange buffer
+  __shared__ R exchange[SHARE ? 3 * 6 * XP + 2 : 1];
+  auto pass = [&](int buffer, const R(&v)[9], Neighbours& x) {
     if constexpr (SHARE) {
-      if (at_edge) {
-        R* e = edge[lv][q][side][wv];
-        e[0] = v[1];
-        e[1] = v[5];
-        e[2] = v[8];
-        e[3] = v[3];
-        e[4] = v[6];
-        e[5] = v[7];
-      }
+      R* const e = exchange + 1 + buffer * 6 * XP + cs;
+      e[0] = v[1];
+      e[XP] = v[5];
+      e[2 * XP] = v[8];
+      e[3 * XP] = v[3];
+      e[4 * XP] = v[6];
+      e[5 * XP] = v[7];
       __syncthreads();
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        x.l[i] = e[i * XP - 1];
+        x.r[i] = e[(3 + i) * XP + 1];
+      }
     }
   };
   const PlaneIO<Tt, BUF> io(src, dst, P, nx);
@@ -263,7 +244,8 @@ __device__ __forceinline__ void fused_strip(const typename Storage<ST>::T* __res
     __asm__ volatile("" : "+v"(C[0]), "+v"(C[1]), "+v"(C[2]), "+v"(C[3]), "+v"(C[4]), "+v"(C[5]),
                      "+v"(C[6]), "+v"(C[7]), "+v"(C[8]));
     if constexpr (NP == K) store_row(Y0 + j - 1 - 2 * K);  // the previous step's output row
-    publish(0, q, C);
+    [[maybe_unused]] Neighbours x;
+    pass(q * K % 3, C, x);
     // Prefetch the next row of level 0.  The last step reloads its own row
     // (a cache hit) instead of skipping the load: an unconditional load
     // leaves nothing of the old buffer alive.
@@ -273,14 +255,14 @@ __device__ __forceinline__ void fused_strip(const typename Storage<ST>::T* __res
 #pragma unroll
     for (int lv = 0; lv < K; ++lv) {
       // Slot q held row j - 3 of the level, which is no longer read.  With
-      // PERM, pops 1, 3, 5 and 6 enter the window already shifted to the
-      // lane that pulls them (they are read one and two steps later).
+      // SHARE and PERM, pops 1, 3, 5 and 6 enter the window already shifted to
+      // the lane that pulls them (they are read one and two steps later).
       Sl[lv][q][0] = C[0];
-      Sl[lv][q][1] = enter(C[1], left_byte);
+      Sl[lv][q][1] = SHARE ? x.l[0] : enter(C[1], left_byte);
       Sl[lv][q][2] = C[2];
-      Sl[lv][q][3] = enter(C[3], right_byte);
-      Sl[lv][q][4] = enter(C[5], left_byte);
-      Sl[lv][q][5] = enter(C[6], right_byte);
+      Sl[lv][q][3] = SHARE ? x.r[0] : enter(C[3], right_byte);
+      Sl[lv][q][4] = SHARE ? x.l[1] : enter(C[5], left_byte);
+      Sl[lv][q][5] = SHARE ? x.r[1] : enter(C[6], right_byte);
       if (lv >= NP) break;  // no rows of level lv + 1 yet
       R N[9];
       const R(&A)[6] = Sl[lv][qa];  // row j - 2 (pops 2, 5, 6 used)
@@ -288,21 +270,12 @@ __device__ __forceinline__ void fused_strip(const typename Storage<ST>::T* __res
       N[0] = B[0];
       N[2] = A[2];
       N[4] = C[4];
-      if constexpr (SHARE) {
-        N[1] = from_left_or(B[1], edge[lv][qb][1][wl][0]);
-        N[5] = from_left_or(A[4], edge[lv][qa][1][wl][1]);
-        N[8] = from_left_or(C[8], edge[lv][q][1][wl][2]);
-        N[3] = from_right_or(B[3], edge[lv][qb][0][wr][3]);
-        N[6] = from_right_or(A[5], edge[lv][qa][0][wr][4]);
-        N[7] = from_right_or(C[7], edge[lv][q][0][wr][5]);
-      } else {
-        N[1] = pull_left(B[1]);
-        N[3] = pull_right(B[3]);
-        N[5] = pull_left(A[4]);
-        N[6] = pull_right(A[5]);
-        N[7] = from_right(C[7]);
-        N[8] = from_left(C[8]);
-      }
+      N[1] = pull_left(B[1]);
+      N[3] = pull_right(B[3]);
+      N[5] = pull_left(A[4]);
+      N[6] = pull_right(A[5]);
+      N[7] = SHARE ? x.r[2] : from_right(C[7]);
+      N[8] = SHARE ? x.l[2] : from_left(C[8]);
       if constexpr (OUT == kNums) {
         if (lv + 1 == K) {
           const Params<R> p = reduce<EQ>(node_moments<S::shifted, S::delta_u>(N, k), k);
@@ -340,9 +313,11 @@ __device__ __forceinline__ void fused_strip(const typename Storage<ST>::T* __res
         // loop and runs out of registers.
         __asm__ volatile("" : "+v"(C[0]), "+v"(C[1]), "+v"(C[2]), "+v"(C[3]), "+v"(C[4]),
                          "+v"(C[5]), "+v"(C[6]), "+v"(C[7]), "+v"(C[8]));
-        publish(lv + 1, q, C);
+        pass((q * K + lv + 1) % 3, C, x);
       }
     }
+    // The fill steps pass fewer rows, so the next step may use the same buffer.
+    if constexpr (SHARE && NP < K) __syncthreads();
   };
   // Pipeline fill: rows 0 .. 2K - 1, level lv + 1 starting at row 2 (lv + 1).
   unroll<0, 2 * K>([&](auto JJ) { one_row(JJ.value, IC<JJ.value % 3>{}, IC<JJ.value / 2>{}); });
@@ -370,29 +345,20 @@ __global__ __launch_bounds__(256) void fused_sweep_kernel(
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const Coeffs<typename Storage<ST>::R> k(c);
-  if constexpr (NW == 4) {
-    const int item = xcd_block();  // one work item per workgroup
-    if (item >= items) return;     // the whole workgroup leaves together
-    const int strip = item % strips, seg = item / strips;
-    fused_strip<K, K, EQ, COLL, BC, ST, true, BUF>(src, dst, g.nx, g.ny, g.plane, strip * W,
-                                                   seg * H, H, k, lane, wv);
+  const int item = NW == 1 ? xcd_block() * 4 + wv : xcd_block();
+  if (item >= items) return;  // whole wavefronts, with NW > 1 whole workgroups, leave together
+  const int strip = item % strips, seg = item / strips;
+  auto sweep = [&](auto IN, auto OUT) {
+    fused_strip<K, K, EQ, COLL, BC, ST, NW, BUF, IN.value, OUT.value>(
+        src, dst, g.nx, g.ny, g.plane, strip * W, seg * H, H, k, lane, NW == 1 ? 0 : wv);
+  };
+  if constexpr (NUMS) {
+    if (item == 0 && threadIdx.x == 0) *fmt_dst = 1;
+    // Uniform over the launch: the pipeline of the buffer's format.
+    if (*fmt_src != 0) sweep(IC<kNums>{}, IC<kNums>{});
+    else sweep(IC<kPops>{}, IC<kNums>{});
   } else {
-    const int wave = xcd_block() * 4 + wv;
-    if (wave >= items) return;  // whole wavefronts leave together
-    const int strip = wave % strips, seg = wave / strips;
-    if constexpr (NUMS) {
-      if (wave == 0 && lane == 0) *fmt_dst = 1;
-      // Uniform over the launch: the pipeline of the buffer's format.
-      if (*fmt_src != 0)
-        fused_strip<K, K, EQ, COLL, BC, ST, false, BUF, kNums, kNums>(
-            src, dst, g.nx, g.ny, g.plane, strip * W, seg * H, H, k, lane);
-      else
-        fused_strip<K, K, EQ, COLL, BC, ST, false, BUF, kPops, kNums>(
-            src, dst, g.nx, g.ny, g.plane, strip * W, seg * H, H, k, lane);
-    } else {
-      fused_strip<K, K, EQ, COLL, BC, ST, false, BUF>(src, dst, g.nx, g.ny, g.plane, strip * W,
-                                                      seg * H, H, k, lane);
-    }
+    sweep(IC<kPops>{}, IC<kPops>{});
   }
 }
 
@@ -418,7 +384,7 @@ hipError_t fused_launch_st(int eq, int coll, int bc, const void* src, void* dst,
           const int strips = (g.nx + W - 1) / W;
           const int segs = (g.ny + rows - 1) / rows;
           const int items = strips * segs;
-          const unsigned int nblocks = (unsigned int)((items + 4 / NW - 1) / (4 / NW));
+          const unsigned int nblocks = (unsigned int)(NW == 1 ? (items + 3) / 4 : items);
           if constexpr (buf_config) {
             if (buf) {
               fused_sweep_kernel<L.value, EQ.value, CO.value, BC.value, ST, true, nums>

@@ -535,14 +535,20 @@ double fused_cost(int st, int nx, int ny, int H, const FusedShape& sh, int K) {
   const int64_t w = (items + sh.simds - 1) / sh.simds;
   const int64_t resident = w < sh.waves_per_simd ? w : sh.waves_per_simd;
   const double work = K * (double)(H + 2 * K) - K * (K + 1) + 2 * K;
-  return (double)w / (1.0 + 0.08 * (double)(resident - 1)) * work;
+  // Throughput of a SIMD against that of one wavefront on it.
+  const double gain = NW == 1        ? 1.0 + 0.08 * (double)(resident - 1)
+                      : resident < 3 ? 0.5 + 0.5 * (double)resident
+                                     : 1.75;
+  return (double)w / gain * work;
 }
 
 int fused_rows(int st, int nx, int ny, const FusedShape& sh, int levels) {
   if (sh.simds <= 0 || sh.waves_per_simd <= 0) return kFusedRowsDefault;
-  // One wavefront per SIMD already runs the pipeline near the SIMD's issue
-  // limit (measured: a second one adds 6-11 %), so a launch takes about w
-  // wavefront-times, w = ceil(work items / SIMDs), and one wavefront's time
+  // One wavefront per SIMD already runs a wavefront's own strip near the SIMD's
+  // issue limit (measured: a second one adds 6-11 %); wavefronts that share a
+  // strip wait for each other, and a second workgroup adds 52 %, a third and a
+  // fourth 75 % (F32S, 4096^2 in 411, 138, 105 and 69 rows: 139, 64.5, 65.3 and
+  // 61.1 us per step).  A launch takes about w wavefront-times by that rate, w = ceil(work items / SIMDs), and one wavefront's time
   // follows its row collisions, K (H + 2K) - K (K + 1), plus a start-up of
   // about 2K.  H (a multiple of 3) minimises the modelled launch time.
   const int hmax = ny < 3 * 1024 ? (ny + 2) / 3 * 3 : 3 * 1024;

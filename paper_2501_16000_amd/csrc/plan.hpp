@@ -222,15 +222,16 @@ inline StepPlan best_block(int st, int nx, int ny, int L, int cus) {
 // wave cost more.  Measured, us per step, block : strip, one lattice at a time
 // (and with three lattices on three streams):
 //   F64   512^2 2.84 : 3.48 (2.46 : 2.78), 600^2 4.38 : 4.21 (3.70 : 3.07);
-//   F32S  2500^2 26.7 : 27.6 (25.1 : 25.5), 3000^2 37.9 : 37.1 (34.6 : 34.1),
-//         4096^2 65.0 : 62.5 (63.8 : 58.0);
-//   F16S  2048^2 18.6 : 19.0 (17.0 : 16.6), 2500^2 25.2 : 26.0 (24.4 : 23.0),
-//         4096^2 64.9 : 61.1 (63.4 : 57.3).
+//   F32S  1500^2 12.7 : 13.5 (9.5 : 9.7), 2048^2 18.9 : 19.8 (16.7 : 15.9),
+//         2236^2 22.8 : 21.8 (19.8 : 18.7), 2500^2 28.1 : 26.8 (24.7 : 22.9);
+//   F16S  1500^2 10.5 : 13.1 (8.7 : 8.9), 2048^2 18.6 : 20.5 (16.6 : 14.7),
+//         2236^2 21.7 : 22.7 (19.4 : 17.6), 4096^2 64.9 : 56.5 (63.4 : 48.5);
+//   BF16S 2048^2 19.0 : 22.6 (16.9 : 15.9), 2236^2 22.3 : 24.3 (19.8 : 18.8).
 // F64 changes over early: its blocks leave two wavefronts per SIMD, which
 // cannot hide their loads.
 inline bool plan_strips(int st, int nx, int ny) {
   const int64_t nodes = (int64_t)nx * ny;
-  const int64_t from = st == LB_F64 ? 300000 : st == LB_F32S ? 7500000 : 5000000;
+  const int64_t from = st == LB_F64 ? 300000 : 4500000;
   return nodes >= from && std::min(nx, ny) > 36;
 }
 

@@ -27,10 +27,10 @@ __device__ __forceinline__ void visit_strip(const double* __restrict__ src, cons
                                             bool numbers, int lane, Visit&& visit) {
   const int strip = wave % strips, seg = wave / strips;
   if (numbers)
-    fused_strip<1, 1, EQ, LB_COLL_OREG, LB_BC_PERIODIC, LB_F64, false, false, kNums, kVisit>(
+    fused_strip<1, 1, EQ, LB_COLL_OREG, LB_BC_PERIODIC, LB_F64, 1, false, kNums, kVisit>(
         src, nullptr, g.nx, g.ny, g.plane, strip * kWidth, seg * H, H, k, lane, 0, visit);
   else
-    fused_strip<1, 1, EQ, LB_COLL_OREG, LB_BC_PERIODIC, LB_F64, false, false, kPops, kVisit>(
+    fused_strip<1, 1, EQ, LB_COLL_OREG, LB_BC_PERIODIC, LB_F64, 1, false, kPops, kVisit>(
         src, nullptr, g.nx, g.ny, g.plane, strip * kWidth, seg * H, H, k, lane, 0, visit);
 }
 

@@ -103,6 +103,37 @@ def test_steps_from_numbers_equal_steps_from_populations(nx, ny, steps, eq):
                                    rtol=1e-11, atol=1e-9)
 
 
+SHARED_CASES = [
+    # nx, ny, steps, storage, equilibrium, collision, boundary: 32- and 16-bit
+    # lattices whose strips of 256 columns are shared by a workgroup
+    (4881, 931, 11, "f32s", "guided", "oreg", "periodic"),   # last strip one column wide, 6 + 5 steps
+    (37, 121700, 9, "f16s", "guided", "oreg", "periodic"),   # narrower than a strip
+    (121700, 37, 14, "bf16s", "poly2", "oreg", "periodic"),
+    (2200, 2101, 8, "f16s", "poly2", "bgk", "periodic"),
+    (2001, 2300, 13, "bf16s", "guided", "oreg", "bounceback"),
+    (2300, 2003, 6, "f32s", "poly2", "bgk", "bounceback"),
+]
+
+
+@pytest.mark.parametrize("nx,ny,steps,storage,eq,coll,bc", SHARED_CASES)
+def test_shared_strips_equal_single_steps(nx, ny, steps, storage, eq, coll, bc):
+    """The same update on the same values, so equality is exact."""
+    import torch
+    from paper_2501_16000_amd import oreg
+    print(f"[shared strips] {nx}x{ny} {steps} {storage} {eq} {coll} {bc}", flush=True)
+    u = [0.03 * torch.from_numpy(workloads.noise((ny, nx), nx + k)).cuda() for k in (0, 1)]
+    with oreg.Lattice(nx, ny, 0.7, equilibrium=eq, storage=storage, collision=coll,
+                      boundary_x=bc) as A, \
+            oreg.Lattice(nx, ny, 0.7, equilibrium=eq, storage=storage, collision=coll,
+                         boundary_x=bc) as B:
+        for L in (A, B):
+            L.init(1.0 + u[0], u[0], u[1])
+        A.step(steps)
+        for _ in range(steps):
+            B.step(1)
+        np.testing.assert_array_equal(A.populations(), B.populations())
+
+
 def test_captured_steps_follow_a_new_init():
     """A captured graph of steps replayed on a state that was initialized after
     the capture: the kernels read the buffers' format on the device."""

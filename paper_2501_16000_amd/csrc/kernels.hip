@@ -185,22 +185,37 @@ __global__ __launch_bounds__(kThreads) void init_kernel(const double* __restrict
 }
 
 // ------------------------------------------------------- import / export --
+// Planes i0 .. i0 + count - 1 of pre-collision populations.  sum carries the sum
+// of a node's populations from one launch to the next, in plane order; bad
+// counts nodes with a value that is not finite (in each launch) and, in the
+// last launch, nodes whose sum is not positive.
 template <int ST>
-__global__ __launch_bounds__(kThreads) void import_kernel(int i, const double* __restrict__ fin,
+__global__ __launch_bounds__(kThreads) void import_kernel(int i0, int count,
+                                                          const double* __restrict__ fin,
                                                           typename Storage<ST>::T* __restrict__ dst,
-                                                          Geometry g, Coef64 c,
-                                                          unsigned int* __restrict__ fmt) {
+                                                          double* __restrict__ sum,
+                                                          unsigned int* __restrict__ bad, Geometry g,
+                                                          Coef64 c) {
   using S = Storage<ST>;
   using R = typename S::R;
   const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (idx >= g.plane) return;
-  if (fmt && idx == 0) *fmt = 0;  // the buffer holds populations
   const int y = (int)(idx / g.nx);
   const int x = (int)(idx - (int64_t)y * g.nx);
-  const int cx = cx_of(i), cy = cy_of(i);
-  const double w = S::shifted ? shift64(cx, cy, c) : 0.0;
-  const int xd = wrap_sub(x, cx, g.nx), yd = wrap_sub(y, cy, g.ny);
-  dst[i * g.plane + (int64_t)yd * g.nx + xd] = S::store((R)(fin[idx] - w));
+  double rho = i0 == 0 ? 0.0 : sum[idx];
+  bool ok = true;
+  for (int p = 0; p < count; ++p) {
+    const int i = i0 + p, cx = cx_of(i), cy = cy_of(i);
+    const double v = fin[p * g.plane + idx];
+    ok = ok && isfinite(v);
+    rho += v;
+    const double w = S::shifted ? shift64(cx, cy, c) : 0.0;
+    const int xd = wrap_sub(x, cx, g.nx), yd = wrap_sub(y, cy, g.ny);
+    dst[i * g.plane + (int64_t)yd * g.nx + xd] = S::store((R)(v - w));
+  }
+  if (i0 + count < 9) sum[idx] = rho;
+  else ok = ok && rho > 0.0;
+  if (!ok) atomicAdd(bad, 1u);
 }
 
 // The readers below take a lattice's equilibrium (NEQ) where its buffers may
@@ -229,7 +244,7 @@ __device__ __forceinline__ typename Storage<ST>::T emitted(const typename Storag
 }
 
 template <int ST, int NEQ>
-__global__ __launch_bounds__(kThreads) void export_kernel(int i,
+__global__ __launch_bounds__(kThreads) void export_kernel(int i0,
                                                           const typename Storage<ST>::T* __restrict__ src,
                                                           double* __restrict__ fout, Geometry g,
                                                           Coef64 c,
@@ -239,6 +254,8 @@ __global__ __launch_bounds__(kThreads) void export_kernel(int i,
   if (idx >= g.plane) return;
   const int y = (int)(idx / g.nx);
   const int x = (int)(idx - (int64_t)y * g.nx);
+  const int i = i0 + blockIdx.y;
+  fout += blockIdx.y * g.plane;
   const int cx = cx_of(i), cy = cy_of(i);
   const double w = S::shifted ? shift64(cx, cy, c) : 0.0;
   const int xs = wrap_sub(x, cx, g.nx), ys = wrap_sub(y, cy, g.ny);
@@ -577,12 +594,13 @@ hipError_t launch_init(int eq, int st, const double* rho, const double* ux, cons
   });
 }
 
-hipError_t launch_import_plane(int st, int i, const double* fin, void* dst, const Geometry& g,
-                               const Coef64& c, unsigned int* fmt, hipStream_t s) {
+hipError_t launch_import_planes(int st, int i, int count, const double* fin, void* dst, double* sum,
+                                unsigned int* bad, const Geometry& g, const Coef64& c,
+                                hipStream_t s) {
   return with_storage(st, [&](auto ST) {
     using T = typename Storage<ST.value>::T;
-    import_kernel<ST.value><<<blocks_for(g.plane), kThreads, 0, s>>>(i, fin, static_cast<T*>(dst),
-                                                                      g, c, fmt);
+    import_kernel<ST.value><<<blocks_for(g.plane), kThreads, 0, s>>>(
+        i, count, fin, static_cast<T*>(dst), sum, bad, g, c);
     return hipGetLastError();
   });
 }
@@ -595,12 +613,12 @@ hipError_t with_form(int eq, int st, const unsigned int* fmt, F&& f) {
   return with_eq(eq, [&](auto EQ) { return f(IC<LB_F64>{}, EQ); });
 }
 
-hipError_t launch_export_plane(int eq, int st, int i, const void* src, double* fout,
-                               const Geometry& g, const Coef64& c, const unsigned int* fmt,
-                               hipStream_t s) {
+hipError_t launch_export_planes(int eq, int st, int i, int count, const void* src, double* fout,
+                                const Geometry& g, const Coef64& c, const unsigned int* fmt,
+                                hipStream_t s) {
   return with_form(eq, st, fmt, [&](auto ST, auto NEQ) {
     using T = typename Storage<ST.value>::T;
-    export_kernel<ST.value, NEQ.value><<<blocks_for(g.plane), kThreads, 0, s>>>(
+    export_kernel<ST.value, NEQ.value><<<dim3(blocks_for(g.plane), count), kThreads, 0, s>>>(
         i, static_cast<const T*>(src), fout, g, c, fmt);
     return hipGetLastError();
   });

@@ -90,14 +90,18 @@ hipError_t launch_init(int eq, int st, const double* rho, const double* ux, cons
                        void* dst, const Geometry& g, const Coef64& c, unsigned int* bad,
                        unsigned int* fmt, hipStream_t s);
 
-// Plane i of g from plane i of pre-collision FP64 populations (device).
-hipError_t launch_import_plane(int st, int i, const double* fin, void* dst, const Geometry& g,
-                               const Coef64& c, unsigned int* fmt, hipStream_t s);
+// Planes i .. i + count - 1 of g from fin[count][ny][nx], pre-collision FP64
+// populations (device).  Called in plane order for all nine, it counts invalid
+// nodes (a value that is not finite, or a sum that is not positive) into *bad;
+// sum[ny][nx] is its workspace.
+hipError_t launch_import_planes(int st, int i, int count, const double* fin, void* dst, double* sum,
+                                unsigned int* bad, const Geometry& g, const Coef64& c,
+                                hipStream_t s);
 
-// Plane i of the pre-collision FP64 populations (device) from g.
-hipError_t launch_export_plane(int eq, int st, int i, const void* src, double* fout,
-                               const Geometry& g, const Coef64& c, const unsigned int* fmt,
-                               hipStream_t s);
+// Planes i .. i + count - 1 of the pre-collision FP64 populations (device) from g.
+hipError_t launch_export_planes(int eq, int st, int i, int count, const void* src, double* fout,
+                                const Geometry& g, const Coef64& c, const unsigned int* fmt,
+                                hipStream_t s);
 
 // rho, ux, uy of the pre-collision state into out[3][ny][nx] (device FP64).
 hipError_t launch_moments(int eq, int st, const void* src, double* out, const Geometry& g,

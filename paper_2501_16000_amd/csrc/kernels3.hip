@@ -166,18 +166,24 @@ __global__ __launch_bounds__(kThreads) void init3_kernel(const double* __restric
   unroll<0, 27>([&](auto I) { dst[I.value * g.cells + upwind(n, I.value, g)] = S::store((R)deq[I.value]); });
 }
 
+// Plane i of pre-collision populations.  sum carries the sum of a node's
+// populations from one plane to the next; bad counts values that are not finite
+// and, with the last plane, nodes whose sum is not positive.
 template <int ST>
 __global__ __launch_bounds__(kThreads) void import3_kernel(int i, const double* __restrict__ fin,
                                                            typename Storage<ST>::T* __restrict__ dst,
-                                                           Geometry3 g, Coef64 c,
-                                                           unsigned int* __restrict__ fmt) {
+                                                           double* __restrict__ sum,
+                                                           unsigned int* __restrict__ bad,
+                                                           Geometry3 g, Coef64 c) {
   using S = Storage<ST>;
   using R = typename S::R;
   const int64_t idx = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (idx >= g.cells) return;
-  if (fmt && idx == 0) *fmt = 0;  // the buffer holds populations
+  const double v = fin[idx], rho = (i == 0 ? 0.0 : sum[idx]) + v;
+  if (i < 26) sum[idx] = rho;
+  if (!isfinite(v) || (i == 26 && !(rho > 0.0))) atomicAdd(bad, 1u);
   const double w = S::shifted ? d3::shift64(d3::cx(i), d3::cy(i), d3::cz(i), c) : 0.0;
-  dst[i * g.cells + upwind(node_of(idx, g), i, g)] = S::store((R)(fin[idx] - w));
+  dst[i * g.cells + upwind(node_of(idx, g), i, g)] = S::store((R)(v - w));
 }
 
 template <int ST>
@@ -343,11 +349,12 @@ hipError_t launch_init3(int eq, int st, const double* rho, const double* ux, con
   });
 }
 
-hipError_t launch_import3(int st, int i, const double* fin, void* dst, const Geometry3& g,
-                          const Coef64& c, unsigned int* fmt, hipStream_t s) {
+hipError_t launch_import3(int st, int i, const double* fin, void* dst, double* sum,
+                          unsigned int* bad, const Geometry3& g, const Coef64& c, hipStream_t s) {
   return with_storage(st, [&](auto ST) {
     using T = typename Storage<ST.value>::T;
-    import3_kernel<ST.value><<<blocks_for(g.cells), kThreads, 0, s>>>(i, fin, static_cast<T*>(dst), g, c, fmt);
+    import3_kernel<ST.value><<<blocks_for(g.cells), kThreads, 0, s>>>(i, fin, static_cast<T*>(dst),
+                                                                      sum, bad, g, c);
     return hipGetLastError();
   });
 }

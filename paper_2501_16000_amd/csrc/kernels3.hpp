@@ -57,9 +57,12 @@ hipError_t launch_init3(int eq, int st, const double* rho, const double* ux, con
                         const double* uz, void* dst, const Geometry3& g, const Coef64& c,
                         unsigned int* bad, unsigned int* fmt, hipStream_t s);
 
-// Plane i of pre-collision FP64 populations in/out of a buffer.
-hipError_t launch_import3(int st, int i, const double* fin, void* dst, const Geometry3& g,
-                          const Coef64& c, unsigned int* fmt, hipStream_t s);
+// Plane i of pre-collision FP64 populations into a buffer.  Called in plane order
+// for all 27, it counts invalid populations and nodes (a value that is not
+// finite, a sum that is not positive) into *bad; sum[cells] is its workspace.
+hipError_t launch_import3(int st, int i, const double* fin, void* dst, double* sum,
+                          unsigned int* bad, const Geometry3& g, const Coef64& c, hipStream_t s);
+// Plane i of them from a buffer.
 hipError_t launch_export3(int st, int i, const void* src, const void* alt,
                           const unsigned int* fmt, double* fout, const Geometry3& g,
                           const Coef64& c, hipStream_t s);

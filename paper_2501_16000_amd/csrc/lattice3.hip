@@ -10,6 +10,7 @@
 #include <string>
 
 #include "kernels3.hpp"
+#include "staging.hpp"
 #include "oreg3.h"
 
 using namespace oreg;
@@ -33,6 +34,7 @@ struct lb3_lattice {
   MarchShape shape{};
   // Format flag of buffer b (null where every buffer holds populations).
   unsigned int* fmt(int b) const { return march ? counter + 1 + b : nullptr; }
+  PinnedPieces pieces;                // for copies from and to the caller's arrays
   std::string err;
 };
 
@@ -257,7 +259,8 @@ lb_status lb3_init(lb3_lattice* h, const double* rho, const double* ux, const do
   lb_status st = ready(h, (rho && ux && uy && uz) ? rho : nullptr, false);
   if (st != LB_OK) return st;
   const int64_t n = h->geo.cells;
-  for (int64_t i = 0; i < n; ++i) {
+  const double* const u[3] = {ux, uy, uz};
+  for (int64_t i = first_suspect_fields(rho, u, 3, n); i < n; ++i) {
     if (!is_finite(rho[i]) || !is_finite(ux[i]) || !is_finite(uy[i]) || !is_finite(uz[i]) ||
         !(rho[i] > 0.0))
       return fail(h, LB_EINVAL, "node %lld has a non-finite field or rho <= 0", (long long)i);
@@ -326,9 +329,10 @@ lb_status lb3_moments(lb3_lattice* h, double* out) {
   if (!ds.ok) return fail(h, LB_EDEVICE, "cannot select device %d", h->device);
   if ((st = ensure_tmp(h)) != LB_OK) return st;
   HIP_TRY(h, enqueue_moments(h, h->tmp));
-  HIP_TRY(h, hipMemcpyAsync(out, h->tmp, 4 * (size_t)h->geo.cells * sizeof(double),
-                            hipMemcpyDeviceToHost, h->stream));
-  HIP_TRY(h, hipStreamSynchronize(h->stream));
+  const size_t bytes = 4 * (size_t)h->geo.cells * sizeof(double);
+  HostTransfer copy(h->pieces, h->stream, bytes);
+  HIP_TRY(h, copy.to_host(out, h->tmp, bytes));
+  HIP_TRY(h, copy.finish());
   return LB_OK;
 }
 
@@ -340,16 +344,16 @@ lb_status lb3_populations(lb3_lattice* h, double* out) {
   if ((st = ensure_tmp(h)) != LB_OK) return st;
   const int64_t n = h->geo.cells;
   HIP_TRY(h, expand(h));
+  HostTransfer copy(h->pieces, h->stream, 27 * (size_t)n * sizeof(double));
   for (int i = 0; i < 27; ++i) {
     // Four staging planes, used in turn, so a plane is not overwritten
     // before its copy has been issued (same stream, so ordered).
     double* stage = h->tmp + (i % 4) * n;
     HIP_TRY(h, launch_export3(h->opt.storage, i, h->buf[h->cur], h->buf[1 - h->cur],
                               h->fmt(h->cur), stage, h->geo, h->coef, h->stream));
-    HIP_TRY(h, hipMemcpyAsync(out + (size_t)i * n, stage, (size_t)n * sizeof(double),
-                              hipMemcpyDeviceToHost, h->stream));
+    HIP_TRY(h, copy.to_host(out + (size_t)i * n, stage, (size_t)n * sizeof(double)));
   }
-  HIP_TRY(h, hipStreamSynchronize(h->stream));
+  HIP_TRY(h, copy.finish());
   return LB_OK;
 }
 
@@ -357,26 +361,41 @@ lb_status lb3_set_populations(lb3_lattice* h, const double* in) {
   lb_status st = ready(h, in, false);
   if (st != LB_OK) return st;
   const int64_t n = h->geo.cells;
-  for (int64_t c = 0; c < n; ++c) {
-    double rho = 0.0;
-    for (int i = 0; i < 27; ++i) {
-      const double v = in[(size_t)i * n + c];
-      if (!is_finite(v))
-        return fail(h, LB_EINVAL, "population %d of node %lld is not finite", i, (long long)c);
-      rho += v;
-    }
-    if (!(rho > 0.0)) return fail(h, LB_EINVAL, "node %lld has sum_i f_i <= 0", (long long)c);
-  }
   DeviceScope ds(h->device);
   if (!ds.ok) return fail(h, LB_EDEVICE, "cannot select device %d", h->device);
   if ((st = ensure_tmp(h)) != LB_OK) return st;
+  // Checked on the device on their way into the buffer that the next step
+  // overwrites; they take the place of the state once they are known to be valid.
+  void* const next = h->buf[1 - h->cur];
+  double* const sum = h->tmp + 3 * n;
+  HIP_TRY(h, hipMemsetAsync(h->counter, 0, sizeof(unsigned int), h->stream));
   for (int i = 0; i < 27; ++i) {
-    double* stage = h->tmp + (i % 4) * n;
+    double* const stage = h->tmp + (i % 3) * n;
     HIP_TRY(h, hipMemcpyAsync(stage, in + (size_t)i * n, (size_t)n * sizeof(double),
                               hipMemcpyHostToDevice, h->stream));
-    HIP_TRY(h, launch_import3(h->opt.storage, i, stage, h->buf[h->cur], h->geo, h->coef,
-                              h->fmt(h->cur), h->stream));
+    HIP_TRY(h, launch_import3(h->opt.storage, i, stage, next, sum, h->counter, h->geo, h->coef,
+                              h->stream));
   }
+  unsigned int bad = 0;
+  HIP_TRY(h, hipMemcpyAsync(&bad, h->counter, sizeof bad, hipMemcpyDeviceToHost, h->stream));
+  HIP_TRY(h, hipStreamSynchronize(h->stream));
+  if (bad) {
+    for (int64_t c = 0; c < n; ++c) {
+      double rho = 0.0;
+      for (int i = 0; i < 27; ++i) {
+        const double v = in[(size_t)i * n + c];
+        if (!is_finite(v))
+          return fail(h, LB_EINVAL, "population %d of node %lld is not finite", i, (long long)c);
+        rho += v;
+      }
+      if (!(rho > 0.0)) return fail(h, LB_EINVAL, "node %lld has sum_i f_i <= 0", (long long)c);
+    }
+    return fail(h, LB_EINVAL, "%u invalid population(s)", bad);
+  }
+  HIP_TRY(h, hipMemcpyAsync(h->buf[h->cur], next, 27 * (size_t)n * h->elem, hipMemcpyDeviceToDevice,
+                            h->stream));
+  if (h->fmt(h->cur))  // the buffer holds populations
+    HIP_TRY(h, hipMemsetAsync(h->fmt(h->cur), 0, sizeof(unsigned int), h->stream));
   HIP_TRY(h, hipStreamSynchronize(h->stream));
   h->initialized = true;
   h->t = 0;
@@ -435,6 +454,7 @@ lb_status lb3_destroy(lb3_lattice* h) {
     for (int b = 0; b < 2; ++b)
       if (h->buf[b]) (void)hipFree(h->buf[b]);
     if (h->tmp) (void)hipFree(h->tmp);
+    h->pieces.release();
     if (h->aux) (void)hipFree(h->aux);
     if (h->counter) (void)hipFree(h->counter);
     if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);

@@ -68,39 +68,72 @@ template <int ST> struct Sweep3Waves { static constexpr int N = 4; };
 template <> struct Sweep3Waves<LB_F64> { static constexpr int N = 8; };
 template <> struct Sweep3Waves<LB_F32S> { static constexpr int N = 16; };
 
-template <int EQ, int COLL, int ST>
+// PACKED: a wavefront takes 64 consecutive nodes of the box instead of a segment
+// of one x-row (sweep3_packed); mx, my: division by nx and ny (magic).
+template <int EQ, int COLL, int ST, bool PACKED>
 __global__ __launch_bounds__(64 * Sweep3Waves<ST>::N) void sweep3_kernel(
     const typename Storage<ST>::T* __restrict__ src, typename Storage<ST>::T* __restrict__ dst,
-    Geometry3 g, Coef64 c, unsigned int nseg, unsigned int tasks) {
+    Geometry3 g, Coef64 c, unsigned int nseg, unsigned int tasks, unsigned int mx,
+    unsigned int my) {
   using S = Storage<ST>;
   using R = typename S::R;
   using T = typename S::T;
   const unsigned int task = blockIdx.x * (blockDim.x >> 6) +
                             (unsigned int)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (task >= tasks) return;
-  const unsigned int row = task / nseg;
-  const unsigned int seg = task - row * nseg;
-  const int y = (int)(row % (unsigned int)g.ny);
-  const int z = (int)(row / (unsigned int)g.ny);
-  const int x = (int)(seg * 64u) + (int)(threadIdx.x & 63);
-  const bool active = x < g.nx;
-  const int xc = active ? x : g.nx - 1;  // lanes past the row end load a valid node
-  const int xm = xc == 0 ? g.nx - 1 : xc - 1;
-  const int xp = xc == g.nx - 1 ? 0 : xc + 1;
   const int64_t P = g.cells;
-  // Start of the source row of g_i(x - c_i) for each (c_y, c_z).
-  int64_t rows[3][3];
-#pragma unroll
-  for (int b = 0; b < 3; ++b)
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-      rows[a][b] = ((int64_t)wrap_sub(z, b - 1, g.nz) * g.ny + wrap_sub(y, a - 1, g.ny)) * g.nx;
   T raw[27];
-  unroll<0, 27>([&](auto I) {
-    constexpr int vx = d3::cx(I.value), vy = d3::cy(I.value), vz = d3::cz(I.value);
-    const T* p = src + I.value * P + rows[vy + 1][vz + 1];
-    raw[I.value] = p[vx == 0 ? xc : (vx > 0 ? xm : xp)];
-  });
+  bool active;
+  T* q;  // the node in plane 0 of dst
+  if constexpr (PACKED) {
+    const unsigned int nx = g.nx, ny = g.ny;
+    const unsigned int first = task * 64u, row0 = first / nx, z0 = row0 / ny;
+    // Node of this lane; past the end of the box, the box's first nodes.
+    const unsigned int t = first - row0 * nx + (threadIdx.x & 63), dy = __umulhi(t, mx);
+    const unsigned int u = row0 - z0 * ny + dy, dz = __umulhi(u, my);
+    const int x = (int)(t - dy * nx), y = (int)(u - dz * ny);
+    int z = (int)(z0 + dz);
+    active = z < g.nz;
+    if (!active) z = 0;
+    // Byte offsets within a plane, 32 bits each: the plane's start is uniform.
+    const unsigned int E = sizeof(T), row_bytes = nx * E, layer_bytes = ny * row_bytes;
+    unsigned int xs[3], ys[3], zs[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+      xs[a] = (unsigned int)wrap_sub(x, a - 1, g.nx) * E;
+      ys[a] = (unsigned int)wrap_sub(y, a - 1, g.ny) * row_bytes;
+      zs[a] = (unsigned int)wrap_sub(z, a - 1, g.nz) * layer_bytes;
+    }
+    unroll<0, 27>([&](auto I) {
+      constexpr int vx = d3::cx(I.value), vy = d3::cy(I.value), vz = d3::cz(I.value);
+      const char* const p = reinterpret_cast<const char*>(src + I.value * P);
+      raw[I.value] = *reinterpret_cast<const T*>(p + (zs[vz + 1] + ys[vy + 1] + xs[vx + 1]));
+    });
+    q = reinterpret_cast<T*>(reinterpret_cast<char*>(dst) + (zs[1] + ys[1] + xs[1]));
+  } else {
+    const unsigned int row = task / nseg;
+    const unsigned int seg = task - row * nseg;
+    const int y = (int)(row % (unsigned int)g.ny);
+    const int z = (int)(row / (unsigned int)g.ny);
+    const int x = (int)(seg * 64u) + (int)(threadIdx.x & 63);
+    active = x < g.nx;
+    const int xc = active ? x : g.nx - 1;  // lanes past the row end load a valid node
+    const int xm = xc == 0 ? g.nx - 1 : xc - 1;
+    const int xp = xc == g.nx - 1 ? 0 : xc + 1;
+    // Start of the source row of g_i(x - c_i) for each (c_y, c_z).
+    int64_t rows[3][3];
+#pragma unroll
+    for (int b = 0; b < 3; ++b)
+#pragma unroll
+      for (int a = 0; a < 3; ++a)
+        rows[a][b] = ((int64_t)wrap_sub(z, b - 1, g.nz) * g.ny + wrap_sub(y, a - 1, g.ny)) * g.nx;
+    unroll<0, 27>([&](auto I) {
+      constexpr int vx = d3::cx(I.value), vy = d3::cy(I.value), vz = d3::cz(I.value);
+      const T* p = src + I.value * P + rows[vy + 1][vz + 1];
+      raw[I.value] = p[vx == 0 ? xc : (vx > 0 ? xm : xp)];
+    });
+    q = dst + rows[1][1] + x;
+  }
   // All 27 loads before the first use: without the ordering point the compiler
   // paired every F16S load with its conversion and waited for each in turn.
   __builtin_amdgcn_sched_barrier(0);
@@ -110,7 +143,6 @@ __global__ __launch_bounds__(64 * Sweep3Waves<ST>::N) void sweep3_kernel(
   const Coeffs<R> k(c);
   d3::collide<EQ, COLL, S::shifted>(f, k);
   if (active) {
-    T* q = dst + rows[1][1] + x;
     unroll<0, 27>([&](auto I) { __builtin_nontemporal_store(S::store(f[I.value]), q + I.value * P); });
   }
 }
@@ -318,19 +350,40 @@ int64_t sweep3_tasks(const Geometry3& g) {
   return (int64_t)((g.nx + 63) / 64) * g.ny * g.nz;
 }
 
+// Whether the sweep packs 64 consecutive nodes of the box into a wavefront.  A
+// segment of a row leaves 64 ceil(nx / 64) - nx lanes idle and starts its lines
+// unaligned; packed nodes cost 33 more instructions (of 577 in the 16-bit
+// formats) for their addresses.  us per step of three boxes in flight, rows :
+// packed: BF16S 17 x 28 x 200 6.8 : 3.6, 60^3 6.2 : 5.2, 100 x 84 x 60 15.0 :
+// 11.6, 200 x 180 x 160 220 : 124, and with whole segments 128^3 43.7 : 44.5; F64
+// BGK 150^3 357 : 290.  Boxes of too few wavefronts run faster spread over more
+// of them (32^3 F64 3.5 : 4.0, 48 x 40 x 30 5.8 : 5.2).  Addresses are 32-bit byte
+// offsets, and __umulhi by ceil(2^32 / n) divides exactly below 2^32 / n.
+bool sweep3_packed(const Geometry3& g, int elem) {
+  return g.nx > 1 && g.ny > 1 && g.ny < 65000 && g.cells >= 45000 &&
+         g.cells * elem < 4294967296LL &&
+         1.04 * (double)g.cells < 64.0 * (double)sweep3_tasks(g);
+}
+
 hipError_t launch_sweep3(int eq, int coll, int st, const void* src, void* dst, const Geometry3& g,
                          const Coef64& c, hipStream_t s) {
   const unsigned int nseg = (unsigned int)((g.nx + 63) / 64);
-  const unsigned int tasks = (unsigned int)sweep3_tasks(g);
+  auto magic = [](int n) { return (unsigned int)((4294967296ULL + n - 1) / (unsigned int)n); };
   return with_storage(st, [&](auto ST) {
     using T = typename Storage<ST.value>::T;
     const unsigned int W = sweep3_waves(g, Sweep3Waves<ST.value>::N);
+    const bool packed = sweep3_packed(g, (int)sizeof(T));
+    const unsigned int tasks = (unsigned int)(packed ? (g.cells + 63) / 64 : sweep3_tasks(g));
     const unsigned int nblocks = (tasks + W - 1) / W;
     return with_eq(eq, [&](auto EQ) {
       return with_coll(coll, [&](auto CO) {
-        sweep3_kernel<EQ.value, CO.value, ST.value><<<nblocks, 64 * W, 0, s>>>(
-            static_cast<const T*>(src), static_cast<T*>(dst), g, c, nseg, tasks);
-        return hipGetLastError();
+        auto go = [&](auto PACKED) {
+          sweep3_kernel<EQ.value, CO.value, ST.value, PACKED.value><<<nblocks, 64 * W, 0, s>>>(
+              static_cast<const T*>(src), static_cast<T*>(dst), g, c, nseg, tasks, magic(g.nx),
+              magic(g.ny));
+          return hipGetLastError();
+        };
+        return packed ? go(IC<1>{}) : go(IC<0>{});
       });
     });
   });

@@ -63,6 +63,36 @@ def test_steps_equal_steps_from_checkpoints(nx, ny, nz, storage, eq):
         assert float(np.max(np.abs(fa - ref) / np.abs(ref))) <= 1e-12
 
 
+PACKED_CASES = [
+    # nx, ny, nz, copies along x: wavefronts of 64 consecutive nodes, against a
+    # box of whole 64-node segments that repeats the first one
+    (17, 28, 101, 64),
+    (2, 3, 8001, 32),     # many rows and layers in one wavefront, a last one not full
+    (65, 2, 401, 64),
+    (200, 5, 47, 8),
+]
+
+
+@pytest.mark.parametrize("nx,ny,nz,copies", PACKED_CASES)
+@pytest.mark.parametrize("storage,eq,coll", [("bf16s", "guided", "oreg"), ("f16s", "poly2", "oreg"),
+                                             ("f64", "poly2", "bgk"), ("f32s", "guided", "bgk"),
+                                             ("f32s", "guided", "oreg")])
+def test_packed_nodes_equal_rows(nx, ny, nz, copies, storage, eq, coll):
+    """The same update on the same values, so equality is exact."""
+    from paper_2501_16000_amd import oreg3
+    print(f"[packed] {nx}x{ny}x{nz} {storage} {eq} {coll}", flush=True)
+    f = [workloads.noise((nz, ny, nx), nx + k, 0.03) for k in range(4)]
+    f[0] = 1.0 + f[0]
+    with oreg3.Lattice3(nx, ny, nz, 0.7, equilibrium=eq, storage=storage, collision=coll) as A, \
+            oreg3.Lattice3(nx * copies, ny, nz, 0.7, equilibrium=eq, storage=storage,
+                           collision=coll) as B:
+        A.init(*f)
+        B.init(*[np.tile(v, (1, 1, copies)) for v in f])
+        for L in (A, B):
+            L.step(3)
+        np.testing.assert_array_equal(np.tile(A.moments(), (1, 1, 1, copies)), B.moments())
+
+
 def test_captured_steps_follow_a_new_init():
     """A captured graph of steps replayed on a state that was initialized after
     the capture: the kernels read the buffers' format on the device."""

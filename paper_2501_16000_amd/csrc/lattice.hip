@@ -360,11 +360,30 @@ lb_status lb_step(lb_lattice* h, int64_t n) {
     h->t += L;
     left -= L;
   };
+  // One launch of L steps by the tile or block sweep, if its plan has one.
+  auto planned = [&](int L) {
+    const StepPlan& p = step_plan(h, L);
+    if (p.us < 0 || p.kind == StepKind::sweep) return hipErrorNotSupported;
+    const hipError_t e =
+        p.kind == StepKind::tile
+            ? launch_tile_sweep(h->opt.equilibrium, h->opt.collision, h->opt.boundary_x,
+                                h->opt.storage, h->buf[h->cur], h->buf[1 - h->cur], h->geo, h->coef,
+                                p.tile, L, h->stream)
+            : launch_block_sweep(h->opt.equilibrium, h->opt.collision, h->opt.boundary_x,
+                                 h->opt.storage, h->buf[h->cur], h->buf[1 - h->cur], h->geo, h->coef,
+                                 p.block, L, h->stream);
+    if (e == hipSuccess) done(L);
+    return e;
+  };
   if (h->strips && (h->numbers || h->opt.fuse_steps != 1)) {
     // Strip launches advance K steps each.  A remainder runs as one shorter
-    // launch where that is compiled (periodic OReg: it reads and writes the
-    // state once, where single steps would do so per step), otherwise, and for
-    // a single step of a lattice stored as populations, one step per launch.
+    // launch where that is compiled (periodic OReg), otherwise as block launches,
+    // which read and write the state once where single steps would do so per
+    // step (4096^2, us for 2 .. 6 steps, single steps / blocks: F64 BGK 870, 1298,
+    // 1730, 2162, 2596 / 573, 581, 606, 718, 814; F32S BGK, 2 .. 5: 394, 591, 785,
+    // 979 / 318, 302, 303, 303; F16S BGK, 2 .. 4: 225, 336, 446 / 167, 199, 237).
+    // A single step of a lattice stored as populations runs by the single-step
+    // sweep.
     const int64_t K = h->opt.fuse_steps == 1 ? 1 : fused_levels(h->opt.storage);
     while (left > 0) {
       const int L = (int)std::min<int64_t>(K, left);
@@ -375,6 +394,11 @@ lb_status lb_step(lb_lattice* h, int64_t n) {
                                     h->fmt(1 - h->cur), h->stream));
       done(L);
     }
+    for (int L = (int)std::min<int64_t>(left, kPlanLevels); L >= 2 && left < K; --L) {
+      if (L > left) continue;
+      const hipError_t e = planned(L);
+      if (e != hipErrorNotSupported) HIP_TRY(h, e);
+    }
   } else if (h->opt.fuse_steps != 1 && h->best.us >= 0) {
     // Tile and block launches: the steps in as few launches as the best plan
     // needs, spread evenly over them.
@@ -382,19 +406,9 @@ lb_status lb_step(lb_lattice* h, int64_t n) {
     for (; launches > 0 && left >= 2; --launches) {
       const int L = (int)((left + launches - 1) / launches);
       if (L < 2) break;
-      const StepPlan& p = step_plan(h, L);
-      if (p.kind == StepKind::tile) {
-        HIP_TRY(h, launch_tile_sweep(h->opt.equilibrium, h->opt.collision, h->opt.boundary_x,
-                                     h->opt.storage, h->buf[h->cur], h->buf[1 - h->cur], h->geo,
-                                     h->coef, p.tile, L, h->stream));
-      } else if (p.kind == StepKind::block) {
-        HIP_TRY(h, launch_block_sweep(h->opt.equilibrium, h->opt.collision, h->opt.boundary_x,
-                                      h->opt.storage, h->buf[h->cur], h->buf[1 - h->cur], h->geo,
-                                      h->coef, p.block, L, h->stream));
-      } else {
-        break;
-      }
-      done(L);
+      const hipError_t e = planned(L);
+      if (e == hipErrorNotSupported) break;
+      HIP_TRY(h, e);
     }
   }
   while (left > 0) {

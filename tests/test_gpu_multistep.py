@@ -105,13 +105,20 @@ def test_steps_from_numbers_equal_steps_from_populations(nx, ny, steps, eq):
 
 SHARED_CASES = [
     # nx, ny, steps, storage, equilibrium, collision, boundary: 32- and 16-bit
-    # lattices whose strips of 256 columns are shared by a workgroup
+    # lattices whose strips of 256 columns are shared by a workgroup; and
+    # remainders that run as block launches, in every storage
     (4881, 931, 11, "f32s", "guided", "oreg", "periodic"),   # last strip one column wide, 6 + 5 steps
     (37, 121700, 9, "f16s", "guided", "oreg", "periodic"),   # narrower than a strip
     (121700, 37, 14, "bf16s", "poly2", "oreg", "periodic"),
     (2200, 2101, 8, "f16s", "poly2", "bgk", "periodic"),
     (2001, 2300, 13, "bf16s", "guided", "oreg", "bounceback"),
     (2300, 2003, 6, "f32s", "poly2", "bgk", "bounceback"),
+    (2300, 2003, 5, "f32s", "guided", "bgk", "periodic"),
+    (2200, 2101, 11, "f16s", "guided", "bgk", "periodic"),   # 6 + 4 + 1 steps
+    (701, 613, 12, "f64", "guided", "bgk", "periodic"),      # 7 + 5 steps
+    (640, 601, 6, "f64", "poly2", "oreg", "bounceback"),
+    (40, 8000, 9, "f64", "guided", "bgk", "bounceback"),
+    (8000, 40, 4, "f64", "poly2", "bgk", "periodic"),
 ]
 
 

@@ -77,7 +77,7 @@ __device__ __forceinline__ int xcd_block() {
 // 331, 401, 476 and 559 us: up to four steps the strips' memory traffic sets
 // the time, beyond that each step adds the 80 us of its collisions, so five to
 // seven steps cost the same per step (80 us; stored as populations, seven steps
-// took 655 us) and seven needs the fewest launches where these count (1024^2).
+// took 655 us); lb_step takes fewer than seven where that is faster.
 // The FP32 formats are bound by their collisions at K = 6 (F32S 4096^2: 0.33 ms
 // per launch) and keep six.
 // NW: wavefronts per strip.  The 32- and 16-bit formats share one 256-column

@@ -357,12 +357,13 @@ int64_t sweep3_tasks(const Geometry3& g) {
 // packed: BF16S 17 x 28 x 200 6.8 : 3.6, 60^3 6.2 : 5.2, 100 x 84 x 60 15.0 :
 // 11.6, 200 x 180 x 160 220 : 124, and with whole segments 128^3 43.7 : 44.5; F64
 // BGK 150^3 357 : 290.  Boxes of too few wavefronts run faster spread over more
-// of them (32^3 F64 3.5 : 4.0, 48 x 40 x 30 5.8 : 5.2).  Addresses are 32-bit byte
+// of them (32^3 F64 3.5 : 4.0, 48 x 40 x 30 5.8 : 5.2; 169 x 20 x 16, 12 % idle,
+// one step and moments 10.6 : 10.8).  Addresses are 32-bit byte
 // offsets, and __umulhi by ceil(2^32 / n) divides exactly below 2^32 / n.
 bool sweep3_packed(const Geometry3& g, int elem) {
   return g.nx > 1 && g.ny > 1 && g.ny < 65000 && g.cells >= 45000 &&
          g.cells * elem < 4294967296LL &&
-         1.04 * (double)g.cells < 64.0 * (double)sweep3_tasks(g);
+         (g.cells < 100000 ? 1.25 : 1.04) * (double)g.cells < 64.0 * (double)sweep3_tasks(g);
 }
 
 hipError_t launch_sweep3(int eq, int coll, int st, const void* src, void* dst, const Geometry3& g,

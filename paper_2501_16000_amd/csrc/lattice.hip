@@ -360,10 +360,11 @@ lb_status lb_step(lb_lattice* h, int64_t n) {
     h->t += L;
     left -= L;
   };
-  // One launch of L steps by the tile or block sweep, if its plan has one.
+  // Whether one launch advances L steps by the tile or block sweep (or L = 1),
+  // and that launch.
+  auto has_plan = [&](int L) { return L == 1 || step_plan(h, L).kind != StepKind::sweep; };
   auto planned = [&](int L) {
     const StepPlan& p = step_plan(h, L);
-    if (p.us < 0 || p.kind == StepKind::sweep) return hipErrorNotSupported;
     const hipError_t e =
         p.kind == StepKind::tile
             ? launch_tile_sweep(h->opt.equilibrium, h->opt.collision, h->opt.boundary_x,
@@ -375,40 +376,64 @@ lb_status lb_step(lb_lattice* h, int64_t n) {
     if (e == hipSuccess) done(L);
     return e;
   };
-  if (h->strips && (h->numbers || h->opt.fuse_steps != 1)) {
-    // Strip launches advance K steps each.  A remainder runs as one shorter
-    // launch where that is compiled (periodic OReg), otherwise as block launches,
-    // which read and write the state once where single steps would do so per
-    // step (4096^2, us for 2 .. 6 steps, single steps / blocks: F64 BGK 870, 1298,
-    // 1730, 2162, 2596 / 573, 581, 606, 718, 814; F32S BGK, 2 .. 5: 394, 591, 785,
-    // 979 / 318, 302, 303, 303; F16S BGK, 2 .. 4: 225, 336, 446 / 167, 199, 237).
-    // A single step of a lattice stored as populations runs by the single-step
-    // sweep.
-    const int64_t K = h->opt.fuse_steps == 1 ? 1 : fused_levels(h->opt.storage);
-    while (left > 0) {
-      const int L = (int)std::min<int64_t>(K, left);
-      if (!fused_levels_available(h->opt.collision, h->opt.boundary_x, h->opt.storage, L)) break;
-      HIP_TRY(h, launch_fused_sweep(h->opt.equilibrium, h->opt.collision, h->opt.boundary_x,
-                                    h->opt.storage, h->buf[h->cur], h->buf[1 - h->cur], h->geo,
-                                    h->coef, h->fused_rows[L], L, h->fmt(h->cur),
-                                    h->fmt(1 - h->cur), h->stream));
-      done(L);
+  auto strip = [&](int L) {
+    const hipError_t e = launch_fused_sweep(
+        h->opt.equilibrium, h->opt.collision, h->opt.boundary_x, h->opt.storage, h->buf[h->cur],
+        h->buf[1 - h->cur], h->geo, h->coef, h->fused_rows[L], L, h->fmt(h->cur),
+        h->fmt(1 - h->cur), h->stream);
+    if (e == hipSuccess) done(L);
+    return e;
+  };
+  const int levels = fused_levels(h->opt.storage);
+  auto has_strip = [&](int L) {
+    return fused_levels_available(h->opt.collision, h->opt.boundary_x, h->opt.storage, L);
+  };
+  const bool swap = swaps_buffers(
+      n, h->opt.fuse_steps == 2 || (h->opt.fuse_steps == 0 && h->geo.plane >= kFusedFrom), levels,
+      has_strip(2));
+  if (h->strips && (h->numbers || h->opt.fuse_steps != 1) && has_strip(2)) {
+    // Strip launches of any length (periodic OReg).  Lattices stored as numbers
+    // take the steps evenly: launches of one to four steps cost the same at 4096^2
+    // (a launch of seven and one of one step 876 us, two of four 662), and below
+    // 4.5 M nodes five steps have the best share of halo and pipeline fill (us per
+    // step of seven / six / five / four steps, one lattice: 700^2 5.2 / 5.1 / 4.6 /
+    // 4.6, 1024^2 7.9 / 7.3 / 7.3 / 7.3, 2048^2 23.7 / 23.7 / 23.2 / 24.7; 4096^2
+    // 83.9 / 83.7 / 86.8 / 90.8).  The others take as many full launches as they
+    // can; a single step of theirs runs by the single-step sweep.
+    const int64_t K = h->opt.fuse_steps == 1 ? 1 : levels;
+    const int64_t most = K > 5 && h->numbers && h->geo.plane < 4500000 ? 5 : K;
+    const int64_t least = (n + K - 1) / K;
+    int64_t launches = launches_for(n, least == 1 ? 1 : (n + most - 1) / most, swap);
+    const bool full = !h->numbers && launches == least;
+    for (; launches > 0; --launches) {
+      const int L = (int)(full ? std::min(K, left) : (left + launches - 1) / launches);
+      if (!has_strip(L)) break;
+      HIP_TRY(h, strip(L));
     }
-    for (int L = (int)std::min<int64_t>(left, kPlanLevels); L >= 2 && left < K; --L) {
-      if (L > left) continue;
-      const hipError_t e = planned(L);
-      if (e != hipErrorNotSupported) HIP_TRY(h, e);
+  } else if (h->strips && h->opt.fuse_steps != 1) {
+    // Strip launches of K steps only.  The remainder runs as block launches, which
+    // read and write the state once where single steps would do so per step
+    // (4096^2, us for 2 .. 6 steps, single steps / one block launch: F64 BGK 870,
+    // 1298, 1730, 2162, 2596 / 573, 581, 606, 718, 814; F32S BGK, 2 .. 5: 394, 591,
+    // 785, 979 / 318, 302, 303, 303; F16S BGK, 2 .. 4: 225, 336, 446 / 167, 199,
+    // 237), spread over the fewest that end in the right buffer.
+    const bool swap_rest = swap != (((n / levels) & 1) != 0);
+    while (left >= levels) HIP_TRY(h, strip(levels));
+    int64_t launches = 1;
+    for (; launches < left; ++launches) {
+      const int L = (int)((left + launches - 1) / launches);
+      if (((launches & 1) != 0) == swap_rest && has_plan(L) && has_plan((int)(left / launches)))
+        break;
     }
+    for (; left > launches; --launches) HIP_TRY(h, planned((int)((left + launches - 1) / launches)));
   } else if (h->opt.fuse_steps != 1 && h->best.us >= 0) {
     // Tile and block launches: the steps in as few launches as the best plan
     // needs, spread evenly over them.
-    int64_t launches = (n + h->best.levels - 1) / h->best.levels;
-    for (; launches > 0 && left >= 2; --launches) {
+    int64_t launches = launches_for(n, (n + h->best.levels - 1) / h->best.levels, swap);
+    for (; left > launches; --launches) {
       const int L = (int)((left + launches - 1) / launches);
-      if (L < 2) break;
-      const hipError_t e = planned(L);
-      if (e == hipErrorNotSupported) break;
-      HIP_TRY(h, e);
+      if (!has_plan(L)) break;
+      HIP_TRY(h, planned(L));
     }
   }
   while (left > 0) {

@@ -111,7 +111,10 @@ inline double tile_us(int st, const TileShape& t, int L, int cus) {
 }
 
 inline double block_us(int st, const BlockShape& b, int L, int cus) {
-  const BlockFit& f = kBlockFit[st];
+  BlockFit f = kBlockFit[st];
+  // BF16S takes its figures from F16S; its six rows measured slower against its
+  // four (62 x 2909: 3.0 us per step in six rows, 2.65 in four, modelled equal).
+  if (st == LB_BF16S && b.rows == 6) f.c *= 1.05, f.c1 *= 1.05;
   const int tiles = b.tx * b.ty;
   const int fit = std::max(1, 4 * block_waves_per_simd(st, b.rows) / b.waves);
   const int need = (tiles + cus - 1) / cus, conc = std::min(fit, need);
@@ -281,6 +284,23 @@ inline StepPlan plan_best(int st, int nx, int ny, int cus) {
     if (p.us >= 0 && (best.us < 0 || p.us * best.levels < best.us * L)) best = p;
   }
   return best;
+}
+
+// Whether a call of n steps leaves the state in the other buffer.  A captured
+// call is replayed on the buffers it was captured with, so programs replay calls
+// that return to their buffer, and which calls do must not depend on the plan:
+// as many launches as strips of K steps would take from 48^2 nodes up (`fused`;
+// a remainder in one launch where `remainder` says so, else in single steps),
+// one per step below, to the parity.
+inline bool swaps_buffers(int64_t n, bool fused, int K, bool remainder) {
+  const int64_t rest = n % K;
+  return ((!fused ? n : n / K + (remainder ? rest > 0 : rest)) & 1) != 0;
+}
+constexpr int64_t kFusedFrom = 48 * 48;
+
+// At least m launches for n steps, as many as end in the right buffer.
+inline int64_t launches_for(int64_t n, int64_t m, bool swap) {
+  return ((m & 1) != 0) == swap ? m : m < n ? m + 1 : m - 1;
 }
 
 // Server launches (serve.hip) advance every resident lattice up to K steps, so

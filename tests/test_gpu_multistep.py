@@ -165,3 +165,56 @@ def test_captured_steps_follow_a_new_init():
                 torch.cuda.synchronize()
                 B.step(14)
                 np.testing.assert_array_equal(A.populations(), B.populations(), err_msg=str(k))
+
+
+REPLAY_CASES = [
+    # nx, ny, storage, collision, boundary, steps: calls that return to the buffer
+    # they started from: two launches of 7 (FP64) or 6 steps from 48^2 nodes up, a
+    # remainder counted once (periodic OReg) or per step, and single steps below
+    (32, 32, "f64", "oreg", "periodic", 50),
+    (800, 1, "f64", "oreg", "bounceback", 90),
+    (128, 128, "f64", "oreg", "periodic", 14),
+    (128, 128, "f64", "oreg", "periodic", 22),
+    (300, 200, "f32s", "bgk", "periodic", 12),
+    (300, 200, "f32s", "oreg", "bounceback", 29),   # 4 x 6 + 5 steps: nine launches
+    (300, 200, "f32s", "oreg", "bounceback", 28),
+    (777, 523, "f16s", "oreg", "periodic", 24),
+    (700, 600, "f64", "oreg", "periodic", 28),
+    (700, 600, "f64", "bgk", "periodic", 16),
+    (700, 600, "f64", "bgk", "periodic", 10),
+    (2200, 2101, "bf16s", "oreg", "periodic", 24),
+    (2200, 2101, "bf16s", "bgk", "periodic", 11),   # 6 + 5 steps: six launches
+]
+
+
+@pytest.mark.parametrize("nx,ny,storage,coll,bc,steps", REPLAY_CASES)
+def test_captured_calls_replay(nx, ny, storage, coll, bc, steps):
+    """Which calls can be replayed (those of an even number of launches by the
+    rule above) does not depend on the plan; every replay equals the eager call."""
+    import torch
+    from paper_2501_16000_amd import oreg
+    print(f"[replay] {nx}x{ny} {storage} {coll} {bc} {steps}", flush=True)
+    K = 7 if storage == "f64" else 6
+    rest = steps % K if coll == "bgk" or bc == "bounceback" else (steps % K > 0)
+    launches = steps if nx * ny < 2304 else steps // K + rest
+    stream = torch.cuda.Stream()
+    rho = np.ones((ny, nx))
+    u = [0.03 * workloads.noise((ny, nx), nx + k) for k in (0, 1)]
+    opts = dict(storage=storage, collision=coll, boundary_x=bc, stream=stream)
+    with torch.cuda.stream(stream), oreg.Lattice(nx, ny, 0.7, **opts) as A, \
+            oreg.Lattice(nx, ny, 0.7, **opts) as B:
+        for L in (A, B):
+            L.init(rho, *u)
+            L.step(2)
+            L.sync()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            A.step(steps)
+            if launches % 2:
+                A.step(steps)
+        for k in range(3):
+            graph.replay()
+            torch.cuda.synchronize()
+            for _ in range(1 + launches % 2):
+                B.step(steps)
+            np.testing.assert_array_equal(A.moments(), B.moments(), err_msg=str(k))

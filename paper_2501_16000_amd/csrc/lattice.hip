@@ -555,6 +555,7 @@ lb_status lb_diagnostics(lb_lattice* h, double out[6]) {
   double* result = h->aux + kDiagBlocks * 6;
   HIP_TRY(h, launch_diagnostics(h->opt.equilibrium, h->opt.storage, h->buf[h->cur], h->aux, result,
                                 h->geo, h->coef, h->theta_energy, h->fmt(h->cur), h->stream));
+  HIP_TRY(h, hipStreamSynchronize(h->stream));  // see HostTransfer::to_host
   HIP_TRY(h, hipMemcpyAsync(out, result, 6 * sizeof(double), hipMemcpyDeviceToHost, h->stream));
   HIP_TRY(h, hipStreamSynchronize(h->stream));
   return LB_OK;
@@ -586,6 +587,7 @@ lb_status lb_density_profile(lb_lattice* h, double* out) {
   if (st != LB_OK) return st;
   HIP_TRY(h, launch_profile(h->opt.equilibrium, h->opt.storage, h->buf[h->cur], h->tmp,
                             h->tmp + h->geo.nx, h->geo, h->coef, h->fmt(h->cur), h->stream));
+  HIP_TRY(h, hipStreamSynchronize(h->stream));  // see HostTransfer::to_host
   HIP_TRY(h, hipMemcpyAsync(out, h->tmp, (size_t)h->geo.nx * sizeof(double),
                             hipMemcpyDeviceToHost, h->stream));
   HIP_TRY(h, hipStreamSynchronize(h->stream));

@@ -421,6 +421,7 @@ lb_status lb3_diagnostics(lb3_lattice* h, double out[7]) {
     HIP_TRY(h, launch_diagnostics3(h->opt.storage, h->buf[h->cur], h->aux, result, h->geo, h->coef,
                                    h->coef.theta, h->stream));
   }
+  HIP_TRY(h, hipStreamSynchronize(h->stream));  // see HostTransfer::to_host
   HIP_TRY(h, hipMemcpyAsync(out, result, 7 * sizeof(double), hipMemcpyDeviceToHost, h->stream));
   HIP_TRY(h, hipStreamSynchronize(h->stream));
   return LB_OK;

@@ -9,7 +9,7 @@ lattice per launch.  Populations are resident in HBM before timing starts.
 
 Prints one JSON line (rank 0):
   value      MLUPS = nx * ny * steps / seconds / 1e6 (FP64 storage)
-  roofline   the sweep kernel's algorithmic bytes (2 * 9 * 8 per node) per
+  roofline   the sweep kernel's algorithmic bytes (2 * 5 * 8 per node) per
              launch over its average launch time (HIP events on the lattice's
              stream), against 8 TB/s; traffic from rocprofv3 counters when
              profiles/ holds them for this kernel
@@ -35,6 +35,12 @@ FP64_PEAK_TFLOPS = 78.6     # MI355X FP64 vector
 FP32_PEAK_TFLOPS = 157.3    # MI355X FP32 vector
 VALU_PEAK = 256 * 4 * 16 * 2.4e9  # lane-instructions/s: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz
 BYTES_PER_NODE = {"f64": 144, "f32s": 72, "f16s": 36, "bf16s": 36}
+# Large periodic OReg lattices in FP64 hold five numbers per node, not nine
+# populations (plan.hpp plan_strips: from 300,000 nodes).
+NUMBERS_FROM, NUMBER_BYTES = 300000, 80
+# D3Q27 OReg boxes hold ten numbers per node in FP64 and F32S (plan3.hpp
+# march_worthwhile: from 60,000 and 300,000 nodes).
+NUMBERS3_FROM = {"f64": 60000, "f32s": 300000}
 STORAGE_BYTES = {"f64": 8, "f32s": 4, "f16s": 2, "bf16s": 2}
 # Time steps per fused launch (dispatch.hpp FusedLevels) and the algorithmic
 # flops of one guided-equilibrium OReg node update as implemented in
@@ -112,9 +118,28 @@ def time_lattice(oreg, torch, n, tau, storage, steps, warmup, fields, fuse_steps
     return ms, diag
 
 
-SOURCES_2D = ("kernels.hip", "d2q9.hpp", "dispatch.hpp", "fused_impl.hpp", "fused_f64.hip",
-              "fused_f32s.hip", "fused_f16s.hip", "fused_bf16s.hip")
-SOURCES_3D = ("kernels3.hip", "d3q27.hpp", "d2q9.hpp")
+SOURCES_2D = ("kernels.hip", "d2q9.hpp", "dispatch.hpp", "lanes.hpp", "fused_impl.hpp",
+              "fused_f64.hip", "fused_f32s.hip", "fused_f16s.hip", "fused_bf16s.hip")
+SOURCES_3D = ("kernels3.hip", "march3.hip", "plan3.hpp", "d3q27.hpp", "d2q9.hpp")
+
+
+def launch_bytes(storage, n):
+    """Bytes that one launch on an n x n lattice has to read and write."""
+    numbers = storage == "f64" and n * n >= NUMBERS_FROM
+    return (NUMBER_BYTES if numbers else BYTES_PER_NODE[storage]) * n * n
+
+
+def box_bytes(storage, n):
+    """The same for an n^3 box: two ways of ten numbers or of 27 populations."""
+    numbers = n ** 3 >= NUMBERS3_FROM.get(storage, float("inf"))
+    return 2 * (10 if numbers else 27) * STORAGE_BYTES[storage] * n ** 3
+
+
+def single_kernel(storage, n):
+    """The kernel of one step per launch."""
+    if storage == "f64" and n * n >= NUMBERS_FROM:
+        return "fused_sweep_kernel<K=1, guided, OReg, periodic, f64>"
+    return f"sweep_kernel<guided, OReg, periodic, {storage}>"
 
 
 def load_traffic(storage, n, nbytes_alg, fused=False, d3=False):
@@ -214,13 +239,14 @@ def d3q27_bench(torch, n, tau, steps, copy_gbs=None):
     fields = workloads.shear_wave3(n, 0.05)
     out = {"workload": f"D3Q27 periodic {n}^3 OReg sweep, shear wave u0=0.05 normal to "
                        f"(1,1,1), guided equilibrium, theta=1/3, tau={tau}, one box per launch",
-           "kernel": "sweep3_kernel<guided, OReg, storage>", "steps": steps}
+           "kernel": "march3_kernel<guided, storage> (F64, F32S), "
+                     "sweep3_kernel<guided, OReg, storage> (F16S, BF16S)", "steps": steps}
     for st in ("f64", "f32s", "f16s", "bf16s"):
         ms, diag = time_box(oreg3, torch, n, tau, st, steps, 10, fields)
         if diag[6] != 0:
             raise RuntimeError(f"non-finite populations in the D3Q27 {st} run")
         launch_s = ms / 1e3 / steps
-        alg = 2 * 27 * STORAGE_BYTES[st] * n ** 3
+        alg = box_bytes(st, n)
         ach = alg / launch_s / 1e9
         out[st] = {"value": round(n ** 3 / launch_s / 1e6, 1), "unit": "MLUPS",
                    "ms_per_step": round(launch_s * 1e3, 5),
@@ -339,19 +365,26 @@ def summarize_pmc(fetch_csv, write_csv, n):
                      "`bench.py --pmc-workload`, scaled by a 1 GiB device copy",
            "copy_fetch_scale": f_scale, "copy_write_scale": w_scale,
            "kernel_source_sha": kernel_source_sha(), "kernels": {}}
-    sts = {"Storage<0>": "f64", "Storage<1>": "f32s", "Storage<2>": "f16s", "Storage<3>": "bf16s"}
+    sts = {"Storage<0>": "f64", "Storage<1>": "f32s", "Storage<2>": "f16s", "Storage<3>": "bf16s",
+           "march3_kernel<0, 0": "f64", "march3_kernel<0, 1": "f32s"}
     for k, v in fetch.items():
-        if "sweep" not in k or "batched" in k:
+        d3 = "sweep3_kernel" in k or "march3_kernel" in k
+        if not d3 and ("sweep" not in k or "batched" in k):
             continue
+        m = re.search(r"fused_sweep_kernel<(\d+)((?:, \w+)*)>", k)
+        levels = int(m.group(1)) if m else 1
+        numbers = bool(m) and m.group(2).count(",") == 6 and m.group(2).endswith("true")
         st = next((name for tag, name in sts.items() if tag in k), None)
         if st is None or k not in write:
             continue
         fb = v * 1024.0 * f_scale
         wb = write[k] * 1024.0 * w_scale
-        d3 = "sweep3_kernel" in k
-        key = ("d3q27_" if d3 else "") + ("fused_" if "fused_sweep_kernel" in k else "") + st
+        if levels not in (1, FUSED_K[st]):
+            continue
+        key = ("d3q27_" if d3 else "") + ("fused_" if levels > 1 else "") + st
         side = D3_PMC_N if d3 else n
-        alg = (2 * 27 * STORAGE_BYTES[st] * side ** 3) if d3 else BYTES_PER_NODE[st] * n * n
+        alg = (box_bytes(st, side) if d3 else
+               (NUMBER_BYTES if numbers else BYTES_PER_NODE[st]) * n * n)
         out["kernels"][key] = {"n": side,
                                "kernel_source_sha": kernel_source_sha(SOURCES_3D if d3 else SOURCES_2D),
                                "kernel": (re.search(r"\w+_kernel<[^>]*>", k) or re.search(".*", k)).group(0),
@@ -538,7 +571,7 @@ def main():
     cells = n * n
     sec = ms / 1e3
     mlups = cells * args.steps / sec / 1e6
-    alg_bytes = BYTES_PER_NODE[args.storage] * cells
+    alg_bytes = launch_bytes(args.storage, n)
     if nl > 0:
         # the dominant kernel: K steps per launch
         per_launch_s = fms / 1e3 / nl
@@ -559,7 +592,7 @@ def main():
         roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                     "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                     "traffic": load_traffic(args.storage, n, alg_bytes),
-                    "kernel": f"sweep_kernel<guided, OReg, periodic, {args.storage}>",
+                    "kernel": single_kernel(args.storage, n),
                     "algorithmic_bytes_per_launch": alg_bytes}
     # the single-step sweep of the same workload (one launch per step)
     sms, _ = time_lattice(oreg, torch, n, tau, args.storage, min(args.steps, 300), 10, fields,
@@ -567,14 +600,14 @@ def main():
     s_launch = sms / 1e3 / min(args.steps, 300)
     s_ach = alg_bytes / s_launch / 1e9
     single = {"value": round(cells / s_launch / 1e6, 1), "unit": "MLUPS",
-              "kernel": f"sweep_kernel<guided, OReg, periodic, {args.storage}>",
+              "kernel": single_kernel(args.storage, n),
               "roofline": {"bound": "hbm", "achieved": round(s_ach, 1), "peak": HBM_PEAK_GBS,
                            "unit": "GB/s", "frac": round(s_ach / HBM_PEAK_GBS, 4),
                            "traffic": load_traffic(args.storage, n, alg_bytes),
                            "algorithmic_bytes_per_launch": alg_bytes}}
     # the practical ceiling: a plain copy of one population buffer of this
     # lattice (each byte read once and written once, as one sweep step does)
-    copy_bytes = alg_bytes // 2 // 16 * 16
+    copy_bytes = BYTES_PER_NODE[args.storage] * cells // 2 // 16 * 16
     copy_gbs = copy_ceiling(oreg, torch, copy_bytes)
     copy = {"value": round(copy_gbs, 1), "unit": "GB/s", "kernel": "copy_kernel (lb_copy_device)",
             "bytes_per_copy": copy_bytes, "copies": 20}
@@ -612,7 +645,7 @@ def main():
         vms, vdiag = time_lattice(oreg, torch, n, tau, st, args.variant_steps,
                                   min(args.warmup, 20), fields)
         vsec = vms / 1e3
-        v_ach = BYTES_PER_NODE[st] * cells / (vsec / args.variant_steps) / 1e9
+        v_ach = launch_bytes(st, n) / (vsec / args.variant_steps) / 1e9
         entry = {"value": round(cells * args.variant_steps / vsec / 1e6, 1),
                  "unit": "MLUPS", "steps": args.variant_steps,
                  "ms_per_step": round(vms / args.variant_steps, 5),
@@ -620,13 +653,13 @@ def main():
         if FUSED_K[st] > 1:
             # K steps per launch: bounded by VALU issue, not by HBM
             tf = FLOPS_PER_UPDATE * cells * args.variant_steps / vsec / 1e12
-            traffic = load_traffic(st, n, BYTES_PER_NODE[st] * cells, fused=True)
+            traffic = load_traffic(st, n, launch_bytes(st, n), fused=True)
             entry["roofline"] = {"bound": "alu", "achieved": round(tf, 2),
                                  "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
                                  "frac": round(tf / FP32_PEAK_TFLOPS, 4),
                                  "kernel": f"fused_sweep_kernel<K={FUSED_K[st]}, {st}>",
                                  "traffic": traffic}
-            entry["roofline"]["hbm"] = hbm_side(traffic, BYTES_PER_NODE[st] * cells,
+            entry["roofline"]["hbm"] = hbm_side(traffic, launch_bytes(st, n),
                                                 vsec / args.variant_steps * FUSED_K[st])
             add_copy_fraction(entry["roofline"]["hbm"], copy_gbs)
         else:
@@ -634,7 +667,7 @@ def main():
                                  "peak": HBM_PEAK_GBS, "unit": "GB/s",
                                  "frac": round(v_ach / HBM_PEAK_GBS, 4),
                                  "kernel": f"sweep_kernel<{st}>",
-                                 "traffic": load_traffic(st, n, BYTES_PER_NODE[st] * cells)}
+                                 "traffic": load_traffic(st, n, launch_bytes(st, n))}
         variants[st] = entry
 
     line = {

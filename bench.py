@@ -371,6 +371,8 @@ def summarize_pmc(fetch_csv, write_csv, n):
         d3 = "sweep3_kernel" in k or "march3_kernel" in k
         if not d3 and ("sweep" not in k or "batched" in k):
             continue
+        if re.search(r"march3_kernel<\d+, \d+, [12]>", k):
+            continue  # its readers
         m = re.search(r"fused_sweep_kernel<(\d+)((?:, \w+)*)>", k)
         levels = int(m.group(1)) if m else 1
         numbers = bool(m) and m.group(2).count(",") == 6 and m.group(2).endswith("true")

@@ -30,9 +30,9 @@ using namespace detail;
 // per trip) has no branches apart from the store predicate.  H is a runtime
 // multiple of 3 chosen per lattice (fused_rows).
 
-// One-lane shifts (from_left, from_right in lanes.hpp) through the LDS crossbar (ds_bpermute: no LDS memory, no
-// VALU issue slot), for values that are needed a step after they are
-// shifted: the latency is hidden and the VALU keeps its slots for the
+// One-lane shifts (from_left, from_right in lanes.hpp) through the LDS crossbar
+// (ds_bpermute: no LDS memory, no VALU issue slot), for values that are needed a
+// step after they are shifted: the latency is hidden and the VALU keeps its slots for the
 // collision.  src_byte is 4 x the source lane (wrapped, so edge lanes read
 // a value from the other edge; they are outside the valid region).
 __device__ __forceinline__ float lane_perm(float v, int src_byte) {

@@ -191,7 +191,7 @@ def hbm_side(traffic, alg_bytes, launch_s):
     written once per K-step launch: 2 * 9 * sizeof(storage) per node) and the
     counter bytes of the committed rocprofv3 summary, each over the launch
     time, against 8 TB/s."""
-    out = {"bytes_model": "2*9*sizeof(storage) per node per K-step launch",
+    out = {"bytes_model": "stored state read and written once per K-step launch",
            "algorithmic_GBs": round(alg_bytes / launch_s / 1e9, 1),
            "algorithmic_frac_of_peak": round(alg_bytes / launch_s / 1e9 / HBM_PEAK_GBS, 4),
            "counter_GBs": None, "counter_frac_of_peak": None}

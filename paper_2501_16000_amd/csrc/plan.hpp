@@ -68,6 +68,14 @@ namespace plan_detail {
 
 constexpr int kBytes[4] = {8, 4, 2, 2};
 
+inline int div_up(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
+
+// Whether a launch of tx x ty workgroups of `threads` covers fewer than 2^32
+// work-items, as a HIP launch has to.
+inline bool one_launch(int tx, int ty, int threads) {
+  return (int64_t)tx * ty < (int64_t)4294967296LL / threads;
+}
+
 // Tile sweep.  Launch t0 + t1, a step `lat` plus `c` for every wavefront of
 // the fullest SIMD that still has nodes to update, and 1/seg for every row
 // segment the first step loads.
@@ -95,8 +103,9 @@ inline double tile_us(int st, const TileShape& t, int L, int cus) {
   int fit = 28 / W;  // 70 VGPRs: seven wavefronts per SIMD
   if (lds) fit = std::min(fit, 160 * 1024 / lds);
   fit = std::max(1, std::min(fit, 16));
-  const int need = (t.tx * t.ty + cus - 1) / cus, conc = std::min(fit, need);
-  const int rounds = (t.tx * t.ty + cus * conc - 1) / (cus * conc);
+  const int64_t tiles = (int64_t)t.tx * t.ty;
+  const int conc = (int)std::min<int64_t>(fit, div_up(tiles, cus));
+  const int rounds = div_up(tiles, (int64_t)cus * conc);
   double us = f.t1 + conc * W * (64.0 / t.rx + 1) / f.seg;
   if (t.hx == 0 && t.hy == 0 && L > 1) {  // every step alike (L may be large)
     us += L * (f.lat + f.c * ((W * conc + 3) / 4));
@@ -115,10 +124,10 @@ inline double block_us(int st, const BlockShape& b, int L, int cus) {
   // BF16S takes its figures from F16S; its six rows measured slower against its
   // four (62 x 2909: 3.0 us per step in six rows, 2.65 in four, modelled equal).
   if (st == LB_BF16S && b.rows == 6) f.c *= 1.05, f.c1 *= 1.05;
-  const int tiles = b.tx * b.ty;
+  const int64_t tiles = (int64_t)b.tx * b.ty;
   const int fit = std::max(1, 4 * block_waves_per_simd(st, b.rows) / b.waves);
-  const int need = (tiles + cus - 1) / cus, conc = std::min(fit, need);
-  const int rounds = (tiles + cus * conc - 1) / (cus * conc);
+  const int conc = (int)std::min<int64_t>(fit, div_up(tiles, cus));
+  const int rounds = div_up(tiles, (int64_t)cus * conc);
   double us = f.t1;
   for (int s = 0; s < L; ++s) {
     const int rows = b.waves * b.rows - 2 * s;
@@ -126,8 +135,6 @@ inline double block_us(int st, const BlockShape& b, int L, int cus) {
   }
   return f.t0 + rounds * us;
 }
-
-inline int div_up(int a, int b) { return (a + b - 1) / b; }
 
 // Best tile shape for exactly L steps; us < 0 if there is none.
 inline StepPlan best_tile(int st, int nx, int ny, int L, int cus) {
@@ -141,15 +148,16 @@ inline StepPlan best_tile(int st, int nx, int ny, int L, int cus) {
     t.oy = wy == 0 ? ny : div_up(ny, div_up(ny, wy));
     t.ty = div_up(ny, t.oy);
     t.hy = t.ty == 1 ? 0 : L - 1;
+    if (t.oy > kTileNodes || t.hy > ny) continue;
     t.ry = t.oy + 2 * t.hy;
-    if (t.ry > kTileNodes || t.hy > ny) continue;
     for (int wx : kX) {
       if (wx >= nx) continue;
       t.ox = wx == 0 ? nx : wx;
       t.tx = div_up(nx, t.ox);
       t.hx = t.tx == 1 ? 0 : L - 1;
+      if (t.ox > kTileNodes || t.hx > nx) continue;
       t.rx = t.ox + 2 * t.hx;
-      if ((int64_t)t.rx * t.ry > kTileNodes || t.hx > nx) continue;
+      if (t.rx * t.ry > kTileNodes) continue;
       if ((int64_t)t.tx * t.ty > 16 * cus) continue;
       const double us = tile_us(st, t, L, cus);
       if (best.us < 0 || us < best.us) {
@@ -187,7 +195,7 @@ inline StepPlan block_large(int st, int nx, int ny, int L, int cus) {
   p.levels = L;
   const int rows = st == LB_F16S ? block_rows_small(st) : block_rows_big(st);
   p.block = block_shape(nx, ny, L, kBlockWaves, rows);
-  p.us = block_us(st, p.block, L, cus);
+  p.us = one_launch(p.block.tx, p.block.ty, 64 * kBlockWaves) ? block_us(st, p.block, L, cus) : -1;
   return p;
 }
 constexpr int block_large_levels(int st) { return st == LB_F16S || st == LB_BF16S ? 4 : 6; }

@@ -22,6 +22,8 @@
 // / 5.3; 512^2 F64 3.9 / 2.9.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "dispatch.hpp"
 #include "lanes.hpp"
 
@@ -174,9 +176,9 @@ __global__ __launch_bounds__(64 * kBlockWaves) void block_kernel(
 // fewer steps, has the same ones.
 template <int RR, int EQ, int ST>
 __global__ __launch_bounds__(64 * kBlockWaves) void batched_block_kernel(
-    const LatticeDesc* __restrict__ d, const int* __restrict__ map, int64_t T) {
+    const LatticeDesc* __restrict__ d, const int* __restrict__ map, int64_t first, int64_t T) {
   using Tt = typename Storage<ST>::T;
-  const int item = xcd_block();
+  const int64_t item = first + xcd_block();
   const LatticeDesc& L = d[map[item]];
   const int local = (int)(item - L.tile_begin);
   const int by = local / L.strips, bx = local - by * L.strips;
@@ -196,9 +198,15 @@ hipError_t launch_batched_block(int eq, int st, const LatticeDesc* d, const int*
   if (waves < 1 || waves > kBlockWaves) return hipErrorInvalidValue;
   return with_eq(eq, [&](auto EQ) {
     auto go = [&](auto RR, auto ST) {
-      batched_block_kernel<RR.value, EQ.value, ST.value>
-          <<<(unsigned int)items, 64 * waves, 0, s>>>(d, item_map, T);
-      return hipGetLastError();
+      // one launch, unless the items ask for 2^32 work-items or more
+      const int64_t most = launch_items(64 * waves);
+      for (int64_t first = 0; first < items; first += most) {
+        batched_block_kernel<RR.value, EQ.value, ST.value>
+            <<<(unsigned int)std::min(most, items - first), 64 * waves, 0, s>>>(d, item_map, first, T);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+      }
+      return hipSuccess;
     };
     auto rr = [&](auto ST) -> hipError_t {
       if (rows == block_rows_small(ST.value)) return go(IC<block_rows_small(ST.value)>{}, ST);

@@ -64,16 +64,17 @@ struct StepPlan {
   BlockShape block{};
 };
 
+// Workgroups of `threads` that one HIP launch can have: fewer than 2^32 work-items.
+constexpr int64_t launch_items(int threads) { return (int64_t)4294967295LL / threads; }
+
 namespace plan_detail {
 
 constexpr int kBytes[4] = {8, 4, 2, 2};
 
 inline int div_up(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
-// Whether a launch of tx x ty workgroups of `threads` covers fewer than 2^32
-// work-items, as a HIP launch has to.
 inline bool one_launch(int tx, int ty, int threads) {
-  return (int64_t)tx * ty < (int64_t)4294967296LL / threads;
+  return (int64_t)tx * ty <= launch_items(threads);
 }
 
 // Tile sweep.  Launch t0 + t1, a step `lat` plus `c` for every wavefront of
@@ -365,7 +366,7 @@ inline int serve_strip_rows(const Sizes& sizes, int K, int width, int cus) {
   for (int most : {132, 99, 66, 48, 33, 24, 18, 12, 9, 6, 3}) {
     int64_t items = 0;
     for (const LatticeSize n : sizes)
-      items += (int64_t)((n.nx + width - 1) / width) * ((n.ny + most - 1) / most);
+      items += (int64_t)plan_detail::div_up(n.nx, width) * plan_detail::div_up(n.ny, most);
     const double w = (double)((items + 4 * cus - 1) / (4 * cus));
     const double cost = w / (1 + 0.08 * (std::min(w, 2.0) - 1)) * (K * (most + 2 * K) - K * (K + 1) + 2 * K);
     if (best_cost < 0 || cost < best_cost) {

@@ -49,6 +49,11 @@ int main() {
           ++plans;
         }
       }
+  // what the server's block launch is cut into
+  for (int waves = 1; waves <= kBlockWaves; ++waves)
+    if (launch_items(64 * waves) * 64 * waves >= 4294967296LL ||
+        (launch_items(64 * waves) + 1) * 64 * waves < 4294967296LL)
+      fail("launch items", waves, 0, 0, 0);
   std::printf("plans %lld\n", plans);
   return 0;
 }

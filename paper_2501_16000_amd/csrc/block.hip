@@ -46,11 +46,8 @@ __device__ __forceinline__ void block_tile(const typename Storage<ST>::T* __rest
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int h = L - 1, RY = W * RR;
-  const int X = X0 - h + lane;
-  int x = X % nx;
-  if (x < 0) x += nx;
-  int y = (Y0 - h + wv * RR) % ny;
-  if (y < 0) y += ny;
+  const int x = wrap_add(X0, lane - h, nx);
+  int y = wrap_add(Y0, wv * RR - h, ny);
   const bool wall = BC == LB_BC_BOUNCEBACK && (x == 0 || x == nx - 1);
 
   auto update = [&](R(&N)[9]) {
@@ -145,12 +142,12 @@ __device__ __forceinline__ void block_tile(const typename Storage<ST>::T* __rest
       pin(f[r]);
     }
   }
-  if (lane >= h && lane < h + ox && X < nx) {
+  if (lane >= h && lane < h + ox && lane - h < nx - X0) {
 #pragma unroll
     for (int r = 0; r < RR; ++r) {
-      const int j = wv * RR + r, Y = Y0 - h + j;
-      if (j >= h && j < h + oy && Y < ny) {
-        T* const q = dst + (int64_t)Y * nx + X;
+      const int j = wv * RR + r;
+      if (j >= h && j < h + oy && j - h < ny - Y0) {
+        T* const q = dst + (int64_t)(Y0 + (j - h)) * nx + (X0 + (lane - h));
 #pragma unroll
         for (int i = 0; i < 9; ++i) q[i * P] = S::store(f[r][i]);
       }

@@ -56,6 +56,13 @@ hipError_t with_bc(int bc, F&& f) {
 
 __device__ __forceinline__ int wrap_dec(int v, int n) { return v == 0 ? n - 1 : v - 1; }
 __device__ __forceinline__ int wrap_inc(int v, int n) { return v == n - 1 ? 0 : v + 1; }
+// (v + d) mod n for 0 <= v < n and any small d.  The sum itself may not fit an
+// int: sides go up to 2^31 - 1.
+__host__ __device__ __forceinline__ int wrap_add(int v, int d, int n) {
+  d %= n;
+  if (d < 0) d += n;
+  return v >= n - d ? v - (n - d) : v + d;
+}
 __device__ __forceinline__ int wrap_sub(int v, int c, int n) {
   return c == 0 ? v : (c > 0 ? wrap_dec(v, n) : wrap_inc(v, n));
 }

@@ -133,9 +133,8 @@ __device__ __forceinline__ void fused_strip(const typename Storage<ST>::T* __res
   constexpr bool SHARE = NW > 1;
   const int J = H + 2 * K;  // rows of level 0 read (H is a multiple of 3)
   const int cs = 64 * wv + lane;  // column within the strip, halo included
-  int col = (X0 - KS + cs) % nx;
-  if (col < 0) col += nx;
-  const bool store_lane = cs >= KS && cs < 64 * NW - KS && X0 - KS + cs < nx;
+  const int col = wrap_add(X0, cs - KS, nx);
+  const bool store_lane = cs >= KS && cs < 64 * NW - KS && cs - KS < nx - X0;
   const int left_byte = ((lane - 1) & 63) << 2, right_byte = ((lane + 1) & 63) << 2;
   // Window shifts of one wavefront's strip through ds_bpermute for the 16-bit
   // formats (measured 16 % faster for F16S and 7 % for BF16S).  F64 shifts by
@@ -213,10 +212,10 @@ __device__ __forceinline__ void fused_strip(const typename Storage<ST>::T* __res
   // (F32S unchanged).  The single-step sweep keeps nontemporal stores (3-6 %
   // faster there).
   Tt pend[NO];
-  auto store_row = [&](int y) {
-    if (OUT != kVisit && store_lane && y >= Y0 && y < ny) {
+  auto store_row = [&](int dy) {  // row Y0 + dy
+    if (OUT != kVisit && store_lane && dy >= 0 && dy < ny - Y0) {
 #pragma unroll
-      for (int i = 0; i < NO; ++i) io.store(i, y, col, pend[i]);
+      for (int i = 0; i < NO; ++i) io.store(i, Y0 + dy, col, pend[i]);
     }
   };
 
@@ -243,7 +242,7 @@ __device__ __forceinline__ void fused_strip(const typename Storage<ST>::T* __res
     }
     __asm__ volatile("" : "+v"(C[0]), "+v"(C[1]), "+v"(C[2]), "+v"(C[3]), "+v"(C[4]), "+v"(C[5]),
                      "+v"(C[6]), "+v"(C[7]), "+v"(C[8]));
-    if constexpr (NP == K) store_row(Y0 + j - 1 - 2 * K);  // the previous step's output row
+    if constexpr (NP == K) store_row(j - 1 - 2 * K);  // the previous step's output row
     [[maybe_unused]] Neighbours x;
     pass(q * K % 3, C, x);
     // Prefetch the next row of level 0.  The last step reloads its own row
@@ -284,8 +283,8 @@ __device__ __forceinline__ void fused_strip(const typename Storage<ST>::T* __res
         }
       } else if constexpr (OUT == kVisit) {
         if (lv + 1 == K) {
-          const int y = Y0 + j - 2 * K;
-          if (store_lane && y >= Y0 && y < ny) visit(N, y);
+          const int dy = j - 2 * K;
+          if (store_lane && dy >= 0 && dy < ny - Y0) visit(N, Y0 + dy);
           break;
         }
       }
@@ -327,7 +326,7 @@ __device__ __forceinline__ void fused_strip(const typename Storage<ST>::T* __res
     one_row(j + 1, IC<(2 * K + 1) % 3>{}, IC<K>{});
     one_row(j + 2, IC<(2 * K + 2) % 3>{}, IC<K>{});
   }
-  store_row(Y0 + J - 1 - 2 * K);
+  store_row(J - 1 - 2 * K);
 }
 
 // fmt_src, fmt_dst: the format flags of the two buffers (0: populations, 1: five

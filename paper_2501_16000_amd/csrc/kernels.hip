@@ -48,7 +48,7 @@ __device__ __forceinline__ void pull(const typename Storage<ST>::T* __restrict__
   typedef T V __attribute__((ext_vector_type(VX)));
   const int64_t P = g.plane;
   const int nx = g.nx;
-  if (x0 >= 1 && x0 + VX < nx) {
+  if (x0 >= 1 && x0 < nx - VX) {
     const V v0 = load_vec<V>(src + 0 * P + r0 + x0);
     const V v1 = load_vec<V>(src + 1 * P + r0 + x0 - 1);
     const V v2 = load_vec<V>(src + 2 * P + rm + x0);
@@ -100,7 +100,7 @@ __device__ __forceinline__ void push_local(typename Storage<ST>::T* __restrict__
   const int64_t P = g.plane;
   // Vector stores need sizeof(V) alignment: an even row length (VX = 2).
   const bool aligned = (VX == 1) || ((((r0 + x0) | P) & (VX - 1)) == 0);
-  if (x0 + VX <= g.nx && aligned) {
+  if (x0 <= g.nx - VX && aligned) {
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
       V v;
@@ -130,8 +130,11 @@ __global__ __launch_bounds__(SweepShape<ST>::BS) void sweep_kernel(
   // the 4 % of reads that straddle two blocks' x ranges but made this
   // HBM-bound sweep 5 % slower (measured), so it is not used here.
   const int y = blockIdx.x / nseg;
-  const int x0 = ((blockIdx.x - y * nseg) * BS + threadIdx.x) * VX;
-  if (x0 >= g.nx) return;
+  // Unsigned until it is known to be a column: the row rounded up to whole
+  // workgroups may pass 2^31.
+  const unsigned int column = ((blockIdx.x - y * nseg) * BS + threadIdx.x) * VX;
+  if (column >= (unsigned int)g.nx) return;
+  const int x0 = (int)column;
   const int ym = wrap_dec(y, g.ny), yp = wrap_inc(y, g.ny);
   const int64_t r0 = (int64_t)y * g.nx, rm = (int64_t)ym * g.nx, rp = (int64_t)yp * g.nx;
   R f[VX][9];
@@ -413,10 +416,11 @@ __global__ __launch_bounds__(kThreads) void profile_kernel(const typename Storag
                                                            double* __restrict__ partials, Geometry g,
                                                            Coef64 c, int rows,
                                                            const unsigned int* __restrict__ fmt) {
-  const int x = blockIdx.x * kThreads + threadIdx.x;
-  if (x >= g.nx) return;
+  const unsigned int column = blockIdx.x * kThreads + threadIdx.x;
+  if (column >= (unsigned int)g.nx) return;
+  const int x = (int)column;
   const bool numbers = holds_numbers<NEQ>(fmt);
-  const int y0 = blockIdx.y * rows, y1 = min(y0 + rows, g.ny);
+  const int y0 = blockIdx.y * rows, y1 = y0 + min(rows, g.ny - y0);
   double sum = 0.0;
   for (int y = y0; y < y1; ++y) {
     double d[9], drho, jx, jy;
@@ -430,8 +434,8 @@ __global__ __launch_bounds__(kThreads) void profile_kernel(const typename Storag
 __global__ __launch_bounds__(kThreads) void profile_final_kernel(const double* __restrict__ partials,
                                                                  double* __restrict__ out, int nx,
                                                                  int ny, int chunks) {
-  const int x = blockIdx.x * kThreads + threadIdx.x;
-  if (x >= nx) return;
+  const unsigned int x = blockIdx.x * kThreads + threadIdx.x;
+  if (x >= (unsigned int)nx) return;
   double sum = 0.0;
   for (int i = 0; i < chunks; ++i) sum += partials[(int64_t)i * nx + x];
   out[x] = sum / ny;
@@ -463,7 +467,7 @@ hipError_t launch_sweep(int eq, int coll, int bc, int st, const void* src, void*
   return with_storage(st, [&](auto ST) {
     using T = typename Storage<ST.value>::T;
     constexpr int tile = SweepShape<ST.value>::VX * SweepShape<ST.value>::BS;
-    const int nseg = (g.nx + tile - 1) / tile;
+    const int nseg = (int)(((int64_t)g.nx + tile - 1) / tile);
     const unsigned int nblocks = (unsigned int)nseg * (unsigned int)g.ny;
     return with_eq(eq, [&](auto EQ) {
       return with_coll(coll, [&](auto CO) {
@@ -666,7 +670,7 @@ hipError_t launch_profile(int eq, int st, const void* src, double* out, double* 
   // About four workgroups per CU, and at least eight rows per chunk.
   const int xblocks = (int)blocks_for(g.nx);
   const int want = std::max(1, std::min(1024 / xblocks, g.ny / 8));
-  const int rows = (g.ny + want - 1) / want, chunks = (g.ny + rows - 1) / rows;
+  const int rows = plan_detail::div_up(g.ny, want), chunks = plan_detail::div_up(g.ny, rows);
   const hipError_t e = with_form(eq, st, fmt, [&](auto ST, auto NEQ) {
     using T = typename Storage<ST.value>::T;
     profile_kernel<ST.value, NEQ.value><<<dim3(xblocks, chunks), kThreads, 0, s>>>(

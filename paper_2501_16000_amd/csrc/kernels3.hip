@@ -115,9 +115,9 @@ __global__ __launch_bounds__(64 * Sweep3Waves<ST>::N) void sweep3_kernel(
     const unsigned int seg = task - row * nseg;
     const int y = (int)(row % (unsigned int)g.ny);
     const int z = (int)(row / (unsigned int)g.ny);
-    const int x = (int)(seg * 64u) + (int)(threadIdx.x & 63);
-    active = x < g.nx;
-    const int xc = active ? x : g.nx - 1;  // lanes past the row end load a valid node
+    const unsigned int x = seg * 64u + (threadIdx.x & 63);
+    active = x < (unsigned int)g.nx;
+    const int xc = active ? (int)x : g.nx - 1;  // lanes past the row end load a valid node
     const int xm = xc == 0 ? g.nx - 1 : xc - 1;
     const int xp = xc == g.nx - 1 ? 0 : xc + 1;
     // Start of the source row of g_i(x - c_i) for each (c_y, c_z).
@@ -347,7 +347,7 @@ unsigned int sweep3_waves(const Geometry3& g, unsigned int most) {
 
 // ------------------------------------------------------------ launchers --
 int64_t sweep3_tasks(const Geometry3& g) {
-  return (int64_t)((g.nx + 63) / 64) * g.ny * g.nz;
+  return ((int64_t)g.nx + 63) / 64 * g.ny * g.nz;
 }
 
 // Whether the sweep packs 64 consecutive nodes of the box into a wavefront.  A
@@ -368,7 +368,7 @@ bool sweep3_packed(const Geometry3& g, int elem) {
 
 hipError_t launch_sweep3(int eq, int coll, int st, const void* src, void* dst, const Geometry3& g,
                          const Coef64& c, hipStream_t s) {
-  const unsigned int nseg = (unsigned int)((g.nx + 63) / 64);
+  const unsigned int nseg = ((unsigned int)g.nx + 63) / 64;
   auto magic = [](int n) { return (unsigned int)((4294967296ULL + n - 1) / (unsigned int)n); };
   return with_storage(st, [&](auto ST) {
     using T = typename Storage<ST.value>::T;

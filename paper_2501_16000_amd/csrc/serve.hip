@@ -210,15 +210,15 @@ LatticeDesc describe(const lb_server* s, const ServedLattice* L) {
     // Strips of equal row blocks, rounded up to a multiple of 3 (the strip
     // loop's unroll).
     d.cols = fused_strip_width(s->opt.storage);
-    const int nblk = (L->ny + s->shape.strip_rows - 1) / s->shape.strip_rows;
-    d.rows = ((L->ny + nblk - 1) / nblk + 2) / 3 * 3;
+    const int nblk = plan_detail::div_up(L->ny, s->shape.strip_rows);
+    d.rows = (plan_detail::div_up(L->ny, nblk) + 2) / 3 * 3;
   } else {
     const BlockShape b = plan_detail::block_shape(L->nx, L->ny, fused_levels(s->opt.storage),
                                                   s->shape.waves, s->shape.rows);
     d.cols = b.ox;
     d.rows = b.oy;
   }
-  d.strips = (L->nx + d.cols - 1) / d.cols;
+  d.strips = plan_detail::div_up(L->nx, d.cols);
   d.coef = s->base;
   d.coef.kappa0 = (1.0 - 1.0 / L->tau) / (2.0 * s->base.theta * s->base.theta);
   d.coef.omega = 1.0 / L->tau;
@@ -288,7 +288,7 @@ lb_status upload_descriptors(lb_server* s) {
   for (int i = 0; i < n; ++i) {
     LatticeDesc d = describe(s, s->active[i]);
     d.tile_begin = tiles;
-    tiles += (int64_t)d.strips * ((d.ny + d.rows - 1) / d.rows);
+    tiles += (int64_t)d.strips * plan_detail::div_up(d.ny, d.rows);
     s->h_desc[slot][i] = d;
   }
   if (tiles > s->map_capacity) {

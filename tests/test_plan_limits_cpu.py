@@ -1,6 +1,9 @@
-"""Plans of csrc/plan.hpp at the largest sizes (host code, no GPU)."""
+"""Plans and index arithmetic at the largest sizes (host code, no GPU)."""
 import os
+import shutil
 import subprocess
+
+import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -19,3 +22,20 @@ def test_longest_lattices(tmp_path):
     out = run_check(tmp_path, "plan_limits_check", "-fsanitize=undefined",
                     "-fno-sanitize-recover=all")
     assert int(out.split()[1]) > 50
+
+
+def test_wrap_up_to_the_longest_side(tmp_path):
+    hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
+    if not os.path.exists(hipcc):
+        pytest.skip("hipcc not available")
+    exe, san = str(tmp_path / "wrap_check"), []
+    for flag in ("-fsanitize=undefined", "-fno-sanitize-recover=all"):
+        san += ["-Xarch_host", flag]
+    inc = ["-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2501_16000_amd", "csrc")]
+    subprocess.run([hipcc, "-std=c++17", "-O1", "-x", "hip", "--cuda-host-only", *san, *inc, "-c",
+                    os.path.join(ROOT, "tests", "host", "wrap_check.cpp"), "-o", exe + ".o"],
+                   check=True)
+    subprocess.run(["/opt/rocm/llvm/bin/clang++", "-fsanitize=undefined", exe + ".o", "-o", exe,
+                    "-L/opt/rocm/lib", "-lamdhip64", "-Wl,-rpath,/opt/rocm/lib"], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout + r.stderr

@@ -299,7 +299,7 @@ lb_status lb_create_ex(const lb_options* opt, lb_lattice** out) {
   if (e != hipSuccess) return cleanup(hip_fail(nullptr, e, "hipMalloc(counter)"));
   if (hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     h->cus = 256;
-  h->strips = plan_strips(h->opt.storage, h->geo.nx, h->geo.ny);
+  h->strips = plan_strips(h->opt.storage, h->geo.nx, h->geo.ny, h->opt.collision, h->opt.boundary_x);
   h->numbers = h->strips && fused_numbers(h->opt.collision, h->opt.boundary_x, h->opt.storage);
   if (h->strips) {
     for (int L = 1; L <= fused_levels(h->opt.storage); ++L)

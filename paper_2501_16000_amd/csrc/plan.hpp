@@ -25,6 +25,7 @@ namespace oreg {
 // region is rx x ry nodes (one per thread), with hx and hy halo nodes per
 // side (levels - 1, or 0 on an axis that one tile covers and that wraps).
 constexpr int kTileNodes = 1024;
+constexpr int kTileMostSide = 2147483647 - 2 * kTileNodes;  // a tile past the end still fits an int
 struct TileShape {
   int tx, ty;
   int ox, oy;
@@ -143,6 +144,7 @@ inline StepPlan best_tile(int st, int nx, int ny, int L, int cus) {
   constexpr int kY[] = {0, 2, 3, 4, 5, 6, 8, 10, 12, 16, 20, 24, 32, 48, 64};
   StepPlan best;
   best.us = -1;
+  if (std::max(nx, ny) > kTileMostSide) return best;
   for (int wy : kY) {
     if (wy >= ny) continue;
     TileShape t;
@@ -225,7 +227,99 @@ inline StepPlan best_block(int st, int nx, int ny, int L, int cus) {
   return best;
 }
 
+// Flat lattices of many rounds of workgroups (one side short): tiles that cover
+// the short side, which then wraps inside LDS, or blocks.  Fitted to 4,700 timed
+// launches on 288 lattices of 5e5, 2e6 and 8e6 nodes with a short side of 1 to
+// 64, all storages, either orientation; the chosen shape ran at the time of the
+// fastest one in the median and within 14 % of it on nine lattices out of ten.
+// Per round of the chip a tile or block takes `wave` for every wavefront
+// (tiles) or row of a wavefront (blocks) and step, `line` for every 128-byte
+// line that it reads or writes, and the latencies of its steps and of itself,
+// shared with the workgroups that are resident beside it.
+struct FlatFit {
+  double t0, wave, line, step, item;
+};
+constexpr FlatFit kFlatTile[4] = {{5.24, 0.0238, 0.00168, 0.601, 0.748},
+                                  {5.94, 0.0306, 0.00119, 0.148, 0.658},
+                                  {6.19, 0.0350, 0.00046, 0.130, 0.817},
+                                  {6.41, 0.0401, 0.00042, 0.148, 0.631}};
+constexpr FlatFit kFlatBlock[4] = {{6.73, 0.0486, 0.00188, 0.508, 0.0},
+                                   {2.20, 0.0383, 0.00121, 0.0, 0.0},
+                                   {6.71, 0.0444, 0.00063, 0.0, 0.0},
+                                   {7.44, 0.0487, 0.00060, 0.061, 0.0}};
+inline double flat_us(const FlatFit& f, double waves, double lines, int L, int conc, int64_t tiles,
+                      int cus) {
+  // In few rounds a last one of some workgroups counts for half of a whole one.
+  double r = (double)tiles / ((double)cus * conc);
+  if (r < 4) r = 0.5 * (r + std::ceil(r));
+  return f.t0 + r * (conc * (f.wave * waves + f.line * lines) + f.step * L + f.item);
+}
+
+// Lines of `rows` rows of `columns` values of each of the nine planes; a region
+// as wide as the lattice is contiguous.
+inline double flat_lines(int st, int columns, int rows, bool whole) {
+  const double l = columns * kBytes[st] / 128.0;
+  return 9.0 * (whole ? rows * l + 1 : rows * (l + 1));
+}
+
+inline StepPlan best_flat(int st, int nx, int ny, int L, int cus) {
+  StepPlan best;
+  best.us = -1;
+  best.levels = L;
+  const int h = L - 1;
+  const bool wide = nx >= ny;
+  const int side = std::min(nx, ny), length = std::max(nx, ny);
+  // Four, eight or sixteen wavefronts: the same number on every SIMD.
+  for (int W : {4, 8, 16}) {
+    const int most = 64 * W / side - 2 * h;
+    if (most < 1 || most >= length || h > length || length > kTileMostSide) continue;
+    TileShape t{};
+    const int out = div_up(length, div_up(length, most));
+    t.ox = wide ? out : nx, t.oy = wide ? ny : out;
+    t.tx = div_up(nx, t.ox), t.ty = div_up(ny, t.oy);
+    t.hx = wide ? h : 0, t.hy = wide ? 0 : h;
+    t.rx = t.ox + 2 * t.hx, t.ry = t.oy + 2 * t.hy;
+    const int threads = (t.rx * t.ry + 63) / 64 * 64;
+    if (!one_launch(t.tx, t.ty, threads)) continue;
+    double waves = 0;  // a tall tile's rows run out step by step
+    for (int s = 0; s < L; ++s) waves += wide ? threads / 64 : std::max(1, (t.rx * (t.ry - 2 * s) + 63) / 64);
+    const int conc = std::max(1, std::min(7 / div_up(threads, 256), 160 * 1024 / (16 * threads * kBytes[st])));
+    const double lines = flat_lines(st, t.rx, t.ry, !wide) + flat_lines(st, t.ox, t.oy, !wide);
+    const double us = flat_us(kFlatTile[st], waves, lines, L, conc, (int64_t)t.tx * t.ty, cus);
+    if (best.us < 0 || us < best.us) best.kind = StepKind::tile, best.us = us, best.tile = t;
+  }
+  for (int rows : {block_rows_small(st), block_rows_big(st)})
+    for (int waves : {4, 5, 6, 8}) {
+      if (rows != block_rows_small(st) && waves % 4 != 0) continue;  // uneven SIMDs
+      // The 16-bit formats' conversions between steps (48 x 41667 F16S: 12.1 us per
+      // step with seven, 10.1 with five; modelled alike).
+      if (st >= LB_F16S && L > 5 && best.us >= 0) continue;
+      if (64 - 2 * h < 8 || waves * rows - 2 * h < 1) continue;
+      const BlockShape b = block_shape(nx, ny, L, waves, rows);
+      if (!one_launch(b.tx, b.ty, 64 * waves)) continue;
+      double work = 0;
+      for (int s = 0; s < L; ++s) work += waves * rows - 2 * s;
+      const int conc = std::max(1, 4 * block_waves_per_simd(st, rows) / waves);
+      const double lines = flat_lines(st, 64, waves * rows, false) + flat_lines(st, b.ox, b.oy, false);
+      const double us = flat_us(kFlatBlock[st], work, lines, L, conc, (int64_t)b.tx * b.ty, cus);
+      if (best.us < 0 || us < best.us) best.kind = StepKind::block, best.us = us, best.block = b;
+    }
+  return best;
+}
+
 }  // namespace plan_detail
+
+// Lattices that best_flat plans.  Below a million nodes best_tile and best_block
+// do better (F32S, us per step: 64 x 7032 4.1 against 5.7, 48 x 16667 4.6 against
+// 6.1), but for columns of a few nodes, which best_tile cuts too short (F64 1 x
+// 450001 133 against 3).  Blocks of F16S are a good fit from 64 rows on (15001 x
+// 100 8.0 against 9.5), the other formats' larger ones are not (BF16S 10.1 against
+// 8.7).
+inline bool plan_flat(int st, int nx, int ny) {
+  const int64_t nodes = (int64_t)nx * ny;
+  if (nodes < 1000000) return nx <= 8 && nodes >= 250000;
+  return std::min(nx, ny) <= (st == LB_F16S ? 64 : 128);
+}
 
 // Whether the strip pipeline (fused_impl.hpp) advances this lattice.  A strip
 // pays for its halo rows once per strip, a block once per block, so strips
@@ -240,11 +334,28 @@ inline StepPlan best_block(int st, int nx, int ny, int L, int cus) {
 //         2236^2 21.7 : 22.7 (19.4 : 17.6), 4096^2 64.9 : 56.5 (63.4 : 48.5);
 //   BF16S 2048^2 19.0 : 22.6 (16.9 : 15.9), 2236^2 22.3 : 24.3 (19.8 : 18.8).
 // F64 changes over early: its blocks leave two wavefronts per SIMD, which
-// cannot hide their loads.
-inline bool plan_strips(int st, int nx, int ny) {
+// cannot hide their loads.  On flat lattices the strips' halo rows (2 K of them
+// above and below) or unused columns decide; us per step, tile or block : strips,
+// 2e6 and 8e6 nodes:
+//   F64 (five numbers)  8 rows 13.1 : 15.7, 50 : 70; 12 rows 15.8 : 15.4, 57 : 57;
+//         16 rows 17.9 : 15.0, 63 : 53; 24 rows 16.3 : 12.9, 60 : 44; 24 columns
+//         17.0 : 19.5, 63 : 68; 32 columns 18.0 : 15.6, 67 : 52;
+//   F32S, 8e6  12 rows 31.5 : 32.9; 20 rows 35.9 : 32.6; 36 rows 38.1 : 33.3;
+//   F16S, 8e6  16 rows 32.4 : 33.4; 20 rows 33.1 : 30.8; BF16S 33.2 : 35.5, and
+//         24 rows 35.6 : 34.3.
+// In FP64 smaller lattices change over at more rows, since tiles and blocks then
+// run in few rounds, and strips that store populations (walls, BGK) at others
+// than strips of five numbers (BGK 23685 x 19 4.8 : 4.0, walls 107143 x 14 12.4 :
+// 14.5).
+inline bool plan_strips(int st, int nx, int ny, int coll = LB_COLL_OREG,
+                        int bc = LB_BC_PERIODIC) {
   const int64_t nodes = (int64_t)nx * ny;
-  const int64_t from = st == LB_F64 ? 300000 : 4500000;
-  return nodes >= from && std::min(nx, ny) > 36;
+  if (st != LB_F64) return nodes >= 4500000 && nx > 36 && ny >= 20;
+  if (nodes < 300000 || nx < (nodes >= 4000000 ? 28 : nodes >= 1000000 ? 32 : nodes >= 800000 ? 36 : 37))
+    return false;
+  if (coll == LB_COLL_BGK) return ny >= (nodes >= 1000000 ? 12 : 16);
+  if (bc == LB_BC_BOUNCEBACK) return ny >= (nodes >= 4000000 ? 16 : 20);
+  return ny >= (nodes >= 1000000 ? 12 : nodes >= 800000 ? 14 : 20);
 }
 
 // Whether the block sweep runs this lattice in many rounds of workgroups.
@@ -261,6 +372,7 @@ inline bool plan_many(int st, int nx, int ny, int cus) {
 inline StepPlan plan_levels(int st, int nx, int ny, int L, int cus) {
   using namespace plan_detail;
   const int64_t nodes = (int64_t)nx * ny;
+  if (plan_flat(st, nx, ny)) return best_flat(st, nx, ny, L, cus);
   StepPlan best;
   best.us = -1;
   // Tiles fill the chip with one small workgroup per CU: up to about 290^2
@@ -285,10 +397,13 @@ inline StepPlan plan_levels(int st, int nx, int ny, int L, int cus) {
 inline StepPlan plan_best(int st, int nx, int ny, int cus) {
   StepPlan best;
   best.us = -1;
-  const bool many = plan_many(st, nx, ny, cus);
+  const bool flat = plan_flat(st, nx, ny), many = !flat && plan_many(st, nx, ny, cus);
   for (int L : {2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 16, 20, 24, 32, 48, kPlanLevels}) {
     // In many rounds the number of steps is measured, not modelled.
     if (many && std::min(nx, ny) > 36 && L != plan_detail::block_large_levels(st)) continue;
+    // Fewer steps than this do not hide what a launch loads (20 x 400000 F32S: 49
+    // us per step with three, 36 with five; modelled alike).
+    if (flat && L < (st <= LB_F32S ? 4 : 3)) continue;
     const StepPlan p = plan_levels(st, nx, ny, L, cus);
     if (p.us >= 0 && (best.us < 0 || p.us * best.levels < best.us * L)) best = p;
   }

@@ -42,14 +42,13 @@ __global__ __launch_bounds__(kTileNodes) void tile_kernel(
   const int rx = s.rx, ry = s.ry;
   const int ly = n / rx, lx = n - ly * rx;
   const int by = blockIdx.x / s.tx, bx = blockIdx.x - by * s.tx;
-  // First column and row of the tile's output, the node's distance from them, and
-  // the lattice's.
-  const int X0 = bx * s.ox, Y0 = by * s.oy, dx = lx - s.hx, dy = ly - s.hy;
-  const int ex = g.nx - X0, ey = g.ny - Y0;
-  // Column and row of the node, wrapped once (halos are no deeper than the
-  // lattice; nodes further out do nothing, see reach).
-  const int x = dx >= ex ? dx - ex : (X0 + dx < 0 ? X0 + dx + g.nx : X0 + dx);
-  const int y = dy >= ey ? dy - ey : (Y0 + dy < 0 ? Y0 + dy + g.ny : Y0 + dy);
+  // Column and row of the node, before the periodic wrap.
+  const int X = bx * s.ox - s.hx + lx, Y = by * s.oy - s.hy + ly;
+  int x = X, y = Y;
+  if (x < 0) x += g.nx;
+  if (x >= g.nx) x -= g.nx;
+  if (y < 0) y += g.ny;
+  if (y >= g.ny) y -= g.ny;
   // Steps this node can take: the distance to the nearest region edge that is
   // not a periodic wrap, plus one; 0 for threads past the region and for
   // columns and rows past the lattice's last tile (their images belong to
@@ -57,8 +56,8 @@ __global__ __launch_bounds__(kTileNodes) void tile_kernel(
   int reach = ly < ry ? L : 0;
   if (s.hx > 0) reach = min(reach, min(lx, rx - 1 - lx) + 1);
   if (s.hy > 0) reach = min(reach, min(ly, ry - 1 - ly) + 1);
-  if (dx - s.hx >= ex || dy - s.hy >= ey) reach = 0;
-  const bool owned = lx >= s.hx && lx < rx - s.hx && ly >= s.hy && ly < ry - s.hy && dx < ex && dy < ey;
+  if (X - s.hx >= g.nx || Y - s.hy >= g.ny) reach = 0;
+  const bool owned = lx >= s.hx && lx < rx - s.hx && ly >= s.hy && ly < ry - s.hy && X < g.nx && Y < g.ny;
   const bool wall = BC == LB_BC_BOUNCEBACK && (x == 0 || x == g.nx - 1);
   const Coeffs<R> k(c);
 
@@ -130,7 +129,8 @@ hipError_t launch_tile_sweep(int eq, int coll, int bc, int st, const void* src, 
                              const Geometry& g, const Coef64& c, const TileShape& sh, int levels,
                              hipStream_t s) {
   const int nodes = sh.rx * sh.ry;
-  if (levels < 1 || nodes < 1 || nodes > kTileNodes) return hipErrorInvalidValue;
+  if (levels < 1 || nodes < 1 || nodes > kTileNodes || g.nx > kTileMostSide || g.ny > kTileMostSide)
+    return hipErrorInvalidValue;
   const int threads = (nodes + 63) / 64 * 64;
   return with_storage(st, [&](auto ST) {
     using T = typename Storage<ST.value>::T;

@@ -21,6 +21,7 @@ static void check(int st, int nx, int ny, int L, const StepPlan& p) {
     const TileShape& t = p.tile;
     if (t.rx < 1 || t.ry < 1 || (long long)t.rx * t.ry > kTileNodes) fail("region", st, nx, ny, L);
     if ((long long)t.tx * t.ox < nx || (long long)t.ty * t.oy < ny) fail("cover", st, nx, ny, L);
+    if (nx > 2147483647 - 2 * kTileNodes || ny > 2147483647 - 2 * kTileNodes) fail("tile past an int", st, nx, ny, L);
     tiles = (long long)t.tx * t.ty;
     threads = (t.rx * t.ry + 63) / 64 * 64;
   } else if (p.kind == StepKind::block) {

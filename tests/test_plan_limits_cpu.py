@@ -24,6 +24,11 @@ def test_longest_lattices(tmp_path):
     assert int(out.split()[1]) > 50
 
 
+def test_large_lattices_compute_few_nodes_twice(tmp_path):
+    """Long flat lattices had blocks of 64 x 64 nodes for one to 36 rows."""
+    assert int(run_check(tmp_path, "plan_waste_check").split()[1].strip(",")) > 1000
+
+
 def test_wrap_up_to_the_longest_side(tmp_path):
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
     if not os.path.exists(hipcc):

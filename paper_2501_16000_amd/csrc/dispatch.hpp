@@ -96,11 +96,14 @@ __device__ __forceinline__ int xcd_block() {
 // 50.8 / 56.7, BF16S 59.7 / 57.5 / 54.9 / 60.3, 8192^2 polynomial F16S 263 /
 // 237 / 219 / 233; F32S (four, edges only through LDS: 58.0) 58.2 / 55.4 /
 // 61.5.  Fewer wavefronts have more halo, more wait longer at each barrier.
+// The 16-bit formats also have strips of one wavefront (NARROW), for lattices whose
+// rows fill the wide ones badly (plan_strips).
 // F64 has registers for two wavefronts per SIMD only, which the six or seven
 // barriers of a row stop too often: 2048^2 21.8 / 36.8 / 28.1, 4096^2 80.3 /
 // 84.1 / 77.5.
 template <int ST> struct FusedLevels {
   static constexpr int K = ST == LB_F64 ? 7 : 6, NW = ST == LB_F64 ? 1 : 4;
+  static constexpr bool NARROW = ST == LB_F16S || ST == LB_BF16S;
 };
 
 // Fused launches of fewer than FusedLevels<ST>::K steps (lb_step's remainder)
@@ -125,8 +128,8 @@ constexpr bool stores_numbers(int coll, int bc, int st) {
 // per format so that they compile in parallel).
 template <int ST>
 hipError_t fused_launch_st(int eq, int coll, int bc, const void* src, void* dst, const Geometry& g,
-                           const Coef64& c, int rows, int levels, const unsigned int* fmt_src,
-                           unsigned int* fmt_dst, hipStream_t s);
+                           const Coef64& c, int waves, int rows, int levels,
+                           const unsigned int* fmt_src, unsigned int* fmt_dst, hipStream_t s);
 template <int ST>
-hipError_t fused_occupancy_st(int levels, int* blocks);
+hipError_t fused_occupancy_st(int waves, int levels, int* blocks);
 }  // namespace oreg

@@ -5,8 +5,8 @@
 namespace oreg {
 
 template hipError_t fused_launch_st<LB_F64>(int, int, int, const void*, void*, const Geometry&,
-                                           const Coef64&, int, int, const unsigned int*,
+                                           const Coef64&, int, int, int, const unsigned int*,
                                            unsigned int*, hipStream_t);
-template hipError_t fused_occupancy_st<LB_F64>(int, int*);
+template hipError_t fused_occupancy_st<LB_F64>(int, int, int*);
 
 }  // namespace oreg

@@ -331,12 +331,11 @@ __device__ __forceinline__ void fused_strip(const typename Storage<ST>::T* __res
 
 // fmt_src, fmt_dst: the format flags of the two buffers (0: populations, 1: five
 // numbers) of lattices that store five numbers after a launch, else null.
-template <int K, int EQ, int COLL, int BC, int ST, bool BUF = false, bool NUMS = false>
+template <int K, int EQ, int COLL, int BC, int ST, int NW, bool BUF = false, bool NUMS = false>
 __global__ __launch_bounds__(256) void fused_sweep_kernel(
     const typename Storage<ST>::T* __restrict__ src, typename Storage<ST>::T* __restrict__ dst,
     Geometry g, Coef64 c, int strips, int items, int H, const unsigned int* __restrict__ fmt_src,
     unsigned int* __restrict__ fmt_dst) {
-  constexpr int NW = FusedLevels<ST>::NW;
   constexpr int W = 64 * NW - 2 * K;
   // Neighbouring strips share their halo columns, which then come from the
   // XCD's L2 instead of HBM a second time.  The wavefront index is uniform:
@@ -361,15 +360,24 @@ __global__ __launch_bounds__(256) void fused_sweep_kernel(
   }
 }
 
+// Runs f(wavefronts per strip) if strips of that many are compiled.
+template <int ST, class F>
+hipError_t with_strip_waves(int waves, F&& f) {
+  if (waves == FusedLevels<ST>::NW) return f(IC<FusedLevels<ST>::NW>{});
+  if constexpr (FusedLevels<ST>::NARROW) {
+    if (waves == 1) return f(IC<1>{});
+  }
+  return hipErrorInvalidValue;
+}
+
 }  // namespace
 
 template <int ST>
 hipError_t fused_launch_st(int eq, int coll, int bc, const void* src, void* dst, const Geometry& g,
-                           const Coef64& c, int rows, int levels, const unsigned int* fmt_src,
-                           unsigned int* fmt_dst, hipStream_t s) {
+                           const Coef64& c, int waves, int rows, int levels,
+                           const unsigned int* fmt_src, unsigned int* fmt_dst, hipStream_t s) {
   using T = typename Storage<ST>::T;
   constexpr int K = FusedLevels<ST>::K;
-  constexpr int NW = FusedLevels<ST>::NW;
   return with_eq(eq, [&](auto EQ) {
     return with_coll(coll, [&](auto CO) {
       return with_bc(bc, [&](auto BC) -> hipError_t {
@@ -378,54 +386,58 @@ hipError_t fused_launch_st(int eq, int coll, int bc, const void* src, void* dst,
         constexpr bool buf_config = short_fused(CO.value, BC.value);
         constexpr bool nums = stores_numbers(CO.value, BC.value, ST);
         const bool buf = buf_config && 9 * g.plane * (int64_t)sizeof(T) <= kBufferFormBytes;
-        auto go = [&](auto L) -> hipError_t {
-          constexpr int W = 64 * NW - 2 * L.value;
+        auto go = [&](auto L, auto WAVES) -> hipError_t {
+          constexpr int NW = WAVES.value, W = 64 * NW - 2 * L.value;
           const int strips = (g.nx + W - 1) / W;
           const int segs = (g.ny + rows - 1) / rows;
           const int items = strips * segs;
           const unsigned int nblocks = (unsigned int)(NW == 1 ? (items + 3) / 4 : items);
           if constexpr (buf_config) {
             if (buf) {
-              fused_sweep_kernel<L.value, EQ.value, CO.value, BC.value, ST, true, nums>
+              fused_sweep_kernel<L.value, EQ.value, CO.value, BC.value, ST, NW, true, nums>
                   <<<nblocks, 256, 0, s>>>(static_cast<const T*>(src), static_cast<T*>(dst), g, c,
                                            strips, items, rows, fmt_src, fmt_dst);
               return hipGetLastError();
             }
           }
-          fused_sweep_kernel<L.value, EQ.value, CO.value, BC.value, ST, false, nums>
+          fused_sweep_kernel<L.value, EQ.value, CO.value, BC.value, ST, NW, false, nums>
               <<<nblocks, 256, 0, s>>>(static_cast<const T*>(src), static_cast<T*>(dst), g, c,
                                        strips, items, rows, fmt_src, fmt_dst);
           return hipGetLastError();
         };
         if (nums && (!fmt_src || !fmt_dst)) return hipErrorInvalidValue;
-        if (levels == K) return go(IC<K>{});
-        hipError_t e = hipErrorInvalidValue;
-        if constexpr (short_fused(CO.value, BC.value)) {
-          unroll<nums ? 1 : 2, K>([&](auto L) {
-            if (levels == L.value) e = go(L);
-          });
-        }
-        return e;
+        return with_strip_waves<ST>(waves, [&](auto WAVES) -> hipError_t {
+          if (levels == K) return go(IC<K>{}, WAVES);
+          hipError_t e = hipErrorInvalidValue;
+          if constexpr (short_fused(CO.value, BC.value)) {
+            unroll<nums ? 1 : 2, K>([&](auto L) {
+              if (levels == L.value) e = go(L, WAVES);
+            });
+          }
+          return e;
+        });
       });
     });
   });
 }
 
 template <int ST>
-hipError_t fused_occupancy_st(int levels, int* blocks) {
+hipError_t fused_occupancy_st(int waves, int levels, int* blocks) {
   constexpr bool nums = stores_numbers(LB_COLL_OREG, LB_BC_PERIODIC, ST);
-  auto occ = [&](auto L) {
+  auto occ = [&](auto L, auto NW) {
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(
         blocks,
         reinterpret_cast<const void*>(&fused_sweep_kernel<L.value, LB_EQ_GUIDED, LB_COLL_OREG,
-                                                          LB_BC_PERIODIC, ST, false, nums>),
+                                                          LB_BC_PERIODIC, ST, NW.value, false, nums>),
         256, 0);
   };
-  hipError_t e = hipErrorInvalidValue;
-  unroll<nums ? 1 : 2, FusedLevels<ST>::K + 1>([&](auto L) {
-    if (levels == L.value) e = occ(L);
+  return with_strip_waves<ST>(waves, [&](auto NW) {
+    hipError_t e = hipErrorInvalidValue;
+    unroll<nums ? 1 : 2, FusedLevels<ST>::K + 1>([&](auto L) {
+      if (levels == L.value) e = occ(L, NW);
+    });
+    return e;
   });
-  return e;
 }
 
 }  // namespace oreg

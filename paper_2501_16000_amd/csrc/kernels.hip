@@ -513,43 +513,33 @@ bool fused_levels_available(int coll, int bc, int st, int levels) {
 }
 
 hipError_t launch_fused_sweep(int eq, int coll, int bc, int st, const void* src, void* dst,
-                              const Geometry& g, const Coef64& c, int rows, int levels,
+                              const Geometry& g, const Coef64& c, int waves, int rows, int levels,
                               const unsigned int* fmt_src, unsigned int* fmt_dst,
                               hipStream_t s) {
   if (rows < 3 || rows % 3 != 0) return hipErrorInvalidValue;
   if (!fused_levels_available(coll, bc, st, levels)) return hipErrorInvalidValue;
   return with_storage(st, [&](auto ST) {
-    return fused_launch_st<ST.value>(eq, coll, bc, src, dst, g, c, rows, levels, fmt_src,
+    return fused_launch_st<ST.value>(eq, coll, bc, src, dst, g, c, waves, rows, levels, fmt_src,
                                      fmt_dst, s);
   });
 }
 
-FusedShape fused_shape(int st, int levels) {
+FusedShape fused_shape(int st, int waves, int levels) {
   FusedShape sh{0, 0};
   int dev = 0, cus = 0, blocks = 0;
   if (hipGetDevice(&dev) != hipSuccess) return sh;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return sh;
   const hipError_t e =
-      with_storage(st, [&](auto ST) { return fused_occupancy_st<ST.value>(levels, &blocks); });
+      with_storage(st, [&](auto ST) { return fused_occupancy_st<ST.value>(waves, levels, &blocks); });
   if (e != hipSuccess) return sh;
   sh.simds = cus * 4;
   sh.waves_per_simd = blocks;  // 256-thread workgroups: one wavefront per SIMD each
   return sh;
 }
 
-int fused_wavefronts(int st) {
-  switch (st) {
-    case LB_F64: return FusedLevels<LB_F64>::NW;
-    case LB_F32S: return FusedLevels<LB_F32S>::NW;
-    case LB_F16S: return FusedLevels<LB_F16S>::NW;
-    case LB_BF16S: return FusedLevels<LB_BF16S>::NW;
-    default: return 1;
-  }
-}
-
-double fused_cost(int st, int nx, int ny, int H, const FusedShape& sh, int K) {
-  const int NW = fused_wavefronts(st), W = 64 * NW - 2 * K;
+double fused_cost(int NW, int nx, int ny, int H, const FusedShape& sh, int K) {
+  const int W = 64 * NW - 2 * K;
   const int64_t strips = (nx + W - 1) / W;
   // a work item takes NW wavefronts, one on each of NW SIMDs
   const int64_t items = strips * ((ny + H - 1) / H) * NW;
@@ -559,24 +549,26 @@ double fused_cost(int st, int nx, int ny, int H, const FusedShape& sh, int K) {
   // Throughput of a SIMD against that of one wavefront on it.
   const double gain = NW == 1        ? 1.0 + 0.08 * (double)(resident - 1)
                       : resident < 3 ? 0.5 + 0.5 * (double)resident
-                                     : 1.75;
+                      : resident < 4 ? 1.75
+                                     : 1.87;
   return (double)w / gain * work;
 }
 
-int fused_rows(int st, int nx, int ny, const FusedShape& sh, int levels) {
+int fused_rows(int waves, int nx, int ny, const FusedShape& sh, int levels) {
   if (sh.simds <= 0 || sh.waves_per_simd <= 0) return kFusedRowsDefault;
   // One wavefront per SIMD already runs a wavefront's own strip near the SIMD's
   // issue limit (measured: a second one adds 6-11 %); wavefronts that share a
-  // strip wait for each other, and a second workgroup adds 52 %, a third and a
-  // fourth 75 % (F32S, 4096^2 in 411, 138, 105 and 69 rows: 139, 64.5, 65.3 and
-  // 61.1 us per step).  A launch takes about w wavefront-times by that rate, w = ceil(work items / SIMDs), and one wavefront's time
+  // strip wait for each other, and a second workgroup adds 52 %, a third 75 % (F32S,
+  // 4096^2 in 411, 138 and 105 rows: 139, 64.5 and 65.3 us per step), a fourth 87 %
+  // (BF16S, 6001 x 3000 in 102 and 75 rows: 69.0 and 64.8; 4096^2 in 93 and 69:
+  // 63.6 and 59.7).  A launch takes about w wavefront-times by that rate, w = ceil(work items / SIMDs), and one wavefront's time
   // follows its row collisions, K (H + 2K) - K (K + 1), plus a start-up of
   // about 2K.  H (a multiple of 3) minimises the modelled launch time.
   const int hmax = ny < 3 * 1024 ? (ny + 2) / 3 * 3 : 3 * 1024;
   int best = 3;
   double best_cost = -1;
   for (int H = 3; H <= hmax; H += 3) {
-    const double c = fused_cost(st, nx, ny, H, sh, levels);
+    const double c = fused_cost(waves, nx, ny, H, sh, levels);
     if (best_cost < 0 || c < best_cost) {
       best_cost = c;
       best = H;

@@ -36,9 +36,6 @@ int64_t sweep_work_items(int st, int nx, int ny);
 // Time steps one fused launch advances for a storage format.
 int fused_levels(int st);
 
-// Wavefronts that sweep one strip of a fused launch together (1 or 4).
-int fused_wavefronts(int st);
-
 // Whether strip launches of this configuration store the five numbers of a
 // node (d2q9.hpp: Params) instead of its populations: periodic OReg in F64.  A
 // device flag per buffer then says what it holds (0: populations, as after an
@@ -53,27 +50,29 @@ bool fused_numbers(int coll, int bc, int st);
 bool fused_levels_available(int coll, int bc, int st, int levels);
 
 // `levels` time steps in one launch: src -> dst; each column strip (of one
-// wavefront, or of a whole workgroup: fused_wavefronts) produces `rows` (a
-// multiple of 3) output rows.
+// wavefront, or of a workgroup of four: `waves`, see plan_strips) produces
+// `rows` (a multiple of 3) output rows.
 hipError_t launch_fused_sweep(int eq, int coll, int bc, int st, const void* src, void* dst,
-                              const Geometry& g, const Coef64& c, int rows, int levels,
+                              const Geometry& g, const Coef64& c, int waves, int rows, int levels,
                               const unsigned int* fmt_src, unsigned int* fmt_dst,
                               hipStream_t s);
 
 // SIMDs of the current device and wavefronts of the `levels`-step fused sweep
-// for storage st that one SIMD holds at once (zeros if the query fails).
+// for storage st, with strips of `waves` wavefronts, that one SIMD holds at once
+// (zeros if the query fails).
 struct FusedShape {
   int simds;
   int waves_per_simd;
 };
-FusedShape fused_shape(int st, int levels);
+FusedShape fused_shape(int st, int waves, int levels);
 
 // Modelled time of one K-step fused launch on an nx x ny lattice with H
-// output rows per strip, in row-collision units of one wavefront.
-double fused_cost(int st, int nx, int ny, int H, const FusedShape& sh, int K);
+// output rows per strip of `waves` wavefronts, in row-collision units of one
+// wavefront.
+double fused_cost(int waves, int nx, int ny, int H, const FusedShape& sh, int K);
 
 // Output rows per strip (a multiple of 3) that minimise fused_cost.
-int fused_rows(int st, int nx, int ny, const FusedShape& sh, int levels);
+int fused_rows(int waves, int nx, int ny, const FusedShape& sh, int levels);
 
 // `levels` time steps in one launch of the tile sweep (tile.hip) or the block
 // sweep (block.hip): src -> dst.

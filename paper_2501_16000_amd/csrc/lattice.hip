@@ -28,7 +28,7 @@ struct lb_lattice {
   size_t elem = 8;                    // bytes per stored population
   Geometry geo{};
   int fused_rows[8] = {};             // output rows per strip of fused launches, by step count
-  bool strips = false;                // multi-step launches use the strip pipeline
+  int strips = 0;                     // wavefronts per strip of the strip pipeline; 0: not used
   int cus = 256;                      // compute units of the device
   StepPlan best;                      // the multi-step launch with the least time per step
   StepPlan exact[kPlanLevels + 1];    // plans for launches of exactly L steps (us = 0: not made yet)
@@ -304,8 +304,8 @@ lb_status lb_create_ex(const lb_options* opt, lb_lattice** out) {
   if (h->strips) {
     for (int L = 1; L <= fused_levels(h->opt.storage); ++L)
       if (fused_levels_available(h->opt.collision, h->opt.boundary_x, h->opt.storage, L))
-        h->fused_rows[L] = fused_rows(h->opt.storage, h->geo.nx, h->geo.ny,
-                                      fused_shape(h->opt.storage, L), L);
+        h->fused_rows[L] = fused_rows(h->strips, h->geo.nx, h->geo.ny,
+                                      fused_shape(h->opt.storage, h->strips, L), L);
   } else {
     h->best = plan_best(h->opt.storage, h->geo.nx, h->geo.ny, h->cus);
   }
@@ -379,7 +379,7 @@ lb_status lb_step(lb_lattice* h, int64_t n) {
   auto strip = [&](int L) {
     const hipError_t e = launch_fused_sweep(
         h->opt.equilibrium, h->opt.collision, h->opt.boundary_x, h->opt.storage, h->buf[h->cur],
-        h->buf[1 - h->cur], h->geo, h->coef, h->fused_rows[L], L, h->fmt(h->cur),
+        h->buf[1 - h->cur], h->geo, h->coef, h->strips, h->fused_rows[L], L, h->fmt(h->cur),
         h->fmt(1 - h->cur), h->stream);
     if (e == hipSuccess) done(L);
     return e;

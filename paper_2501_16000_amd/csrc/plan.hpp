@@ -321,7 +321,8 @@ inline bool plan_flat(int st, int nx, int ny) {
   return std::min(nx, ny) <= (st == LB_F16S ? 64 : 128);
 }
 
-// Whether the strip pipeline (fused_impl.hpp) advances this lattice.  A strip
+// Wavefronts per strip of the strip pipeline (fused_impl.hpp: 1 or 4) if it
+// advances this lattice, 0 if it does not.  A strip
 // pays for its halo rows once per strip, a block once per block, so strips
 // have the smaller halo share where a lattice fills the chip with long ones;
 // below that their pipeline fill (2 K row steps per launch) and the uneven last
@@ -347,12 +348,29 @@ inline bool plan_flat(int st, int nx, int ny) {
 // run in few rounds, and strips that store populations (walls, BGK) at others
 // than strips of five numbers (BGK 23685 x 19 4.8 : 4.0, walls 107143 x 14 12.4 :
 // 14.5).
-inline bool plan_strips(int st, int nx, int ny, int coll = LB_COLL_OREG,
+// The strips of four wavefronts store 244 columns; where a row fills the last one
+// badly, the 16-bit formats take strips of one wavefront (52 columns), and F32S,
+// which has none, blocks.  us per step, four : one wavefronts (and with three
+// lattices on three streams), by the share of columns that hold nodes: F16S 48 x
+// 250001 (0.20) 179 : 48; 300 x 20001 (0.61) 32.9 : 24.5; 600 x 10001 (0.82) 26.6
+// : 24.1 (21.5 : 22.4); 1500 x 12001 (0.88) 64.5 : 62.0 (57.5 : 60.4); 4096^2
+// (0.99) 54.9 : 59.0 (48.9 : 56.5); BF16S 1500 x 12001 75.4 : 65.3 (61.8 : 62.9);
+// 2048 x 4096 (0.93) 36.9 : 32.5 (28.6 : 29.9); 4096^2 64.0 : 61.2 (52.8 : 58.5);
+// few rows: 250001 x 24 28.8 : 25.2 (21.0 : 23.2), x 48 52.1 : 45.9 (43.1 : 44.0),
+// 93751 x 64 29.1 : 26.7 (23.3 : 22.8).
+// F32S 48 x 166667, strips of four against blocks: 109 : 36.
+inline int plan_strips(int st, int nx, int ny, int coll = LB_COLL_OREG,
                         int bc = LB_BC_PERIODIC) {
   const int64_t nodes = (int64_t)nx * ny;
-  if (st != LB_F64) return nodes >= 4500000 && nx > 36 && ny >= 20;
+  if (st != LB_F64) {
+    if (nodes < 4500000 || nx <= 36 || ny < 20) return 0;
+    const double fill = nx / (244.0 * ((nx + 243) / 244));
+    if (st == LB_F32S) return fill < 0.8 ? 0 : 4;
+    if (st == LB_F16S) return fill < 0.85 ? 1 : 4;
+    return fill < 0.9 || (ny >= 28 && ny < 100) ? 1 : 4;
+  }
   if (nodes < 300000 || nx < (nodes >= 4000000 ? 28 : nodes >= 1000000 ? 32 : nodes >= 800000 ? 36 : 37))
-    return false;
+    return 0;
   if (coll == LB_COLL_BGK) return ny >= (nodes >= 1000000 ? 12 : 16);
   if (bc == LB_BC_BOUNCEBACK) return ny >= (nodes >= 4000000 ? 16 : 20);
   return ny >= (nodes >= 1000000 ? 12 : nodes >= 800000 ? 14 : 20);

@@ -1,5 +1,6 @@
 // Halos and unused lanes of the plans of lattices of a million nodes and more: no
-// plan computes more than three nodes for each one that it stores.
+// plan computes more than three nodes for each one that it stores, and no strips
+// leave more than half of their columns empty.
 #include <cstdio>
 #include <cstdlib>
 
@@ -16,7 +17,16 @@ int main() {
         const int length = (int)(nodes / side) + 1;
         for (int flip = 0; flip < 2; ++flip) {
           const int nx = flip ? side : length, ny = flip ? length : side;
-          if (plan_strips(st, nx, ny)) continue;
+          // strips: the share of their columns that hold nodes
+          if (const int waves = plan_strips(st, nx, ny)) {
+            const int w = 64 * waves - (st == 0 ? 14 : 12);
+            const double fill = nx / ((double)w * ((nx + w - 1) / w));
+            if (fill < 0.5) {
+              std::printf("FAIL storage %d, %d x %d: strips %.2f full\n", st, nx, ny, fill);
+              return 1;
+            }
+            continue;
+          }
           const StepPlan p = plan_best(st, nx, ny, 256);
           double computed = 0;
           if (p.kind == StepKind::tile) computed = (double)p.tile.tx * p.tile.ty * p.tile.rx * p.tile.ry;

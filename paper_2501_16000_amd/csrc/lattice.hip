@@ -393,20 +393,14 @@ lb_status lb_step(lb_lattice* h, int64_t n) {
       has_strip(2));
   if (h->strips && (h->numbers || h->opt.fuse_steps != 1) && has_strip(2)) {
     // Strip launches of any length (periodic OReg).  Lattices stored as numbers
-    // take the steps evenly: launches of one to four steps cost the same at 4096^2
-    // (a launch of seven and one of one step 876 us, two of four 662), and below
-    // 4.5 M nodes five steps have the best share of halo and pipeline fill (us per
-    // step of seven / six / five / four steps, one lattice: 700^2 5.2 / 5.1 / 4.6 /
-    // 4.6, 1024^2 7.9 / 7.3 / 7.3 / 7.3, 2048^2 23.7 / 23.7 / 23.2 / 24.7; 4096^2
-    // 83.9 / 83.7 / 86.8 / 90.8).  The others take as many full launches as they
-    // can; a single step of theirs runs by the single-step sweep.
+    // spread the steps evenly over the cheapest number of launches (4096^2: one of
+    // seven and one of one step 876 us, two of four 662; 2048^2, twelve steps: four
+    // launches 369 us, two 270).  The others take as many full launches as they can;
+    // a single step of theirs runs by the single-step sweep.
     const int64_t K = h->opt.fuse_steps == 1 ? 1 : levels;
-    const int64_t most = K > 5 && h->numbers && h->geo.plane < 4500000 ? 5 : K;
-    const int64_t least = (n + K - 1) / K;
-    int64_t launches = launches_for(n, least == 1 ? 1 : (n + most - 1) / most, swap);
-    const bool full = !h->numbers && launches == least;
+    int64_t launches = h->numbers ? number_launches(n, (int)K, h->geo.plane, swap) : (n + K - 1) / K;
     for (; launches > 0; --launches) {
-      const int L = (int)(full ? std::min(K, left) : (left + launches - 1) / launches);
+      const int L = (int)(h->numbers ? (left + launches - 1) / launches : std::min(K, left));
       if (!has_strip(L)) break;
       HIP_TRY(h, strip(L));
     }
@@ -428,8 +422,13 @@ lb_status lb_step(lb_lattice* h, int64_t n) {
     for (; left > launches; --launches) HIP_TRY(h, planned((int)((left + launches - 1) / launches)));
   } else if (h->opt.fuse_steps != 1 && h->best.us >= 0) {
     // Tile and block launches: the steps in as few launches as the best plan
-    // needs, spread evenly over them.
-    int64_t launches = launches_for(n, (n + h->best.levels - 1) / h->best.levels, swap);
+    // needs, spread evenly over them.  Where the last one would leave the state in
+    // the wrong buffer, one more or, where longer launches are cheaper, one fewer
+    // (520^2 F64, seven steps: three launches 28.6 us, one 24).
+    const double single = 2.5 + 18 * (double)h->elem * h->geo.plane / 5e6;  // us of a sweep at 5 TB/s
+    int64_t launches = launches_for(n, (n + h->best.levels - 1) / h->best.levels, swap, [&](int L) {
+      return L == 1 ? single : L <= kPlanLevels && has_plan(L) ? step_plan(h, L).us : -1.0;
+    });
     for (; left > launches; --launches) {
       const int L = (int)((left + launches - 1) / launches);
       if (!has_plan(L)) break;

@@ -440,9 +440,49 @@ inline bool swaps_buffers(int64_t n, bool fused, int K, bool remainder) {
 }
 constexpr int64_t kFusedFrom = 48 * 48;
 
-// At least m launches for n steps, as many as end in the right buffer.
-inline int64_t launches_for(int64_t n, int64_t m, bool swap) {
-  return ((m & 1) != 0) == swap ? m : m < n ? m + 1 : m - 1;
+// Time of n steps spread evenly over m launches, us(L) being that of one of L
+// steps; < 0 if there is no launch of that many (us(L) < 0).
+template <class Us>
+inline double spread_us(int64_t n, int64_t m, Us&& us) {
+  const int64_t q = n / m, longer = n % m;
+  const double a = longer > 0 ? us((int)(q + 1)) : 0.0, b = us((int)q);
+  return a < 0 || b < 0 ? -1 : a * longer + b * (m - longer);
+}
+
+// Launches for n steps: m, or where they would end in the wrong buffer the
+// cheaper of one launch fewer and one more.
+template <class Us>
+inline int64_t launches_for(int64_t n, int64_t m, bool swap, Us&& us) {
+  if (((m & 1) != 0) == swap) return m;
+  if (m >= n) return m - 1;
+  if (m <= 1) return m + 1;
+  const double fewer = spread_us(n, m - 1, us), more = spread_us(n, m + 1, us);
+  return fewer >= 0 && (more < 0 || fewer <= more) ? m - 1 : m + 1;
+}
+
+// Launches of at most K steps for n steps of a lattice stored as numbers: the
+// cheapest count that ends in the right buffer.  A launch of 1 .. 7 steps takes,
+// in units of one of four (us of that one: 560^2 13.4, 1024^2 27, 1700^2 61,
+// 2048^2 93, 4096^2 336), 0.6, 0.7, 0.8, 1, 1.2, 1.5 and 1.8 while both buffers
+// fit the 256 MB cache, where the steps' arithmetic shows from the first on (1.3, 1.7
+// and 2 for the longest on lattices of a few strips per CU, whose halo rows then
+// weigh more), and 0.9, 0.9, 0.95, 1, 1.2, 1.4 and 1.66 beyond, where
+// memory traffic hides up to four steps.
+inline int64_t number_launches(int64_t n, int K, int64_t nodes, bool swap) {
+  static constexpr double kSmall[8] = {0, 0.58, 0.67, 0.8, 1, 1.3, 1.7, 2.0};
+  static constexpr double kCached[8] = {0, 0.58, 0.66, 0.79, 1, 1.22, 1.5, 1.8};
+  static constexpr double kStreamed[8] = {0, 0.9, 0.9, 0.94, 1, 1.19, 1.42, 1.66};
+  const double* const cost = nodes < 600000 ? kSmall : 80 * nodes < 256000000 ? kCached : kStreamed;
+  const int64_t least = (n + K - 1) / K;
+  int64_t best = n;
+  double best_cost = -1;
+  for (int l = K; l >= 1; --l)  // counts around those of launches of l steps each
+    for (int64_t m = std::max(least, n / l - 1); m <= std::min(n, n / l + 2); ++m) {
+      if (((m & 1) != 0) != swap) continue;
+      const double c = spread_us(n, m, [&](int L) { return cost[L]; });
+      if (best_cost < 0 || c < best_cost || (c == best_cost && m < best)) best_cost = c, best = m;
+    }
+  return best;
 }
 
 // Server launches (serve.hip) advance every resident lattice up to K steps, so

@@ -29,6 +29,10 @@ def test_large_lattices_compute_few_nodes_twice(tmp_path):
     assert int(run_check(tmp_path, "plan_waste_check").split()[1].strip(",")) > 1000
 
 
+def test_launch_counts(tmp_path):
+    assert int(run_check(tmp_path, "launch_count_check").split()[1]) > 5000
+
+
 def test_wrap_up_to_the_longest_side(tmp_path):
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
     if not os.path.exists(hipcc):

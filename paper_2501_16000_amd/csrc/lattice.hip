@@ -42,7 +42,7 @@ struct lb_lattice {
   bool numbers = false;               // steps store five numbers per node (see fused_numbers)
   // Format flag of buffer b (null where every buffer holds populations).
   unsigned int* fmt(int b) const { return numbers ? counter + 1 + b : nullptr; }
-  PinnedPieces pieces;                // for copies from and to the caller's arrays
+  PinnedPieces pieces;                // for copies to the caller's arrays
   std::string err;
 };
 
@@ -554,9 +554,9 @@ lb_status lb_diagnostics(lb_lattice* h, double out[6]) {
   double* result = h->aux + kDiagBlocks * 6;
   HIP_TRY(h, launch_diagnostics(h->opt.equilibrium, h->opt.storage, h->buf[h->cur], h->aux, result,
                                 h->geo, h->coef, h->theta_energy, h->fmt(h->cur), h->stream));
-  HIP_TRY(h, hipStreamSynchronize(h->stream));  // see HostTransfer::to_host
-  HIP_TRY(h, hipMemcpyAsync(out, result, 6 * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-  HIP_TRY(h, hipStreamSynchronize(h->stream));
+  HostTransfer copy(h->pieces, h->stream, 6 * sizeof(double));
+  HIP_TRY(h, copy.to_host(out, result, 6 * sizeof(double)));
+  HIP_TRY(h, copy.finish());
   return LB_OK;
 }
 
@@ -586,10 +586,10 @@ lb_status lb_density_profile(lb_lattice* h, double* out) {
   if (st != LB_OK) return st;
   HIP_TRY(h, launch_profile(h->opt.equilibrium, h->opt.storage, h->buf[h->cur], h->tmp,
                             h->tmp + h->geo.nx, h->geo, h->coef, h->fmt(h->cur), h->stream));
-  HIP_TRY(h, hipStreamSynchronize(h->stream));  // see HostTransfer::to_host
-  HIP_TRY(h, hipMemcpyAsync(out, h->tmp, (size_t)h->geo.nx * sizeof(double),
-                            hipMemcpyDeviceToHost, h->stream));
-  HIP_TRY(h, hipStreamSynchronize(h->stream));
+  const size_t bytes = (size_t)h->geo.nx * sizeof(double);
+  HostTransfer copy(h->pieces, h->stream, bytes);
+  HIP_TRY(h, copy.to_host(out, h->tmp, bytes));
+  HIP_TRY(h, copy.finish());
   return LB_OK;
 }
 

@@ -34,7 +34,7 @@ struct lb3_lattice {
   MarchShape shape{};
   // Format flag of buffer b (null where every buffer holds populations).
   unsigned int* fmt(int b) const { return march ? counter + 1 + b : nullptr; }
-  PinnedPieces pieces;                // for copies from and to the caller's arrays
+  PinnedPieces pieces;                // for copies to the caller's arrays
   std::string err;
 };
 
@@ -421,9 +421,9 @@ lb_status lb3_diagnostics(lb3_lattice* h, double out[7]) {
     HIP_TRY(h, launch_diagnostics3(h->opt.storage, h->buf[h->cur], h->aux, result, h->geo, h->coef,
                                    h->coef.theta, h->stream));
   }
-  HIP_TRY(h, hipStreamSynchronize(h->stream));  // see HostTransfer::to_host
-  HIP_TRY(h, hipMemcpyAsync(out, result, 7 * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-  HIP_TRY(h, hipStreamSynchronize(h->stream));
+  HostTransfer copy(h->pieces, h->stream, 7 * sizeof(double));
+  HIP_TRY(h, copy.to_host(out, result, 7 * sizeof(double)));
+  HIP_TRY(h, copy.finish());
   return LB_OK;
 }
 

@@ -318,7 +318,7 @@ lb_status lb_init(lb_lattice* h, const double* rho, const double* ux, const doub
   if (!rho || !ux || !uy) return fail(h, LB_EINVAL, "field pointer is NULL");
   const int64_t n = h->geo.plane;
   const double* const u[2] = {ux, uy};
-  for (int64_t i = first_suspect_fields(rho, u, 2, n); i < n; ++i) {
+  for (int64_t i = first_suspect_fields(rho, u, n); i < n; ++i) {
     if (!is_finite(rho[i]) || !is_finite(ux[i]) || !is_finite(uy[i]) || !(rho[i] > 0.0))
       return fail(h, LB_EINVAL, "node %lld has a non-finite field or rho <= 0", (long long)i);
   }

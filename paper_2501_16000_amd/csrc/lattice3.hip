@@ -260,7 +260,7 @@ lb_status lb3_init(lb3_lattice* h, const double* rho, const double* ux, const do
   if (st != LB_OK) return st;
   const int64_t n = h->geo.cells;
   const double* const u[3] = {ux, uy, uz};
-  for (int64_t i = first_suspect_fields(rho, u, 3, n); i < n; ++i) {
+  for (int64_t i = first_suspect_fields(rho, u, n); i < n; ++i) {
     if (!is_finite(rho[i]) || !is_finite(ux[i]) || !is_finite(uy[i]) || !is_finite(uz[i]) ||
         !(rho[i] > 0.0))
       return fail(h, LB_EINVAL, "node %lld has a non-finite field or rho <= 0", (long long)i);

@@ -160,17 +160,21 @@ class HostTransfer {
 
 // First node from which fields have to be looked at one by one (one with a value
 // that is not finite or rho <= 0 is among the next kCheck nodes), or n.  Without
-// an early exit per node the check runs on vectors.
+// an early exit per node the check runs on vectors.  All arrays in one loop: one
+// after the other in blocks of kCheck, the check waited for memory (12.0 ms for
+// 2048^2 nodes, 8.7 with an exit per node, 6.4 like this).
 constexpr int64_t kCheck = 1024;
-inline int64_t first_suspect_fields(const double* rho, const double* const* u, int d, int64_t n) {
+template <int D>
+inline int64_t first_suspect_fields(const double* rho, const double* const (&u)[D], int64_t n) {
   constexpr double most = std::numeric_limits<double>::max();
   for (int64_t c0 = 0; c0 < n; c0 += kCheck) {
-    const int64_t m = std::min(kCheck, n - c0);
+    const int64_t end = std::min(c0 + kCheck, n);
     int bad = 0;
-    for (int64_t c = c0; c < c0 + m; ++c) bad |= (int)!(rho[c] > 0.0) | (int)!(rho[c] <= most);
-    for (int a = 0; a < d; ++a) {
-      const double* const v = u[a];
-      for (int64_t c = c0; c < c0 + m; ++c) bad |= (int)!(std::fabs(v[c]) <= most);
+    for (int64_t c = c0; c < end; ++c) {
+      int b = (int)!(rho[c] > 0.0) | (int)!(rho[c] <= most);
+#pragma unroll
+      for (int a = 0; a < D; ++a) b |= (int)!(std::fabs(u[a][c]) <= most);
+      bad |= b;
     }
     if (bad) return c0;
   }

@@ -63,14 +63,15 @@ __host__ __device__ __forceinline__ int wrap_sub(int v, int c, int n) {
 // ---------------------------------------------------------------- sweep --
 // Most wavefronts per workgroup of the sweep, per storage (measured on 256^3:
 // 8 for F64 and 16 for F32S beat 4 by 2 %; 4 is best for the 16-bit formats).
-// Smaller boxes take four (sweep3_waves).
+// Smaller boxes take fewer (sweep3_waves).
 template <int ST> struct Sweep3Waves { static constexpr int N = 4; };
 template <> struct Sweep3Waves<LB_F64> { static constexpr int N = 8; };
 template <> struct Sweep3Waves<LB_F32S> { static constexpr int N = 16; };
 
 // PACKED: a wavefront takes 64 consecutive nodes of the box instead of a segment
-// of one x-row (sweep3_packed); mx, my: division by nx and ny (magic).
-template <int EQ, int COLL, int ST, bool PACKED>
+// of one x-row (sweep3_packed); mx, my: division by nx and ny (magic).  ORDERED:
+// all loads before the first use (sweep3_ordered).
+template <int EQ, int COLL, int ST, bool PACKED, bool ORDERED>
 __global__ __launch_bounds__(64 * Sweep3Waves<ST>::N) void sweep3_kernel(
     const typename Storage<ST>::T* __restrict__ src, typename Storage<ST>::T* __restrict__ dst,
     Geometry3 g, Coef64 c, unsigned int nseg, unsigned int tasks, unsigned int mx,
@@ -134,9 +135,7 @@ __global__ __launch_bounds__(64 * Sweep3Waves<ST>::N) void sweep3_kernel(
     });
     q = dst + rows[1][1] + x;
   }
-  // All 27 loads before the first use: without the ordering point the compiler
-  // paired every F16S load with its conversion and waited for each in turn.
-  __builtin_amdgcn_sched_barrier(0);
+  if constexpr (ORDERED) __builtin_amdgcn_sched_barrier(0);
   R f[27];
 #pragma unroll
   for (int i = 0; i < 27; ++i) f[i] = S::load(raw[i]);
@@ -337,17 +336,35 @@ unsigned int blocks_for(int64_t n) { return (unsigned int)((n + kThreads - 1) / 
 
 }  // namespace
 
-// Wavefronts per workgroup.  Boxes of less than 8 M nodes run faster with
-// four, which spread small boxes over more CUs (us per step, F64 eight / four:
-// 32^3 6.9 / 5.6, 128^3 189 / 173; F32S sixteen / four: 32^3 7.8 / 4.3, 128^3
-// 98 / 87).
-unsigned int sweep3_waves(const Geometry3& g, unsigned int most) {
-  return g.cells < (8 << 20) ? std::min(4u, most) : most;
-}
-
 // ------------------------------------------------------------ launchers --
 int64_t sweep3_tasks(const Geometry3& g) {
   return ((int64_t)g.nx + 63) / 64 * g.ny * g.nz;
+}
+
+// F64 rows that take one round of wavefronts, two per SIMD (2048), but more than
+// one per SIMD.  They run fastest in workgroups of eight, one per CU, and with the
+// loads left to the compiler: us per step, four and ordered : eight and free, 41^3
+// 9.8 : 9.2, 45^3 10.8 : 9.5, 64 x 32 x 48 10.6 : 8.8, 100 x 30 x 25 10.3 : 8.6.
+bool sweep3_one_round(const Geometry3& g, int elem) {
+  return elem == 8 && sweep3_tasks(g) > 1024 && sweep3_tasks(g) <= 2048;
+}
+
+// Wavefronts per workgroup.  Other boxes of less than 8 M nodes run faster with
+// four, which spread small boxes over more CUs (us per step, F64 eight / four:
+// 32^3 6.9 / 5.6, 128^3 189 / 173; F32S sixteen / four: 32^3 7.8 / 4.3, 128^3
+// 98 / 87).
+unsigned int sweep3_waves(const Geometry3& g, unsigned int most, bool one_round) {
+  return !one_round && g.cells < (8 << 20) ? std::min(4u, most) : most;
+}
+
+// Whether all 27 loads of a node come before their first use.  Left to itself the
+// compiler pairs every F16S load with its conversion and waits for each in turn
+// (64^3 16.4 us per step, ordered 7.7).  F64 has no conversions: ordered loads
+// help only where each SIMD has one wavefront at most (free : ordered, 16^3 5.6 :
+// 4.5, 64 x 32 x 30 6.7 : 5.4; 64 x 64 x 40 15.0 : 16.1, 128^3 182 : 179, 256^3
+// 1319 : 1373).
+bool sweep3_ordered(const Geometry3& g, int elem, bool packed) {
+  return packed || elem < 8 || sweep3_tasks(g) <= 1024;
 }
 
 // Whether the sweep packs 64 consecutive nodes of the box into a wavefront.  A
@@ -358,9 +375,13 @@ int64_t sweep3_tasks(const Geometry3& g) {
 // 11.6, 200 x 180 x 160 220 : 124, and with whole segments 128^3 43.7 : 44.5; F64
 // BGK 150^3 357 : 290.  Boxes of too few wavefronts run faster spread over more
 // of them (32^3 F64 3.5 : 4.0, 48 x 40 x 30 5.8 : 5.2; 169 x 20 x 16, 12 % idle,
-// one step and moments 10.6 : 10.8).  Addresses are 32-bit byte
+// one step and moments 10.6 : 10.8), and so do F64 boxes of more nodes than one
+// packed wavefront per SIMD holds (1024 of them) whose rows take one round (40^3
+// 8.9 : 8.4 but 41^3 9.2 : 10.5, 43^3 9.3 : 10.4, 45^3 9.5 : 11.4, 100 x 30 x 25
+// 8.6 : 10.1, 250 x 18 x 18 9.8 : 11.2; 46^3 11.9 : 11.2).  Addresses are 32-bit byte
 // offsets, and __umulhi by ceil(2^32 / n) divides exactly below 2^32 / n.
 bool sweep3_packed(const Geometry3& g, int elem) {
+  if (g.cells > 65536 && sweep3_one_round(g, elem)) return false;
   return g.nx > 1 && g.ny > 1 && g.ny < 65000 && g.cells >= 45000 &&
          g.cells * elem < 4294967296LL &&
          (g.cells < 100000 ? 1.25 : 1.04) * (double)g.cells < 64.0 * (double)sweep3_tasks(g);
@@ -372,19 +393,23 @@ hipError_t launch_sweep3(int eq, int coll, int st, const void* src, void* dst, c
   auto magic = [](int n) { return (unsigned int)((4294967296ULL + n - 1) / (unsigned int)n); };
   return with_storage(st, [&](auto ST) {
     using T = typename Storage<ST.value>::T;
-    const unsigned int W = sweep3_waves(g, Sweep3Waves<ST.value>::N);
-    const bool packed = sweep3_packed(g, (int)sizeof(T));
+    constexpr int E = (int)sizeof(T);
+    const bool packed = sweep3_packed(g, E), ordered = sweep3_ordered(g, E, packed);
+    const unsigned int W =
+        sweep3_waves(g, Sweep3Waves<ST.value>::N, !packed && sweep3_one_round(g, E));
     const unsigned int tasks = (unsigned int)(packed ? (g.cells + 63) / 64 : sweep3_tasks(g));
     const unsigned int nblocks = (tasks + W - 1) / W;
     return with_eq(eq, [&](auto EQ) {
       return with_coll(coll, [&](auto CO) {
-        auto go = [&](auto PACKED) {
-          sweep3_kernel<EQ.value, CO.value, ST.value, PACKED.value><<<nblocks, 64 * W, 0, s>>>(
-              static_cast<const T*>(src), static_cast<T*>(dst), g, c, nseg, tasks, magic(g.nx),
-              magic(g.ny));
+        auto go = [&](auto PACKED, auto ORDERED) {
+          sweep3_kernel<EQ.value, CO.value, ST.value, PACKED.value, ORDERED.value>
+              <<<nblocks, 64 * W, 0, s>>>(static_cast<const T*>(src), static_cast<T*>(dst), g, c,
+                                          nseg, tasks, magic(g.nx), magic(g.ny));
           return hipGetLastError();
         };
-        return packed ? go(IC<1>{}) : go(IC<0>{});
+        if constexpr (E == 8)
+          if (!ordered) return go(IC<0>{}, IC<0>{});
+        return packed ? go(IC<1>{}, IC<1>{}) : go(IC<0>{}, IC<1>{});
       });
     });
   });

@@ -245,7 +245,7 @@ lb_status lb3_create(const lb3_options* opt, lb3_lattice** out) {
   if (e != hipSuccess) return cleanup(hip_fail(nullptr, e, "hipMalloc(counter)"));
   int cus = 256;
   (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  h->march = march_worthwhile(opt->collision, opt->storage, h->geo.cells);
+  h->march = march_worthwhile(opt->collision, opt->storage, h->geo.cells, sweep3_tasks(h->geo));
   if (h->march) {
     h->shape = march_shape(opt->storage, opt->nx, opt->ny, opt->nz, cus);
     h->march = march_shape_ok(h->shape, opt->nx, opt->ny, opt->nz);

@@ -31,6 +31,11 @@ namespace oreg {
 namespace {
 using namespace detail;
 
+// What passes between wavefronts w - 1 and w through LDS, double buffered: pops
+// 4, 7, 8 of the first row of w and pops 2, 5, 6 of the last row of w - 1.
+template <typename R> struct Edge {
+  R up[2][3][64], dn[2][3][64];
+};
 template <int RR, int EQ, int COLL, int BC, int ST>
 __device__ __forceinline__ void block_tile(const typename Storage<ST>::T* __restrict__ src,
                                            typename Storage<ST>::T* __restrict__ dst, int nx,
@@ -40,11 +45,11 @@ __device__ __forceinline__ void block_tile(const typename Storage<ST>::T* __rest
   using S = Storage<ST>;
   using R = typename S::R;
   using T = typename S::T;
-  // Edge rows: pops 4, 7, 8 of a wavefront's first row (read by the
-  // wavefront above) and pops 2, 5, 6 of its last row (read by the one below).
-  __shared__ R up[2][kBlockWaves][3][64], dn[2][kBlockWaves][3][64];
+  static_assert((kBlockWaves + 1) * sizeof(Edge<R>) == block_lds(ST, kBlockWaves));
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  extern __shared__ double edges[];
+  Edge<R>&top = reinterpret_cast<Edge<R>*>(edges)[wv], &bottom = (&top)[1];
   const int h = L - 1, RY = W * RR;
   const int x = wrap_add(X0, lane - h, nx);
   int y = wrap_add(Y0, wv * RR - h, ny);
@@ -99,22 +104,21 @@ __device__ __forceinline__ void block_tile(const typename Storage<ST>::T* __rest
     update(f[r]);
     pin(f[r]);
   }
-  // Wavefronts above and below (the outermost rows of the region read their
-  // own, which only feeds halo rows that are no longer valid).
-  const int wu = wv > 0 ? wv - 1 : 0, wd = wv + 1 < W ? wv + 1 : wv;
+  // The outermost rows of the region read what no wavefront wrote; it would only
+  // feed halo rows that are no longer valid, which are left out below.
   for (int t = 2; t <= L; ++t) {
     const int b = t & 1;
-    up[b][wv][0][lane] = f[0][4];
-    up[b][wv][1][lane] = f[0][7];
-    up[b][wv][2][lane] = f[0][8];
-    dn[b][wv][0][lane] = f[RR - 1][2];
-    dn[b][wv][1][lane] = f[RR - 1][5];
-    dn[b][wv][2][lane] = f[RR - 1][6];
+    top.up[b][0][lane] = f[0][4];
+    top.up[b][1][lane] = f[0][7];
+    top.up[b][2][lane] = f[0][8];
+    bottom.dn[b][0][lane] = f[RR - 1][2];
+    bottom.dn[b][1][lane] = f[RR - 1][5];
+    bottom.dn[b][2][lane] = f[RR - 1][6];
     // One barrier per step: buffer b is written again two steps later, after
     // the barrier that this step's readers reach next.
     __syncthreads();
-    R a2 = dn[b][wu][0][lane], a5 = dn[b][wu][1][lane], a6 = dn[b][wu][2][lane];
-    const R b4 = up[b][wd][0][lane], b7 = up[b][wd][1][lane], b8 = up[b][wd][2][lane];
+    R a2 = top.dn[b][0][lane], a5 = top.dn[b][1][lane], a6 = top.dn[b][2][lane];
+    const R b4 = bottom.up[b][0][lane], b7 = bottom.up[b][1][lane], b8 = bottom.up[b][2][lane];
 #pragma unroll
     for (int r = 0; r < RR; ++r) {
       const int j = wv * RR + r;  // row of the region: valid after t steps in [t - 1, RY - t]
@@ -199,7 +203,8 @@ hipError_t launch_batched_block(int eq, int st, const LatticeDesc* d, const int*
       const int64_t most = launch_items(64 * waves);
       for (int64_t first = 0; first < items; first += most) {
         batched_block_kernel<RR.value, EQ.value, ST.value>
-            <<<(unsigned int)std::min(most, items - first), 64 * waves, 0, s>>>(d, item_map, first, T);
+            <<<(unsigned int)std::min(most, items - first), 64 * waves,
+               block_lds(ST.value, waves), s>>>(d, item_map, first, T);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
       }
@@ -232,7 +237,8 @@ hipError_t launch_block_sweep(int eq, int coll, int bc, int st, const void* src,
         return with_bc(bc, [&](auto BC) -> hipError_t {
           auto go = [&](auto RR) {
             block_kernel<RR.value, EQ.value, CO.value, BC.value, ST.value>
-                <<<(unsigned int)(b.tx * b.ty), 64 * b.waves, 0, s>>>(
+                <<<(unsigned int)(b.tx * b.ty), 64 * b.waves,
+                   block_lds(ST.value, b.waves), s>>>(
                     static_cast<const T*>(src), static_cast<T*>(dst), g, c, b.tx, b.ox, b.oy,
                     levels);
             return hipGetLastError();

@@ -53,6 +53,16 @@ constexpr int block_rows_big(int st) { return st == LB_BF16S ? 6 : 8; }
 constexpr int block_waves_per_simd(int st, int rows) {
   return st == LB_F64 ? (rows == 4 ? 3 : 2) : (rows == 4 ? 7 : 4);
 }
+// LDS of one of its workgroups: what passes between its wavefronts (and both ends),
+// twelve rows of 64 values.
+constexpr int block_lds(int st, int waves) {
+  return (waves + 1) * 12 * 64 * (st == LB_F64 ? 8 : 4);
+}
+// Workgroups of it that one CU holds.
+constexpr int block_fit(int st, int rows, int waves) {
+  return std::max(1, std::min(4 * block_waves_per_simd(st, rows) / waves,
+                              160 * 1024 / block_lds(st, waves)));
+}
 
 enum class StepKind { sweep, tile, block };
 constexpr int kPlanLevels = 128;  // most steps of one launch
@@ -127,7 +137,7 @@ inline double block_us(int st, const BlockShape& b, int L, int cus) {
   // four (62 x 2909: 3.0 us per step in six rows, 2.65 in four, modelled equal).
   if (st == LB_BF16S && b.rows == 6) f.c *= 1.05, f.c1 *= 1.05;
   const int64_t tiles = (int64_t)b.tx * b.ty;
-  const int fit = std::max(1, 4 * block_waves_per_simd(st, b.rows) / b.waves);
+  const int fit = block_fit(st, b.rows, b.waves);
   const int conc = (int)std::min<int64_t>(fit, div_up(tiles, cus));
   const int rounds = div_up(tiles, (int64_t)cus * conc);
   double us = f.t1;
@@ -210,7 +220,7 @@ inline StepPlan best_block(int st, int nx, int ny, int L, int cus) {
     for (int waves = 1; waves <= kBlockWaves; ++waves) {
       if (64 - 2 * (L - 1) < 16 || waves * rows - 2 * (L - 1) < 4) continue;
       const BlockShape b = block_shape(nx, ny, L, waves, rows);
-      const int fit = std::max(1, 4 * block_waves_per_simd(st, rows) / waves);
+      const int fit = block_fit(st, rows, waves);
       const int64_t tiles = (int64_t)b.tx * b.ty;
       // More than one round only with every SIMD equally loaded.
       if (tiles > (int64_t)cus * fit && waves % 4 != 0) continue;
@@ -299,7 +309,7 @@ inline StepPlan best_flat(int st, int nx, int ny, int L, int cus) {
       if (!one_launch(b.tx, b.ty, 64 * waves)) continue;
       double work = 0;
       for (int s = 0; s < L; ++s) work += waves * rows - 2 * s;
-      const int conc = std::max(1, 4 * block_waves_per_simd(st, rows) / waves);
+      const int conc = block_fit(st, rows, waves);
       const double lines = flat_lines(st, 64, waves * rows, false) + flat_lines(st, b.ox, b.oy, false);
       const double us = flat_us(kFlatBlock[st], work, lines, L, conc, (int64_t)b.tx * b.ty, cus);
       if (best.us < 0 || us < best.us) best.kind = StepKind::block, best.us = us, best.block = b;
@@ -381,7 +391,7 @@ inline bool plan_many(int st, int nx, int ny, int cus) {
   using namespace plan_detail;
   const int Lb = block_large_levels(st);
   const StepPlan p = block_large(st, nx, ny, Lb, cus);
-  const int fit = 4 * block_waves_per_simd(st, p.block.rows) / kBlockWaves;
+  const int fit = block_fit(st, p.block.rows, kBlockWaves);
   return 2 * (int64_t)p.block.tx * p.block.ty > (int64_t)3 * cus * fit;
 }
 

@@ -49,7 +49,8 @@ struct BlockShape {
 // per SIMD, six do.
 constexpr int block_rows_small(int) { return 4; }
 constexpr int block_rows_big(int st) { return st == LB_BF16S ? 6 : 8; }
-// Wavefronts of the block sweep that one SIMD holds (from its VGPRs).
+// Wavefronts of the block sweep that one SIMD holds (from its VGPRs; polynomial
+// OReg in four rows of 32-bit arithmetic holds six).
 constexpr int block_waves_per_simd(int st, int rows) {
   return st == LB_F64 ? (rows == 4 ? 3 : 2) : (rows == 4 ? 7 : 4);
 }

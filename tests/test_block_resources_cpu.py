@@ -40,3 +40,22 @@ def test_lds_is_what_the_launch_asks_for(kernels, tmp_path):
     assert len(kernels) > 60
     assert {k: v for k, v in kernels.items() if v["LDS"] or v["ScratchSize"]} == {}
     assert int(run_check(tmp_path, "block_fit_check").split()[1]) == 64
+
+
+def test_registers_leave_the_wavefronts_that_the_plan_counts(kernels, tmp_path):
+    """Periodic BGK in F16S held three wavefronts of eight rows per SIMD, not four.
+    (Polynomial OReg in four rows holds six, modelled as the others' seven.)"""
+    checked = 0
+    for name, v in kernels.items():
+        m = re.search(r"20batched_block_kernelILi(\d)ELi(\d)ELi(\d)E", name)
+        coll = "0"
+        if m:
+            rows, eq, st = m.groups()
+        else:
+            m = re.search(r"12block_kernelILi(\d)ELi(\d)ELi(\d)ELi\dELi(\d)E", name)
+            rows, eq, coll, st = m.groups()
+        count = (3 if rows == "4" else 2) if st == "0" else (7 if rows == "4" else 4)
+        polynomial = rows == "4" and st != "0" and eq == "1" and coll == "0"
+        assert v["Occupancy"] >= count - polynomial, name
+        checked += 1
+    assert checked == len(kernels)

@@ -424,11 +424,15 @@ lb_status lb_step(lb_lattice* h, int64_t n) {
     // Tile and block launches: the steps in as few launches as the best plan
     // needs, spread evenly over them.  Where the last one would leave the state in
     // the wrong buffer, one more or, where longer launches are cheaper, one fewer
-    // (520^2 F64, seven steps: three launches 28.6 us, one 24).
+    // (520^2 F64, seven steps: three launches 28.6 us, one 24).  In FP64 longer
+    // launches of lattices that leave CUs idle have to be clearly cheaper: they take
+    // the CUs of other lattices in flight (24 steps in four launches / two, one
+    // lattice and three in flight: 128^2 26.9 / 24.5 us and 15.6 / 22.3, 200 x 300 39.8 /
+    // 41.3 and 20.9 / 36.7; F32S 128^2 25.8 / 21.8 and 15.7 / 11.9).
     const double single = 2.5 + 18 * (double)h->elem * h->geo.plane / 5e6;  // us of a sweep at 5 TB/s
     int64_t launches = launches_for(n, (n + h->best.levels - 1) / h->best.levels, swap, [&](int L) {
       return L == 1 ? single : L <= kPlanLevels && has_plan(L) ? step_plan(h, L).us : -1.0;
-    });
+    }, h->opt.storage == LB_F64 && h->geo.plane < 262144 ? 0.9 : 1);
     for (; left > launches; --launches) {
       const int L = (int)((left + launches - 1) / launches);
       if (!has_plan(L)) break;

@@ -29,6 +29,8 @@ int main() {
       fail("two launches", n, number_launches(n, 7, 4194304, false), 4194304);
   for (int64_t n : {16, 17, 18})
     if (number_launches(n, 7, 4194304, true) != 3) fail("three launches", n, 0, 4194304);
+  // in cache a launch of six costs more than 1.5 of four
+  if (number_launches(24, 7, 1000000, false) != 6) fail("six launches", 24, 0, 1000000);
   // tile and block launches: us of a launch of L steps
   auto cheap = [](int L) { return L <= 7 ? 10.0 + L : -1.0; };
   auto dear = [](int L) { return L <= 7 ? 1.0 + 10 * L * L : -1.0; };
@@ -36,6 +38,9 @@ int main() {
   if (launches_for(7, 2, true, cheap) != 1) fail("one launch of seven", 7, launches_for(7, 2, true, cheap), 0);
   if (launches_for(7, 2, true, dear) != 3) fail("three launches", 7, launches_for(7, 2, true, dear), 0);
   if (launches_for(7, 2, true, none) != 3) fail("no launch of seven", 7, launches_for(7, 2, true, none), 0);
+  auto even = [](int L) { return 10.0 + 2 * L; };  // one of twelve 34, three of four 54
+  if (launches_for(12, 2, true, even, 0.63) != 1 || launches_for(12, 2, true, even, 0.62) != 3)
+    fail("clearly cheaper", 12, 0, 0);
   if (launches_for(12, 2, false, dear) != 2 || launches_for(2, 2, true, cheap) != 1 ||
       launches_for(9, 1, false, cheap) != 2)
     fail("ends", 0, 0, 0);

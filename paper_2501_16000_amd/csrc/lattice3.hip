@@ -32,6 +32,7 @@ struct lb3_lattice {
   unsigned int* counter = nullptr;    // invalid-input count, then the buffers' format flags
   bool march = false;                 // steps store ten numbers per node (march3.hip)
   MarchShape shape{};
+  MarchShape sums{};                  // of lb3_diagnostics
   // Format flag of buffer b (null where every buffer holds populations).
   unsigned int* fmt(int b) const { return march ? counter + 1 + b : nullptr; }
   PinnedPieces pieces;                // for copies to the caller's arrays
@@ -248,7 +249,9 @@ lb_status lb3_create(const lb3_options* opt, lb3_lattice** out) {
   h->march = march_worthwhile(opt->collision, opt->storage, h->geo.cells, sweep3_tasks(h->geo));
   if (h->march) {
     h->shape = march_shape(opt->storage, opt->nx, opt->ny, opt->nz, cus);
-    h->march = march_shape_ok(h->shape, opt->nx, opt->ny, opt->nz);
+    h->sums = cus == 256 ? h->shape : sums_shape(opt->storage, opt->nx, opt->ny, opt->nz);
+    h->march = march_shape_ok(h->shape, opt->nx, opt->ny, opt->nz) &&
+               march_shape_ok(h->sums, opt->nx, opt->ny, opt->nz);
   }
   *out = h;
   return LB_OK;
@@ -412,9 +415,9 @@ lb_status lb3_diagnostics(lb3_lattice* h, double out[7]) {
     // The partial sums, one set per workgroup, go to the buffer that the next
     // step overwrites: a workgroup has a node or more, of 27 elements.
     double* partials = static_cast<double*>(h->buf[1 - h->cur]);
-    const int groups = h->shape.ntx * h->shape.nty * h->shape.nzc;
+    const int groups = h->sums.ntx * h->sums.nty * h->sums.nzc;
     HIP_TRY(h, launch_march3_sums(h->opt.equilibrium, h->opt.storage, h->buf[h->cur], partials,
-                                  h->fmt(h->cur), h->geo, h->coef, h->coef.theta, h->shape,
+                                  h->fmt(h->cur), h->geo, h->coef, h->coef.theta, h->sums,
                                   h->stream));
     HIP_TRY(h, launch_diagnostics3_final(partials, groups, result, h->stream));
   } else {

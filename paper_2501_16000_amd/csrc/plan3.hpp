@@ -100,4 +100,10 @@ inline MarchShape march_shape(int st, int nx, int ny, int nz, int cus) {
   return best;
 }
 
+// The shape of the diagnostics, whose partial sums are per workgroup: the same on
+// every device (and partition of one), so that their order is.
+inline MarchShape sums_shape(int st, int nx, int ny, int nz) {
+  return march_shape(st, nx, ny, nz, 256);
+}
+
 }  // namespace oreg

@@ -39,6 +39,10 @@ def test_served_sets(tmp_path):
     assert int(out.split()[1]) == 504
 
 
+def test_order_of_box_sums(tmp_path):
+    assert int(run_check(tmp_path, "sums_shape_check").split()[1]) == 7
+
+
 def test_wrap_up_to_the_longest_side(tmp_path):
     hipcc = shutil.which("hipcc") or "/opt/rocm/bin/hipcc"
     if not os.path.exists(hipcc):

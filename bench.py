@@ -39,8 +39,8 @@ BYTES_PER_NODE = {"f64": 144, "f32s": 72, "f16s": 36, "bf16s": 36}
 # populations (plan.hpp plan_strips: from 300,000 nodes).
 NUMBERS_FROM, NUMBER_BYTES = 300000, 80
 # D3Q27 OReg boxes hold ten numbers per node in FP64 and F32S (plan3.hpp
-# march_worthwhile: from 60,000 and 300,000 nodes).
-NUMBERS3_FROM = {"f64": 60000, "f32s": 300000}
+# march_worthwhile: cubes from 46^3 and 300,000 nodes).
+NUMBERS3_FROM = {"f64": 46 ** 3, "f32s": 300000}
 STORAGE_BYTES = {"f64": 8, "f32s": 4, "f16s": 2, "bf16s": 2}
 # Time steps per fused launch (dispatch.hpp FusedLevels) and the algorithmic
 # flops of one guided-equilibrium OReg node update as implemented in
@@ -188,9 +188,8 @@ def time_box(oreg3, torch, n, tau, storage, steps, warmup, fields):
 
 def hbm_side(traffic, alg_bytes, launch_s):
     """HBM view of a fused launch: the algorithmic bytes (the state read and
-    written once per K-step launch: 2 * 9 * sizeof(storage) per node) and the
-    counter bytes of the committed rocprofv3 summary, each over the launch
-    time, against 8 TB/s."""
+    written once per K-step launch: ``launch_bytes``) and the counter bytes of
+    the committed rocprofv3 summary, each over the launch time, against 8 TB/s."""
     out = {"bytes_model": "stored state read and written once per K-step launch",
            "algorithmic_GBs": round(alg_bytes / launch_s / 1e9, 1),
            "algorithmic_frac_of_peak": round(alg_bytes / launch_s / 1e9 / HBM_PEAK_GBS, 4),

@@ -109,8 +109,11 @@ typedef struct lb_options {
                                  registers on middle ones, column strips on
                                  large ones (up to 7 steps per launch for
                                  LB_F64, 6 for the shifted formats);
-                                 1: one sweep launch per time step;
-                                 2: as 0                                       */
+                                 1: one launch per time step (a sweep, or on
+                                 large periodic LB_F64 OReg lattices a strip
+                                 launch);
+                                 2: as 0, but for the launch counts of lattices
+                                 below 48 x 48 nodes (see lb_step)             */
 } lb_options;
 
 /* Defaults: 0 x 0, tau 1, theta 1/3, guided, LB_F64, OReg, periodic, rho0 1,
@@ -149,6 +152,11 @@ lb_status lb_init_device(lb_lattice* h, const double* rho, const double* ux,
    them by f^eq + (1 - 1/tau) f^OReg (Eq. 6), or by the lattice-BGK update of
    Eq. (1).  Enqueue n time steps on the lattice's stream and return
    (asynchronous).
+   A captured call may be replayed if it leaves the state in the buffer where it
+   found it.  With K = 7 (LB_F64) or 6 that is so for an even number of launches:
+   n / K plus, for n % K > 0, one where strips of every length exist (periodic
+   OReg) and n % K otherwise; n with fuse_steps 1, and with fuse_steps 0 below
+   48 x 48 nodes.
    n == 0 is a no-op.  LB_EINVAL for n < 0, LB_ESTATE before init.  With
    check_nonfinite set, waits and returns LB_ENONFINITE if a node holds a
    non-finite population. */

@@ -108,8 +108,7 @@ template <int ST> struct FusedLevels {
 
 // Fused launches of fewer than FusedLevels<ST>::K steps (lb_step's remainder)
 // are compiled for periodic OReg lattices, the configuration the benchmark
-// and the server use; other configurations run a remainder one step per
-// launch.
+// and the server use; other configurations run a remainder as block launches.
 constexpr bool short_fused(int coll, int bc) {
   return coll == LB_COLL_OREG && bc == LB_BC_PERIODIC;
 }

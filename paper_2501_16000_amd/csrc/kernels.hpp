@@ -20,8 +20,9 @@ struct Geometry {
   int64_t plane;  // nx * ny
 };
 
-// Number of workgroups of the diagnostics reduction (fixed: the reduction
-// order, hence the FP64 result, depends only on the lattice size).
+// Most workgroups of the diagnostics reduction.  How many there are, the reduction
+// order and so the FP64 result depend only on the lattice's size and storage and on
+// the format of its buffer, not on the device.
 constexpr int kDiagBlocks = 1024;
 
 // One time step: src -> dst.

@@ -406,11 +406,12 @@ lb_status lb_step(lb_lattice* h, int64_t n) {
     }
   } else if (h->strips && h->opt.fuse_steps != 1) {
     // Strip launches of K steps only.  The remainder runs as block launches, which
-    // read and write the state once where single steps would do so per step
-    // (4096^2, us for 2 .. 6 steps, single steps / one block launch: F64 BGK 870,
-    // 1298, 1730, 2162, 2596 / 573, 581, 606, 718, 814; F32S BGK, 2 .. 5: 394, 591,
-    // 785, 979 / 318, 302, 303, 303; F16S BGK, 2 .. 4: 225, 336, 446 / 167, 199,
-    // 237), spread over the fewest that end in the right buffer.
+    // read and write the state once where single steps would do so per step, spread
+    // over the fewest that end in the right buffer: one for an odd number of steps,
+    // two for four, two of three for six, and two steps as single sweeps (4096^2, us
+    // for 2 .. 6 steps, single steps : so: F64 BGK 859, 1290, 1720, 2150, 2590 : 860,
+    // 577, 1139, 708, 1153; F32S BGK, 2 .. 5: 397, 596, 795, 993 : 397, 304, 644, 305;
+    // F16S BGK 222, 333, 444, 555 : 223, 175, 311, 417).
     const bool swap_rest = swap != (((n / levels) & 1) != 0);
     while (left >= levels) HIP_TRY(h, strip(levels));
     int64_t launches = 1;

@@ -44,8 +44,8 @@ struct BlockShape {
 };
 
 // Rows per wavefront of the block sweep, two sizes per storage: eight rows of
-// nine populations take 250 VGPRs in F64 (two wavefronts per SIMD) and 106 -
-// 119 in F32S and F16S (four); in BF16S eight rows do not fit four wavefronts
+// nine populations take 197 - 250 VGPRs in F64 (two wavefronts per SIMD) and 105 -
+// 111 in F32S and F16S (four); in BF16S eight rows do not fit four wavefronts
 // per SIMD, six do.
 constexpr int block_rows_small(int) { return 4; }
 constexpr int block_rows_big(int st) { return st == LB_BF16S ? 6 : 8; }
@@ -135,7 +135,10 @@ inline double tile_us(int st, const TileShape& t, int L, int cus) {
 inline double block_us(int st, const BlockShape& b, int L, int cus) {
   BlockFit f = kBlockFit[st];
   // BF16S takes its figures from F16S; its six rows measured slower against its
-  // four (62 x 2909: 3.0 us per step in six rows, 2.65 in four, modelled equal).
+  // four than modelled.  Of 24 lattices from 62 x 2909 to 1800 x 900 whose plan the
+  // factor changes, it gains 2 % on one lattice alone and 8 % on three in flight in the
+  // mean (62 x 2909 2.73 -> 2.51 and 1.93 -> 1.59, 1200 x 300 3.32 -> 2.84 and 2.10 ->
+  // 1.71; the other way 1024 x 1100 6.1 -> 6.8 and 4.5 -> 5.1, 777 x 600 3.4 -> 3.6).
   if (st == LB_BF16S && b.rows == 6) f.c *= 1.05, f.c1 *= 1.05;
   const int64_t tiles = (int64_t)b.tx * b.ty;
   const int fit = block_fit(st, b.rows, b.waves);

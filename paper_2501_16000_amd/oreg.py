@@ -159,8 +159,9 @@ class Lattice:
     equilibrium 'guided' | 'poly2', storage 'f64' | 'f32s' | 'f16s' | 'bf16s',
     collision 'oreg' | 'bgk', boundary_x 'periodic' | 'bounceback'.
     ``fuse_steps`` 0 lets ``step`` advance several time steps per launch (kernel
-    and step count chosen from the lattice's size and storage), 1 runs one sweep
-    launch per step, 2 is as 0 (identical results in every case).
+    and step count chosen from the lattice's size and storage), 1 runs one launch
+    per step, 2 is as 0 but for which calls can be captured and replayed on
+    lattices below 48 x 48 (``lb_step`` in oreg.h; identical results in every case).
     ``stream`` is a HIP stream handle (int, 0 = the null stream) or a
     ``torch.cuda.Stream``; None lets the lattice create its own stream.
     """

@@ -39,8 +39,9 @@ inline bool march_shape_ok(const MarchShape& s, int nx, int ny, int nz) {
 // : 11.0, 46^3 (2116) 13.6 : 11.6, 17 x 28 x 200 (5600) 17.5 : 11.0, 64^3 23.5 :
 // 16.8, 256^3 1322 : 552 (and moments 6.4 : 7.9 to 10.3 : 13.0); F32S 17 x 28 x 200
 // 8.7 : 9.5, 64^3 12.5 : 11.8 (and diagnostics then 32 : 38), 100 x 84 x 60 25.5 :
-// 17.8, 256^3 648 : 352.  The 16-bit formats would store ten FP32 numbers (40 bytes) for 27 populations (54), and the march's
-// arithmetic then costs more than the bytes save (256^3 BF16S 376 : 417).
+// 17.8, 256^3 648 : 352.  The 16-bit formats would store ten FP32 numbers (40 bytes)
+// for 27 populations (54), and the march's arithmetic then costs more than the bytes
+// save (256^3 BF16S 376 : 417).
 // BGK keeps all 27 numbers of a node.
 inline bool march_worthwhile(int coll, int st, int64_t cells, int64_t segments = INT64_MAX) {
   if (coll != LB_COLL_OREG) return false;

@@ -8,12 +8,13 @@
 // pages), moments of 2000^2 5.4 -> 3.8 ms.  To the device the runtime's own path
 // is as fast as these pieces (520 us).
 //
-// Small results (sums, profiles, moments of small lattices) go through one pinned
-// block: one wait for the stream, then a copy by the host.  A pageable copy of 48
-// bytes behind one / six / seven launches of 5 us takes 24 / 51 / 79 us in all,
-// with a wait for the stream before it 35 / 61 / 67, through pinned memory 17 / 43
-// / 48 (15 / 42 / 47 without a copy); of 24 KB 36 / 61 / 90, 36 / 63 / 68 and 26 /
-// 52 / 64; of 98 KB 29 / 56 / 84, 30 / 56 / 62 and 29 / 56 / 67.
+// Small results (sums, profiles, moments of the smallest lattices) go through one
+// pinned block: one wait for the stream, then a copy by the host.  lb_diagnostics of
+// 32^2, us alone / behind 10 / 50 steps: a pageable copy 32 / 41 / 88, one after a wait
+// for the stream 43 / 51 / 88, pinned 25 / 33 / 69; moments of 16^2 (6 KB) 30 / 35 / 49,
+// 39 / 45 / 59 and 20 / 27 / 42; of 32^2 (24 KB) 28 / 36 / 92, 28 / 37 / 68 and 28 / 35 /
+// 78, so larger results wait first.  The block costs 25 us when it is allocated: a
+// lattice that is read once has its pageable copy.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -26,20 +27,24 @@
 
 namespace oreg {
 
-// The pinned memory of one lattice: a block for small results and pieces for
-// larger ones, each allocated by the first copy that takes it and freed with the
-// lattice.  If they cannot be had, copies stay pageable.
+// The pinned memory of one lattice: a block for small results, from the second one
+// on, and pieces for larger ones, each allocated by the first copy that takes it and
+// freed with the lattice.  If they cannot be had, copies stay pageable.
 struct PinnedPieces {
   static constexpr int kPieces = 4;
-  static constexpr size_t kBytes = 1 << 20, kSmall = 32 << 10;
+  static constexpr size_t kBytes = 1 << 20, kSmall = 16 << 10;
   char* base = nullptr;
   hipEvent_t done[kPieces] = {};
   bool refused = false;
   char* small = nullptr;
-  bool small_refused = false;
+  bool small_refused = false, small_read = false;
 
   bool small_ready() {
     if (small || small_refused) return small != nullptr;
+    if (!small_read) {  // the first one
+      small_read = true;
+      return false;
+    }
     if (hipHostMalloc((void**)&small, kSmall, hipHostMallocDefault) == hipSuccess) return true;
     (void)hipGetLastError();  // not an error of the caller's
     small = nullptr;
@@ -86,7 +91,8 @@ class HostTransfer {
   HostTransfer(PinnedPieces& p, hipStream_t s, size_t bytes)
       : p_(p),
         s_(s),
-        small_(bytes <= PinnedPieces::kSmall && p.small_ready()),
+        few_(bytes <= PinnedPieces::kSmall),
+        small_(few_ && p.small_ready()),
         pinned_(bytes >= 1500000 && p.ready()) {}
   ~HostTransfer() {
     if (busy_) (void)hipStreamSynchronize(s_);
@@ -106,8 +112,8 @@ class HostTransfer {
     if (!pinned_) {
       // The runtime waits for the stream by itself, but 25 us longer from seven
       // queued launches on (32^2, 50 steps and moments: 89 us, 66 with the wait
-      // here).
-      const hipError_t e = hipStreamSynchronize(s_);
+      // here), unless there is little to copy.
+      const hipError_t e = few_ ? hipSuccess : hipStreamSynchronize(s_);
       return e != hipSuccess ? e : hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s_);
     }
     busy_ = true;
@@ -150,7 +156,7 @@ class HostTransfer {
 
   PinnedPieces& p_;
   hipStream_t s_;
-  bool small_, pinned_, busy_ = false;
+  bool few_, small_, pinned_, busy_ = false;
   size_t used_ = 0;        // bytes of the small block
   char* first_ = nullptr;  // where they go
   int next_ = 0;

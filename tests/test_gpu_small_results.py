@@ -1,5 +1,6 @@
-"""Results that come back through the pinned block (up to 32 KiB a call) and just
-above it, from calls that follow each other: the same numbers as the device holds."""
+"""Results that come back through the pinned block (up to 16 KiB a call, from the
+second one on) and just above it, from calls that follow each other: the same numbers
+as the device holds."""
 import numpy as np
 import pytest
 
@@ -16,8 +17,9 @@ def lattice(nx, ny):
     return L
 
 
-@pytest.mark.parametrize("nx,ny", [(1, 1), (455, 1), (456, 1), (1365, 1), (1366, 1), (35, 39),
-                                   (4096, 1), (4097, 1)])
+@pytest.mark.parametrize("nx,ny", [(1, 1), (455, 1), (456, 1), (682, 1), (683, 1), (1365, 1),
+                                   (1366, 1), (35, 39), (2048, 1), (2049, 1), (4096, 1),
+                                   (4097, 1)])
 def test_results_around_the_block(nx, ny):
     import torch
     print(f"[small results] {nx}x{ny}", flush=True)

@@ -380,8 +380,9 @@ lb_status lb3_set_populations(lb3_lattice* h, const double* in) {
                               h->stream));
   }
   unsigned int bad = 0;
-  HIP_TRY(h, hipMemcpyAsync(&bad, h->counter, sizeof bad, hipMemcpyDeviceToHost, h->stream));
-  HIP_TRY(h, hipStreamSynchronize(h->stream));
+  HostTransfer count(h->pieces, h->stream, sizeof bad);
+  HIP_TRY(h, count.to_host(&bad, h->counter, sizeof bad));
+  HIP_TRY(h, count.finish());
   if (bad) {
     for (int64_t c = 0; c < n; ++c) {
       double rho = 0.0;

@@ -64,6 +64,7 @@ hipError_t launch_fused_sweep(int eq, int coll, int bc, int st, const void* src,
 struct FusedShape {
   int simds;
   int waves_per_simd;
+  double four;  // gain of four resident workgroups (fused_rows)
 };
 FusedShape fused_shape(int st, int waves, int levels);
 

@@ -480,14 +480,14 @@ inline int64_t launches_for(int64_t n, int64_t m, bool swap, Us&& us, double gai
 // 2048^2 93, 4096^2 336), 0.6, 0.7, 0.8, 1, 1.26, 1.53 and 1.82 while both buffers
 // fit the 256 MB cache, where the steps' arithmetic shows from the first on (1.3, 1.7
 // and 2 for the longest on lattices of a few strips per CU, whose halo rows then
-// weigh more), and 0.9, 0.9, 0.95, 1, 1.2, 1.4 and 1.66 beyond, where
+// weigh more), and 0.9, 0.9, 0.95, 1, 1.2, 1.43 and 1.66 beyond, where
 // memory traffic hides up to four steps.  24 steps in six launches of four, not four of
 // six: 1000^2 6.5 against 6.8 us per step, 900 x 700 5.1 against 5.6 (1448^2 and
 // 1700^2 2 % more).
 inline int64_t number_launches(int64_t n, int K, int64_t nodes, bool swap) {
   static constexpr double kSmall[8] = {0, 0.58, 0.67, 0.8, 1, 1.3, 1.7, 2.0};
   static constexpr double kCached[8] = {0, 0.58, 0.66, 0.79, 1, 1.26, 1.53, 1.82};
-  static constexpr double kStreamed[8] = {0, 0.9, 0.9, 0.94, 1, 1.19, 1.42, 1.66};
+  static constexpr double kStreamed[8] = {0, 0.9, 0.9, 0.94, 1, 1.19, 1.43, 1.66};
   const double* const cost = nodes < 600000 ? kSmall : 80 * nodes < 256000000 ? kCached : kStreamed;
   const int64_t least = (n + K - 1) / K;
   int64_t best = n;

@@ -29,6 +29,8 @@ int main() {
       fail("two launches", n, number_launches(n, 7, 4194304, false), 4194304);
   for (int64_t n : {16, 17, 18})
     if (number_launches(n, 7, 4194304, true) != 3) fail("three launches", n, 0, 4194304);
+  // beyond the cache long calls take as few launches as there are
+  if (number_launches(994, 7, 16777216, false) != 142) fail("sevens", 994, 0, 16777216);
   // in cache a launch of six costs more than 1.5 of four
   if (number_launches(24, 7, 1000000, false) != 6) fail("six launches", 24, 0, 1000000);
   // tile and block launches: us of a launch of L steps

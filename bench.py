@@ -308,7 +308,7 @@ def summarize_counters(paths, n):
         c = mean[k]
         args = [a.strip() for a in k.split("<")[1].rstrip(">").split(",")]
         fused = k.startswith("fused")
-        st = names.get(args[4 if fused else 3], "?")  # <K, eq, coll, bc, storage[, buf]>
+        st = names.get(args[4 if fused else 3], "?")  # <K, eq, coll, bc, storage, ...>
         steps = int(args[0]) if fused else 1
         upd = steps * n * n
 
@@ -374,7 +374,7 @@ def summarize_pmc(fetch_csv, write_csv, n):
             continue  # its readers
         m = re.search(r"fused_sweep_kernel<(\d+)((?:, \w+)*)>", k)
         levels = int(m.group(1)) if m else 1
-        numbers = bool(m) and m.group(2).count(",") == 6 and m.group(2).endswith("true")
+        numbers = bool(m) and m.group(2).count(",") >= 6 and m.group(2).endswith("true")
         st = next((name for tag, name in sts.items() if tag in k), None)
         if st is None or k not in write:
             continue

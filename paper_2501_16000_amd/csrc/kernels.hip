@@ -461,7 +461,7 @@ hipError_t launch_fused_sweep(int eq, int coll, int bc, int st, const void* src,
 }
 
 FusedShape fused_shape(int st, int waves, int levels) {
-  FusedShape sh{0, 0, st == LB_F32S ? 1.75 : 1.87};
+  FusedShape sh{0, 0, st == LB_BF16S ? 1.87 : 1.75};
   int dev = 0, cus = 0, blocks = 0;
   if (hipGetDevice(&dev) != hipSuccess) return sh;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
@@ -495,11 +495,12 @@ int fused_rows(int waves, int nx, int ny, const FusedShape& sh, int levels) {
   // One wavefront per SIMD already runs a wavefront's own strip near the SIMD's
   // issue limit (measured: a second one adds 6-11 %); wavefronts that share a
   // strip wait for each other, and a second workgroup adds 52 %, a third 75 % (F32S,
-  // 4096^2 in 411, 138 and 105 rows: 139, 64.5 and 65.3 us per step), a fourth 87 %
-  // (BF16S, 6001 x 3000 in 102 and 75 rows: 69.0 and 64.8; 4096^2 in 93 and 69:
-  // 63.6 and 59.7).  In F32S a fourth gains that with one lattice only (4096^2, 60
-  // steps, in 93 and 69 rows: 3930 and 3790 us, three in flight 3313 and 3339), so
-  // strips stay as for three.  A launch takes about w wavefront-times by that rate, w = ceil(work items / SIMDs), and one wavefront's time
+  // 4096^2 in 411, 138 and 105 rows: 139, 64.5 and 65.3 us per step).  In BF16S a
+  // fourth makes it 87 % (4096^2 in 93 and 69 rows: 64.2 and 60.8, three lattices in
+  // flight 55.9 and 56.2; 6001 x 3000 in 102 and 75: 70.0 and 65.5, 59.7 and 60.2;
+  // strips of one wavefront 62.9 and 61.5, 68.6 and 66.6).  F32S and F16S gain less by
+  // it than three in flight lose (4096^2 F32S, 60 steps: 3930 and 3790 us, 3313 and
+  // 3339; F16S 57.0 and 56.4, 3000 x 6001 three in flight 56.5 and 57.4).  A launch takes about w wavefront-times by that rate, w = ceil(work items / SIMDs), and one wavefront's time
   // follows its row collisions, K (H + 2K) - K (K + 1), plus a start-up of
   // about 2K.  H (a multiple of 3) minimises the modelled launch time.
   const int hmax = ny < 3 * 1024 ? (ny + 2) / 3 * 3 : 3 * 1024;

@@ -429,11 +429,16 @@ lb_status lb_step(lb_lattice* h, int64_t n) {
     // launches of lattices that leave CUs idle have to be clearly cheaper: they take
     // the CUs of other lattices in flight (24 steps in four launches / two, one
     // lattice and three in flight: 128^2 26.9 / 24.5 us and 15.6 / 22.3, 200 x 300 39.8 /
-    // 41.3 and 20.9 / 36.7; F32S 128^2 25.8 / 21.8 and 15.7 / 11.9).
+    // 41.3 and 20.9 / 36.7; F32S 128^2 25.8 / 21.8 and 15.7 / 11.9).  On lattices of a
+    // few rows or columns the model flatters long launches (42 steps, one more / one
+    // fewer, us per step: F32S 14 x 32143 2.56 / 3.12, 400001 x 2 3.35 / 3.74).
     const double single = 2.5 + 18 * (double)h->elem * h->geo.plane / 5e6;  // us of a sweep at 5 TB/s
-    int64_t launches = launches_for(n, (n + h->best.levels - 1) / h->best.levels, swap, [&](int L) {
+    const double gain = std::min(h->geo.nx, h->geo.ny) <= 36 ? 0
+                        : h->opt.storage == LB_F64 && h->geo.plane < 262144 ? 0.9 : 1;
+    auto us = [&](int L) {
       return L == 1 ? single : L <= kPlanLevels && has_plan(L) ? step_plan(h, L).us : -1.0;
-    }, h->opt.storage == LB_F64 && h->geo.plane < 262144 ? 0.9 : 1);
+    };
+    int64_t launches = launches_for(n, (n + h->best.levels - 1) / h->best.levels, swap, us, gain);
     for (; left > launches; --launches) {
       const int L = (int)((left + launches - 1) / launches);
       if (!has_plan(L)) break;

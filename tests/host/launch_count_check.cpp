@@ -43,6 +43,9 @@ int main() {
   auto even = [](int L) { return 10.0 + 2 * L; };  // one of twelve 34, three of four 54
   if (launches_for(12, 2, true, even, 0.63) != 1 || launches_for(12, 2, true, even, 0.62) != 3)
     fail("clearly cheaper", 12, 0, 0);
+  if (launches_for(7, 2, true, cheap, 0) != 3 || launches_for(9, 1, false, cheap, 0) != 2 ||
+      launches_for(2, 2, true, cheap, 0) != 1)
+    fail("never fewer", 7, 0, 0);
   if (launches_for(12, 2, false, dear) != 2 || launches_for(2, 2, true, cheap) != 1 ||
       launches_for(9, 1, false, cheap) != 2)
     fail("ends", 0, 0, 0);
